@@ -75,46 +75,25 @@ __device__ __forceinline__ double wave_sum(double v) {
 }
 
 // Loads rows row0..row0+3 of one operand column (Q or a dense Theta) into av; rows at or
-// beyond n read as zero.  `vec`: the column pointer is 32-byte aligned for every group.
+// beyond n read as zero.  `full`: all four rows lie below n.
 template <typename TA>
-__device__ __forceinline__ void load_col4(const TA* q, bool vec, bool full, int64_t row0, int64_t n,
-                                          double av[4]) {
-    if (vec && full) {
-        if constexpr (sizeof(TA) == 8) {
-            const double2 v0 = *reinterpret_cast<const double2*>(q);
-            const double2 v1 = *reinterpret_cast<const double2*>(q + 2);
-            av[0] = v0.x;
-            av[1] = v0.y;
-            av[2] = v1.x;
-            av[3] = v1.y;
-        } else {
-            const float4 v = *reinterpret_cast<const float4*>(q);
-            av[0] = v.x;
-            av[1] = v.y;
-            av[2] = v.z;
-            av[3] = v.w;
-        }
+__device__ __forceinline__ void load_col4(const TA* q, bool full, int64_t row0, int64_t n, double (&av)[4]) {
+    if (full) {
+        load4(q, av);
     } else {
 #pragma unroll
         for (int u = 0; u < 4; ++u) av[u] = (row0 + u < n) ? ldv(q + u) : 0.0;
     }
 }
 
-// Rows row0..row0+R-1 of one column (zero at or beyond n); `vec`: R == 2 and the column
-// start and leading dimension allow 2-element vector accesses.
+// Rows row0..row0+R-1 of one column (zero at or beyond n).
 template <int R, typename T>
-__device__ __forceinline__ void load_rows(const T* col, bool vec, int64_t row0, int64_t n, double v[R]) {
+__device__ __forceinline__ void load_rows(const T* col, int64_t row0, int64_t n, double v[R]) {
     if constexpr (R == 2) {
-        if (vec && row0 + 1 < n) {
-            if constexpr (sizeof(T) == 8) {
-                const double2 p = *reinterpret_cast<const double2*>(col + row0);
-                v[0] = p.x;
-                v[1] = p.y;
-            } else {
-                const float2 p = *reinterpret_cast<const float2*>(col + row0);
-                v[0] = p.x;
-                v[1] = p.y;
-            }
+        if (row0 + 1 < n) {
+            const RawRows<2, T> p = load_raw<2>(col + row0);
+            v[0] = p.v[0];
+            v[1] = p.v[1];
             return;
         }
     }
@@ -123,25 +102,17 @@ __device__ __forceinline__ void load_rows(const T* col, bool vec, int64_t row0, 
 }
 
 template <int R, typename T>
-__device__ __forceinline__ void store_rows(T* col, bool vec, int64_t row0, int64_t n, const double v[R]) {
+__device__ __forceinline__ void store_rows(T* col, int64_t row0, int64_t n, const double v[R]) {
     if constexpr (R == 2) {
-        if (vec && row0 + 1 < n) {
-            if constexpr (sizeof(T) == 8) {
-                *reinterpret_cast<double2*>(col + row0) = double2{v[0], v[1]};
-            } else {
-                *reinterpret_cast<float2*>(col + row0) = float2{static_cast<float>(v[0]), static_cast<float>(v[1])};
-            }
+        if (row0 + 1 < n) {
+            typedef typename Unaligned<T>::v2 V;
+            *reinterpret_cast<V*>(col + row0) = V{static_cast<T>(v[0]), static_cast<T>(v[1])};
             return;
         }
     }
 #pragma unroll
     for (int r = 0; r < R; ++r)
         if (row0 + r < n) stv(col + row0 + r, v[r]);
-}
-
-template <typename T>
-__device__ __forceinline__ bool pair_aligned(const void* p, int64_t ld) {
-    return p == nullptr || (((uintptr_t)p % (2 * sizeof(T))) == 0 && (ld % 2) == 0);
 }
 
 // Element types of a pass: TY the input block Y, TQ the basis operand (Qu of the update,
@@ -191,8 +162,20 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
     // triangular factors (W x W, column-major) and update coefficients (pu x W)
     const CD gR0[2] = {as_uniform(a.R1), as_uniform(a.R2)};
     const CD gC0 = as_uniform(a.Cu);
-    double rinv[NTRSM > 0 ? NTRSM * W : 1];
-    if constexpr (NTRSM > 0) {
+    // their diagonals' reciprocals: in registers, or for wide blocks in LDS, read again per
+    // strip (two solves of 11 columns would hold 44 registers of them for the whole sweep:
+    // 144 against 101 VGPRs, 3 against 4 waves, for the FP32 solve + projection on 64 columns,
+    // 0.88 against 0.79 ms at 2^24 rows)
+    constexpr bool RINV_LDS = NTRSM > 0 && W >= 9;
+    __shared__ double srinv[RINV_LDS ? NTRSM * W : 1];
+    double rinv[NTRSM > 0 && !RINV_LDS ? NTRSM * W : 1];
+    if constexpr (RINV_LDS) {
+        for (int i = tid; i < NTRSM * W; i += NT) {
+            const int t = i / W, c = i - t * W;
+            srinv[i] = 1.0 / (t == 0 ? a.R1 : a.R2)[c * W + c];
+        }
+        __syncthreads();
+    } else if constexpr (NTRSM > 0) {
 #pragma unroll
         for (int t = 0; t < NTRSM; ++t)
 #pragma unroll
@@ -257,9 +240,6 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
         }
     }
 
-    // 2-row vector accesses need every tall operand's column starts 2-element aligned
-    const bool vec = RPT == 2 && pair_aligned<TY>(a.Y, a.ldy) && (!UPD || pair_aligned<TQ>(a.Qu, a.ldqu)) &&
-                     (!WRITE || pair_aligned<TX>(a.X, a.ldx));
     const int64_t nstrips = (n + STRIP - 1) / STRIP;
     for (int64_t s = wg; s < nstrips; s += nwg) {
         const int64_t base = s * STRIP;
@@ -272,6 +252,13 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
             gR[1] = per_strip(gR[1]);
             gC = per_strip(gC);
         }
+        const int ri0 = RINV_LDS ? per_strip(0) : 0;
+        auto rdiag = [&](int i) {
+            if constexpr (RINV_LDS)
+                return srinv[ri0 + i];
+            else
+                return rinv[i];
+        };
         // ---------------- phase A: RPT consecutive rows per thread ----------------
         if constexpr (RPT == 1)
         {
@@ -291,7 +278,7 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
                         double v = x[c];
 #pragma unroll
                         for (int q = 0; q < c; ++q) v -= x[q] * R[q + c * W];
-                        x[c] = v * rinv[t * W + c];
+                        x[c] = v * rdiag(t * W + c);
                     }
                 }
                 if constexpr (WRITE) {
@@ -319,47 +306,22 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
 #pragma unroll
                 for (int c = 0; c < W; ++c) {
                     double v[RPT];
-                    load_rows<RPT>(Y + (int64_t)c * a.ldy, vec, row0, n, v);
+                    load_rows<RPT>(Y + (int64_t)c * a.ldy, row0, n, v);
 #pragma unroll
                     for (int r = 0; r < RPT; ++r) x[r][c] = v[r];
                 }
                 if constexpr (UPD) {
-                  if (vec && row0 + RPT - 1 < n) {
-                    update_rows<W, RPT, TQ>(x, static_cast<const TQ*>(a.Qu) + row0, a.ldqu, a.pu, gC);
-                  } else {
-                    const TQ* Q = static_cast<const TQ*>(a.Qu);
-                    const int pu = a.pu;
-                    int j = 0;
-                    for (; j + 4 <= pu; j += 4) {
-                        double q[4][RPT];
+                    // the last row alone (an odd n) updates its single row
+                    if (row0 + RPT - 1 < n) {
+                        update_rows<W, RPT, TQ>(x, static_cast<const TQ*>(a.Qu) + row0, a.ldqu, a.pu, gC);
+                    } else {
+                        const TQ* Q = static_cast<const TQ*>(a.Qu) + row0;
+                        for (int j = 0; j < a.pu; ++j) {
+                            const double q = ldv(Q + (int64_t)j * a.ldqu);
 #pragma unroll
-                        for (int u = 0; u < 4; ++u) load_rows<RPT>(Q + (int64_t)(j + u) * a.ldqu, vec, row0, n, q[u]);
-#pragma unroll
-                        for (int c = 0; c < W; ++c) {
-                            const double c0 = gC[j + 0 + c * pu], c1 = gC[j + 1 + c * pu];
-                            const double c2 = gC[j + 2 + c * pu], c3 = gC[j + 3 + c * pu];
-#pragma unroll
-                            for (int r = 0; r < RPT; ++r) {
-                                double v = x[r][c];
-                                v -= q[0][r] * c0;
-                                v -= q[1][r] * c1;
-                                v -= q[2][r] * c2;
-                                v -= q[3][r] * c3;
-                                x[r][c] = v;
-                            }
+                            for (int c = 0; c < W; ++c) x[0][c] -= q * gC[j + c * a.pu];
                         }
                     }
-                    for (; j < pu; ++j) {
-                        double q[RPT];
-                        load_rows<RPT>(Q + (int64_t)j * a.ldqu, vec, row0, n, q);
-#pragma unroll
-                        for (int c = 0; c < W; ++c) {
-                            const double cj = gC[j + c * pu];
-#pragma unroll
-                            for (int r = 0; r < RPT; ++r) x[r][c] -= q[r] * cj;
-                        }
-                    }
-                  }
                 }
 #pragma unroll
                 for (int t = 0; t < NTRSM; ++t) {
@@ -371,7 +333,7 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
                             double v = x[r][c];
 #pragma unroll
                             for (int q = 0; q < c; ++q) v -= x[r][q] * R[q + c * W];
-                            x[r][c] = v * rinv[t * W + c];
+                            x[r][c] = v * rdiag(t * W + c);
                         }
                     }
                 }
@@ -382,7 +344,7 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
                         double v[RPT];
 #pragma unroll
                         for (int r = 0; r < RPT; ++r) v[r] = x[r][c];
-                        store_rows<RPT>(X + (int64_t)c * a.ldx, vec, row0, n, v);
+                        store_rows<RPT>(X + (int64_t)c * a.ldx, row0, n, v);
                     }
                 }
                 // rows past n (a partial last pair) contribute zero to the reduction
@@ -511,11 +473,6 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
                 const int g = lane >> 4, ci = lane & 15;
                 const TQ* Qp = static_cast<const TQ*>(a.Qp);
                 const double* Th = a.theta;
-                // 32-byte row pieces can be read as two 16-byte vectors when aligned
-                bool vec = false;
-                if constexpr (RED == RED_PROJ)
-                    vec = (a.ldqp % 4) == 0 && ((uintptr_t)Qp % (4 * sizeof(TQ))) == 0;
-                if constexpr (RED == RED_SKETCH_DENSE) vec = (a.ldtheta % 4) == 0 && ((uintptr_t)Th % 32) == 0;
                 // rows per group: 16 (4 per lane), or 32 (8 per lane) for projections against an
                 // FP32 basis on 4 x 4 x 4 blocks: a 4-byte piece load moves half the bytes of a
                 // double one, so each lane loads two per column, as many bytes in flight as the
@@ -531,7 +488,7 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
                 for (int gam = g0, it = 0; it < GPW; gam += gstep, ++it) {
                     const int r0 = gam * GR + UR * g;  // strip-local rows r0..r0+UR-1 for this lane
                     const bool full = base + r0 + 3 < n;
-                    const bool full2 = base + r0 + UR - 1 < n;
+                    const bool gfull = base + (gam + 1) * GR <= n;  // the whole group lies below n
                     // B operands: 16 x 16 x 4 tiles take column ci of the 4 rows; 4 x 4 x 4 blocks
                     // take column 4cb + lane % 4
                     double bv[B4 ? 1 : 4];
@@ -552,20 +509,21 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
                         if (m < ntiles) {
                             const int col = 16 * m + ci;
                             if constexpr (UR == 8) {
-                                // the 8 pieces stay in float until their MFMA
-                                float af[8];
+                                // the 8 pieces stay in float until their MFMA; a lane past the last
+                                // output row reads that row's column (its own row is never written)
+                                typedef Unaligned<float>::v4 V4;
+                                const float* qc = reinterpret_cast<const float*>(Qp) +
+                                                  (int64_t)(col < a.red_rows ? col : a.red_rows - 1) * a.ldqp + base + r0;
+                                V4 v0, v1;
+                                if (gfull) {
+                                    v0 = *reinterpret_cast<const V4*>(qc);
+                                    v1 = *reinterpret_cast<const V4*>(qc + 4);
+                                } else {
+                                    const int64_t rr = base + r0;
 #pragma unroll
-                                for (int u = 0; u < 8; ++u) af[u] = 0.0f;
-                                if (col < a.red_rows) {
-                                    const float* qc = reinterpret_cast<const float*>(Qp) + (int64_t)col * a.ldqp + base + r0;
-                                    if (vec && full2) {
-                                        const float4 v0 = *reinterpret_cast<const float4*>(qc);
-                                        const float4 v1 = *reinterpret_cast<const float4*>(qc + 4);
-                                        af[0] = v0.x; af[1] = v0.y; af[2] = v0.z; af[3] = v0.w;
-                                        af[4] = v1.x; af[5] = v1.y; af[6] = v1.z; af[7] = v1.w;
-                                    } else {
-#pragma unroll
-                                        for (int u = 0; u < 8; ++u) af[u] = (base + r0 + u < n) ? qc[u] : 0.0f;
+                                    for (int u = 0; u < 4; ++u) {
+                                        v0[u] = (rr + u < n) ? qc[u] : 0.0f;
+                                        v1[u] = (rr + 4 + u < n) ? qc[4 + u] : 0.0f;
                                     }
                                 }
 #pragma unroll
@@ -573,15 +531,16 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
 #pragma unroll
                                     for (int cb = 0; cb < CB; ++cb)
                                         acc4[m * CB + cb] = __builtin_amdgcn_mfma_f64_4x4x4f64(
-                                            (double)af[u], (double)bq[cb][u], acc4[m * CB + cb], 0, 0, 0);
+                                            (double)(u < 4 ? v0[u & 3] : v1[u & 3]), (double)bq[cb][u], acc4[m * CB + cb],
+                                            0, 0, 0);
                                 continue;
                             }
                             double av[4] = {0.0, 0.0, 0.0, 0.0};
                             if (col < a.red_rows) {
                                 if constexpr (RED == RED_PROJ)
-                                    load_col4(Qp + (int64_t)col * a.ldqp + base + r0, vec, full, base + r0, n, av);
+                                    load_col4(Qp + (int64_t)col * a.ldqp + base + r0, full, base + r0, n, av);
                                 else
-                                    load_col4(Th + (int64_t)col * a.ldtheta + base + r0, vec, full, base + r0, n, av);
+                                    load_col4(Th + (int64_t)col * a.ldtheta + base + r0, full, base + r0, n, av);
                             }
                             if constexpr (B4) {
 #pragma unroll
@@ -716,8 +675,21 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
     }
 }
 
+// Waves per SIMD the register allocation must leave room for (1: no demand).  Float-storage
+// projections and plain sketches of up to 12 columns sit a few registers above a limit when
+// left alone, and the lost wave costs up to 20 % (11 columns on 128 rows of Q with two solves,
+// n = 2^24: 2.46 ms with 184 VGPRs and two waves, 2.00 ms now).
+template <int W, typename T, int RED, bool UPD, int NTRSM, int MTX>
+constexpr int min_waves() {
+    constexpr int MT = MTX > 0 ? MTX : Cfg<W, RED>::MT;
+    if (sizeof(T) != 4 || W > 12) return 1;
+    if (RED == RED_PROJ && W >= 9) return MT == 8 ? (NTRSM > 0 ? 3 : 4) : MT == 4 && NTRSM == 0 ? 5 : 1;
+    if (RED == RED_SKETCH_SPARSE && !UPD) return MT == 4 ? (W <= 6 ? 6 : W <= 9 ? 5 : 1) : (W <= 10 ? 4 : 1);
+    return 1;
+}
+
 template <int W, typename T, int RED, bool UPD, int NTRSM, bool WRITE, int MTX = 0>
-__global__ void __launch_bounds__((Cfg<W, RED>::NT)) pass_kernel(const PassArgs a) {
+__global__ void __launch_bounds__((Cfg<W, RED>::NT), (min_waves<W, T, RED, UPD, NTRSM, MTX>())) pass_kernel(const PassArgs a) {
     pass_body<W, Tys<T, T, T>, RED, UPD, NTRSM, WRITE, MTX>(a, blockIdx.x, gridDim.x);
 }
 
@@ -729,7 +701,7 @@ __global__ void __launch_bounds__((Cfg<W, RED>::NT)) pass_kernel_panel(const Pas
 
 // Batched form: the template arguments are moved to the system of blockIdx.y.
 template <int W, typename T, int RED, bool UPD, int NTRSM, bool WRITE, int MTX = 0>
-__global__ void __launch_bounds__((Cfg<W, RED>::NT)) pass_kernel_batched(const PassArgs t, const BatchReloc br) {
+__global__ void __launch_bounds__((Cfg<W, RED>::NT), (min_waves<W, T, RED, UPD, NTRSM, MTX>())) pass_kernel_batched(const PassArgs t, const BatchReloc br) {
     const int sys = batch_system(br);
     const BatchSys& d = br.sys[sys];
     PassArgs a = t;

@@ -110,27 +110,12 @@ struct GemmArgs {
 
 // Rows row0..row0+3 of one column into v (zero past n or for a column past the block).
 template <typename T>
-__device__ __forceinline__ void load_piece(const T* col, bool live, bool vec, int64_t row0, int64_t n, double v[4]) {
-    if (!live) {
-        v[0] = v[1] = v[2] = v[3] = 0.0;
-    } else if (vec && row0 + 3 < n) {
-        if constexpr (sizeof(T) == 8) {
-            const double2 p0 = *reinterpret_cast<const double2*>(col + row0);
-            const double2 p1 = *reinterpret_cast<const double2*>(col + row0 + 2);
-            v[0] = p0.x;
-            v[1] = p0.y;
-            v[2] = p1.x;
-            v[3] = p1.y;
-        } else {
-            const float4 p = *reinterpret_cast<const float4*>(col + row0);
-            v[0] = p.x;
-            v[1] = p.y;
-            v[2] = p.z;
-            v[3] = p.w;
-        }
+__device__ __forceinline__ void load_piece(const T* col, bool live, int64_t row0, int64_t n, double (&v)[4]) {
+    if (live && row0 + 3 < n) {
+        load4(col + row0, v);
     } else {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = (row0 + u < n) ? ldv(col + row0 + u) : 0.0;
+        for (int u = 0; u < 4; ++u) v[u] = (live && row0 + u < n) ? ldv(col + row0 + u) : 0.0;
     }
 }
 
@@ -140,47 +125,24 @@ __device__ __forceinline__ void load_piece(const T* col, bool live, bool vec, in
 // flight together.  A branch per piece would wait for each load in turn.  The group at the
 // end of the rows keeps the guarded loads.
 template <typename T, int NTL>
-__device__ __forceinline__ void load_pieces(const T* base, int64_t ld, int m, int ci, bool vec, bool full,
-                                            int64_t row0, int64_t n, double (&v)[NTL][4]) {
-    if (full && vec) {
+__device__ __forceinline__ void load_pieces(const T* base, int64_t ld, int m, int ci, bool full, int64_t row0,
+                                            int64_t n, double (&v)[NTL][4]) {
+    if (full) {
 #pragma unroll
         for (int t = 0; t < NTL; ++t) {
             const int c = 16 * t + ci;
-            const T* col = base + (int64_t)(c < m ? c : m - 1) * ld;
-            if constexpr (sizeof(T) == 8) {
-                const double2 p0 = *reinterpret_cast<const double2*>(col + row0);
-                const double2 p1 = *reinterpret_cast<const double2*>(col + row0 + 2);
-                v[t][0] = p0.x;
-                v[t][1] = p0.y;
-                v[t][2] = p1.x;
-                v[t][3] = p1.y;
-            } else {
-                const float4 p = *reinterpret_cast<const float4*>(col + row0);
-                v[t][0] = p.x;
-                v[t][1] = p.y;
-                v[t][2] = p.z;
-                v[t][3] = p.w;
-            }
+            load4(base + (int64_t)(c < m ? c : m - 1) * ld + row0, v[t]);
         }
-    } else if (full) {
 #pragma unroll
-        for (int t = 0; t < NTL; ++t) {
-            const int c = 16 * t + ci;
-            const T* col = base + (int64_t)(c < m ? c : m - 1) * ld;
-#pragma unroll
-            for (int u = 0; u < 4; ++u) v[t][u] = ldv(col + row0 + u);
-        }
+        for (int t = 0; t < NTL; ++t)
+            if (16 * t + ci >= m) v[t][0] = v[t][1] = v[t][2] = v[t][3] = 0.0;
     } else {
 #pragma unroll
         for (int t = 0; t < NTL; ++t) {
             const int c = 16 * t + ci;
-            load_piece(base + (int64_t)(c < m ? c : 0) * ld, c < m, vec, row0, n, v[t]);
+            load_piece(base + (int64_t)(c < m ? c : 0) * ld, c < m, row0, n, v[t]);
         }
-        return;
     }
-#pragma unroll
-    for (int t = 0; t < NTL; ++t)
-        if (16 * t + ci >= m) v[t][0] = v[t][1] = v[t][2] = v[t][3] = 0.0;
 }
 
 }  // namespace wide

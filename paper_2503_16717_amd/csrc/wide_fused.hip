@@ -67,7 +67,6 @@ __device__ __forceinline__ void rowop_red_body(const FusedArgs& fa, const int wg
         __syncthreads();
     }
     const CD R0 = as_uniform(ra.Rpk), C0 = as_uniform(ra.Cu);
-    const bool vece = !GRAM && (fa.lde % 4) == 0 && ((uintptr_t)E % (4 * sizeof(T))) == 0;
     double* st = stage + wave * SW;
     double4_t acc[TA][TX];
 #pragma unroll
@@ -107,7 +106,7 @@ __device__ __forceinline__ void rowop_red_body(const FusedArgs& fa, const int wg
             double ea[GRAM ? 1 : TA][4];
             if constexpr (!GRAM) {
                 const int64_t crow = wrow0 + 16 * q;
-                load_pieces<T, TA>(E, fa.lde, fa.me, ci, vece, crow + 16 <= n, crow + 4 * g, n, ea);
+                load_pieces<T, TA>(E, fa.lde, fa.me, ci, crow + 16 <= n, crow + 4 * g, n, ea);
             }
             if (g == q) {
 #pragma unroll

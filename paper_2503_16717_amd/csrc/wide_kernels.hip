@@ -105,9 +105,6 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& ga) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int ci = lane & 15, g = lane >> 4;
     constexpr int NW = GT / 64;
-    // 4-row pieces can be read as vectors when every column start is aligned
-    const bool veca = (ga.lda % 4) == 0 && ((uintptr_t)A % (4 * sizeof(T))) == 0;
-    const bool vecb = (ga.ldb % 4) == 0 && ((uintptr_t)B % (4 * sizeof(T))) == 0;
     double4_t acc[TA][TB];
 #pragma unroll
     for (int i = 0; i < TA; ++i)
@@ -119,8 +116,8 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& ga) {
         const int64_t row0 = grp * 16 + 4 * g;
         const bool full = grp * 16 + 16 <= n;
         double a[TA][4], b[SYM ? 1 : TB][4];
-        load_pieces<T, TA>(A, ga.lda, ma, ci, veca, full, row0, n, a);
-        if constexpr (!SYM) load_pieces<T, TB>(B, ga.ldb, nb, ci, vecb, full, row0, n, b);
+        load_pieces<T, TA>(A, ga.lda, ma, ci, full, row0, n, a);
+        if constexpr (!SYM) load_pieces<T, TB>(B, ga.ldb, nb, ci, full, row0, n, b);
         // row step outermost: consecutive MFMAs go to different accumulator tiles
 #pragma unroll
         for (int u = 0; u < 4; ++u)
