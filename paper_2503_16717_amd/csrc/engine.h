@@ -148,6 +148,12 @@ struct Engine {
             rows_bytes * (A == B ? ma : ma + nbc) * (f32 ? 4.0 : 8.0));
         SKO_HIP(launch_skinny_gemm_tn(n, A, lda, ma, B, ldb, nbc, f32, partials, G, st, br));
         pend(ev);
+        return wide_reduce(small, ma, nbc, G, ldo, kGemmUnitRows);
+    }
+
+    // Sum the ma x nbc partials of G workgroups (unit_rows rows per workgroup index) into
+    // `small`, placed with leading dimension ldo.
+    sko_status wide_reduce(SmallArgs small, int ma, int nbc, int G, int64_t ldo, int unit_rows) {
         ReduceArgs ra{};
         ra.partials = partials;
         ra.stride = (int64_t)ma * nbc;
@@ -159,23 +165,32 @@ struct Engine {
         ra.ldo = ldo;
         ra.small = small;
         ra.small.status = status;
-        ra.unit_rows = kGemmUnitRows;
-        const int ev2 = pbegin([&] { return std::string(reduce_name(small.op)); }, 8.0 * G * ra.count);
+        ra.unit_rows = unit_rows;
+        const int ev = pbegin([&] { return std::string(reduce_name(small.op)); }, 8.0 * G * ra.count);
         SKO_HIP(launch_reduce(ra, st, br));
-        pend(ev2);
+        pend(ev);
         return SKO_OK;
     }
 
     // X = (Y - Qu Cu) R^{-1} (rowop) and, in the same sweep over X, C = E^T X (E: me <= 64
     // tall columns, solve only) or the Gram X^T X (E null), reduced into `small` as
-    // gemm_reduction does.  Panels wider than kFusedMaxW keep the two sweeps apart (the row
-    // and the accumulators no longer fit two waves' registers), and so do projections on more
-    // than 48 columns and the update form: its Q_u loads and the MFMA accumulators together
-    // run slower than two sweeps (measured 5.4-5.6 ms against 4.3 ms, 36 columns on 36,
-    // n = 2^24, with four or eight update columns in flight).
+    // gemm_reduction does.  An update without a solve takes the MFMA update kernel with its
+    // Gram matrix (36 columns on 36, n = 2^24: %UPD%).  Row solves wider than kFusedMaxW
+    // keep the two sweeps apart (the row and the accumulators no longer fit two waves'
+    // registers), and so do projections on more than 48 columns.
     sko_status rowop_reduction(int Wd, const void* Y, int64_t ldy, const void* Qu, int64_t ldqu, int pu,
                                const double* Cu, const double* Rpk, void* X, int64_t ldx, const void* E, int64_t lde,
                                int me, SmallArgs small, int64_t ldo) {
+        if (pu > 0 && !Rpk && !E && wide_update_fits(Wd, pu, true)) {
+            int G = br ? (int)std::max<int64_t>(1, std::min<int64_t>(gemm_grid(true, Wd, Wd),
+                                                                     (n + kUpdateUnitRows - 1) / kUpdateUnitRows))
+                       : 0;
+            const int ev = pbegin([&] { return std::string("wide_update+gram f") + (f32 ? "32" : "64"); },
+                                  rows_bytes * (2 * Wd + pu) * (f32 ? 4.0 : 8.0));
+            SKO_HIP(launch_wide_update(n, Wd, f32, Y, ldy, Qu, ldqu, pu, Cu, X, ldx, partials, &G, st, br));
+            pend(ev);
+            return wide_reduce(small, Wd, Wd, G, ldo, kUpdateUnitRows);
+        }
         if (pu > 0 || Wd > kFusedMaxW || (E && me > 48)) {
             sko_status s = rowop(Wd, Y, ldy, Qu, ldqu, pu, Cu, Rpk, X, ldx);
             if (s) return s;
@@ -196,22 +211,7 @@ struct Engine {
         SKO_HIP(launch_wide_rowop_reduce(n, Wd, f32, Y, ldy, Qu, ldqu, pu, Cu, Rpk, X, ldx, E, lde, me, partials, &G,
                                          st, br));
         pend(ev);
-        ReduceArgs ra{};
-        ra.partials = partials;
-        ra.stride = (int64_t)ma * Wd;
-        ra.G = G;
-        ra.count = ma * Wd;
-        ra.scale = 1.0;
-        ra.counter = counter;
-        ra.rows = ma;
-        ra.ldo = ldo;
-        ra.small = small;
-        ra.small.status = status;
-        ra.unit_rows = kFusedUnitRows;
-        const int ev2 = pbegin([&] { return std::string(reduce_name(small.op)); }, 8.0 * G * ra.count);
-        SKO_HIP(launch_reduce(ra, st, br));
-        pend(ev2);
-        return SKO_OK;
+        return wide_reduce(small, ma, Wd, G, ldo, kFusedUnitRows);
     }
 
     // Rpk: the triangular factor packed by the Cholesky step that produced it (SmallArgs::Rpk)
@@ -222,7 +222,13 @@ struct Engine {
                 return std::string("wide_rowop f") + (f32 ? "32" : "64") + (pu > 0 ? " upd" : "") + (Rpk ? " trsm" : "");
             },
             rows_bytes * (2 * Wd + pu) * (f32 ? 4.0 : 8.0));
-        SKO_HIP(launch_wide_rowop(n, Wd, f32, Y, ldy, Qu, ldqu, pu, Cu, Rpk, X, ldx, st, br));
+        if (pu > 0 && !Rpk && wide_update_fits(Wd, pu, false)) {
+            // batched: up to 8 units of rows per workgroup, as the row operation takes strips
+            int G = (int)((n + 8 * kUpdateUnitRows - 1) / (8 * kUpdateUnitRows));
+            SKO_HIP(launch_wide_update(n, Wd, f32, Y, ldy, Qu, ldqu, pu, Cu, X, ldx, nullptr, &G, st, br));
+        } else {
+            SKO_HIP(launch_wide_rowop(n, Wd, f32, Y, ldy, Qu, ldqu, pu, Cu, Rpk, X, ldx, st, br));
+        }
         pend(ev);
         return SKO_OK;
     }

@@ -687,6 +687,7 @@ sko_status two_stage_blocks(sko_ctx c, int64_t n, int32_t nb, int32_t w, const v
     const size_t o_Rh = ar.reserve(sizeof(double) * (size_t)Wb * Wb);
     const size_t o_Rt = ar.reserve(sizeof(double) * (size_t)Wb * Wb);
     const size_t o_Rpk = ar.reserve(sizeof(double) * (size_t)Wb * (Wb + 1) / 2);
+    const size_t o_Rbp = ar.reserve(sizeof(double) * (size_t)Wb * (Wb + 1) / 2);
     const size_t o_Rf = ar.reserve(sizeof(double) * (size_t)N * N);
     const size_t o_st = ar.reserve(256);
     sko_status s = ensure_workspace(c, ar.used());
@@ -709,6 +710,7 @@ sko_status two_stage_blocks(sko_ctx c, int64_t n, int32_t nb, int32_t w, const v
     double* Rh = ar.at<double>(o_Rh);
     double* Rt = ar.at<double>(o_Rt);
     double* Rpk = ar.at<double>(o_Rpk);  // packed copy of Rh, then of Rt, for the row solves
+    double* Rbpk = ar.at<double>(o_Rbp);  // packed copy of Rbar
     double* Rfull = ar.at<double>(o_Rf);
     SKO_HIP(launch_zero(e.status, 256, c->stream));
     SKO_HIP(launch_zero(Rfull, sizeof(double) * (size_t)N * N, c->stream));
@@ -721,13 +723,65 @@ sko_status two_stage_blocks(sko_ctx c, int64_t n, int32_t nb, int32_t w, const v
         const int p_old = big * Wb;
         void* Qb = offset_elems(Q, (int64_t)p_old * ldq, f32);
         SKO_HIP(launch_zero(Rbar, sizeof(double) * (size_t)Wb * Wb, c->stream));
-        // ---- first stage: pre-process panel by panel (Fig. 5 Lines 10, 12; Fig. 8)
-        for (int i = 0; i < ppb; ++i) {
+        // ---- first stage, RandBCGS2 (Fig. 5 Lines 10, 12; Fig. 8).  The whole big panel is at
+        // hand, so the steps that a solver runs panel by panel run once over all its columns:
+        // C = Q_old^T V and V_hat = V - Q_old C on Wb columns, the sketch of every panel of V_hat
+        // (the sketch-space orthogonalisation needs nothing but the sketches), and the forward
+        // substitution of all panels as one row solve with Rbar, fused below with the big panel's
+        // Gram matrix.  Per row of an s_hat = 30 big panel of 36 columns that reads and writes
+        // 36 + 72 columns instead of 198 + 36 (first big panel), 72 + 108 + 36 + 72 instead of
+        // 252 + 288 + 198 + 36 (behind one of 36).
+        const void* Vb = offset_elems(V, (int64_t)p_old * ldv, f32);
+        const void* Vh = Vb;  // V_hat of the big panel
+        int64_t ldvh = ldv;
+        if (!pip) {
+            if (p_old > 0) {
+                for (int a0 = 0; a0 < p_old; a0 += 64) {
+                    const int ma = std::min(64, p_old - a0);
+                    SmallArgs sm{};
+                    sm.op = OP_STORE;
+                    sm.w = Wb;
+                    sm.out = C + a0;
+                    if ((s = e.gemm_reduction(offset_elems(Q, (int64_t)a0 * ldq, f32), ldq, ma, Vb, ldv, Wb, sm, p_old)))
+                        return s;
+                }
+                if ((s = e.rowop(Wb, Vb, ldv, Q, ldq, p_old, C, nullptr, Qb, ldq))) return s;
+                Vh = Qb;
+                ldvh = ldq;
+            }
+            for (int i = 0; i < ppb; ++i) {
+                const void* Vi = offset_elems(Vh, (int64_t)i * w * ldvh, f32);
+                PassArgs a{};
+                a.Y = Vi;
+                a.ldy = ldvh;
+                SmallArgs sm{};
+                sm.op = OP_SKETCH_BCGS2;
+                sm.w = w;
+                sm.k = k;
+                sm.col0 = p_old + i * w;
+                sm.out = Ysk;
+                sm.R = rho;
+                sm.Yacc = Yacc;
+                sm.nacc = i * w;
+                sm.r = rt;
+                sm.Rbar = Rbar;
+                sm.ldrbar = Wb;
+                sm.rbar_col0 = i * w;
+                sm.Rbar_pk = Rbpk;
+                sm.rpk_w = Wb;
+                sketch_small(sm, sp);
+                if ((s = e.reduction({w, f32, red_sk, false, 0, false}, a, kr, Vi, ldvh, nullptr, 0, sm, sk_scale)))
+                    return s;
+            }
+        }
+        // ---- first stage, BCGS-PIP, panel by panel (its inner products are those of the
+        // orthonormalised panels before it)
+        for (int i = 0; pip && i < ppb; ++i) {
             const int col = p_old + i * w;
             const void* Vi = offset_elems(V, (int64_t)col * ldv, f32);
             void* Qi = offset_elems(Q, (int64_t)col * ldq, f32);
-            const void* Vh = Vi;
-            int64_t ldvh = ldv;
+            const void* Vhi = Vi;
+            int64_t ldvhi = ldv;
             double* Ci = C + (int64_t)i * w * p_old;
             if (p_old > 0) {
                 PassArgs a{};
@@ -740,90 +794,56 @@ sko_status two_stage_blocks(sko_ctx c, int64_t n, int32_t nb, int32_t w, const v
                 if ((s = e.reduction({w, f32, RED_PROJ, false, 0, false}, a, p_old, Vi, ldv, Q, ldq, sm, 1.0)))
                     return s;
             }
-            if (pip) {
-                // BCGS-PIP (Fig. 7): G = V_hat^T V_hat (fused with the update against Q_old), then
-                // P = Q_bar_prev^T V_hat, R = chol(G - P^T P); the first panel is CholQR.
-                SmallArgs sp_{};
-                sp_.op = OP_PIP;
-                sp_.w = w;
-                sp_.col0 = col;
-                sp_.R = rho;
-                sp_.r = rt;
-                sp_.gram = Gpip;
-                sp_.nacc = i * w;
-                sp_.Rbar = Rbar;
-                sp_.ldrbar = Wb;
-                sp_.rbar_col0 = i * w;
-                SmallArgs sg{};
-                sg.op = OP_STORE;
-                sg.w = w;
-                sg.out = Gpip;
-                PassArgs a{};
-                a.Y = Vi;
-                a.ldy = ldv;
-                PassKey key{w, f32, RED_GRAM, false, 0, false};
-                if (p_old > 0) {
-                    key.upd = true;
-                    key.write = true;
-                    a.Qu = Q;
-                    a.ldqu = ldq;
-                    a.pu = p_old;
-                    a.Cu = Ci;
-                    a.X = Qi;
-                    a.ldx = ldq;
-                    Vh = Qi;
-                    ldvh = ldq;
-                }
-                if (i == 0) {
-                    sp_.out = Ysk;
-                    if ((s = e.reduction(key, a, w, nullptr, 0, nullptr, 0, sp_, 1.0))) return s;
-                } else {
-                    if ((s = e.reduction(key, a, w, nullptr, 0, nullptr, 0, sg, 1.0))) return s;
-                    PassArgs pa{};
-                    pa.Y = Vh;
-                    pa.ldy = ldvh;
-                    sp_.out = Ysk;
-                    if ((s = e.reduction({w, f32, RED_PROJ, false, 0, false}, pa, i * w, Vh, ldvh, Qb, ldq, sp_,
-                                         1.0)))
-                        return s;
-                }
+            // BCGS-PIP (Fig. 7): G = V_hat^T V_hat (fused with the update against Q_old), then
+            // P = Q_bar_prev^T V_hat, R = chol(G - P^T P); the first panel is CholQR.
+            SmallArgs sp_{};
+            sp_.op = OP_PIP;
+            sp_.w = w;
+            sp_.col0 = col;
+            sp_.R = rho;
+            sp_.r = rt;
+            sp_.gram = Gpip;
+            sp_.nacc = i * w;
+            sp_.Rbar = Rbar;
+            sp_.ldrbar = Wb;
+            sp_.rbar_col0 = i * w;
+            SmallArgs sg{};
+            sg.op = OP_STORE;
+            sg.w = w;
+            sg.out = Gpip;
+            PassArgs a{};
+            a.Y = Vi;
+            a.ldy = ldv;
+            PassKey key{w, f32, RED_GRAM, false, 0, false};
+            if (p_old > 0) {
+                key.upd = true;
+                key.write = true;
+                a.Qu = Q;
+                a.ldqu = ldq;
+                a.pu = p_old;
+                a.Cu = Ci;
+                a.X = Qi;
+                a.ldx = ldq;
+                Vhi = Qi;
+                ldvhi = ldq;
+            }
+            if (i == 0) {
+                sp_.out = Ysk;
+                if ((s = e.reduction(key, a, w, nullptr, 0, nullptr, 0, sp_, 1.0))) return s;
             } else {
-                PassArgs a{};
-                a.Y = Vi;
-                a.ldy = ldv;
-                PassKey key{w, f32, red_sk, false, 0, false};
-                if (p_old > 0) {
-                    key.upd = true;
-                    key.write = true;
-                    a.Qu = Q;
-                    a.ldqu = ldq;
-                    a.pu = p_old;
-                    a.Cu = Ci;
-                    a.X = Qi;
-                    a.ldx = ldq;
-                    Vh = Qi;
-                    ldvh = ldq;
-                }
-                SmallArgs sm{};
-                sm.op = OP_SKETCH_BCGS2;
-                sm.w = w;
-                sm.k = k;
-                sm.col0 = col;
-                sm.out = Ysk;
-                sm.R = rho;
-                sm.Yacc = Yacc;
-                sm.nacc = i * w;
-                sm.r = rt;
-                sm.Rbar = Rbar;
-                sm.ldrbar = Wb;
-                sm.rbar_col0 = i * w;
-                sketch_small(sm, sp);
-                if ((s = e.reduction(key, a, kr, Vh, ldvh, nullptr, 0, sm, sk_scale))) return s;
+                if ((s = e.reduction(key, a, w, nullptr, 0, nullptr, 0, sg, 1.0))) return s;
+                PassArgs pa{};
+                pa.Y = Vhi;
+                pa.ldy = ldvhi;
+                sp_.out = Ysk;
+                if ((s = e.reduction({w, f32, RED_PROJ, false, 0, false}, pa, i * w, Vhi, ldvhi, Qb, ldq, sp_,
+                                     1.0)))
+                    return s;
             }
             {   // Q_bar_i = (V_hat_i - Q_bar_prev r) rho^{-1}
                 PassArgs a{};
-                a.Y = Vh;
-                a.ldy = ldvh;
+                a.Y = Vhi;
+                a.ldy = ldvhi;
                 a.R1 = rho;
                 a.X = Qi;
                 a.ldx = ldq;
@@ -876,7 +896,13 @@ sko_status two_stage_blocks(sko_ctx c, int64_t n, int32_t nb, int32_t w, const v
                 sm.Rout = Rfull + (int64_t)p_old * N;
                 sm.ldr = N;
             }
-            if ((s = e.gemm_reduction(Qb, ldq, Wb, Qb, ldq, Wb, sm, Wb))) return s;
+            if (pip) {
+                if ((s = e.gemm_reduction(Qb, ldq, Wb, Qb, ldq, Wb, sm, Wb))) return s;
+            } else {
+                // Q_bar = V_hat Rbar^{-1} and its Gram matrix
+                if ((s = e.rowop_reduction(Wb, Vh, ldvh, nullptr, 0, 0, nullptr, Rbpk, Qb, ldq, nullptr, 0, 0, sm, Wb)))
+                    return s;
+            }
             if (reorth && p_old == 0) {
                 // Q_b = Q_bar R_h^{-1} and its Gram matrix -> R_t
                 if ((s = e.rowop_reduction(Wb, Qb, ldq, nullptr, 0, 0, nullptr, Rpk, Qb, ldq, nullptr, 0, 0, chol2,

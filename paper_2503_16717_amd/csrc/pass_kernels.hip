@@ -3,6 +3,7 @@
 #include <algorithm>
 #include <map>
 #include <mutex>
+#include <tuple>
 #include <utility>
 
 #include "pass_impl.h"
@@ -43,14 +44,14 @@ int pass_strip_rows(const PassKey& key) { return select_kernel(key).threads; }
 
 const void* pass_kernel_id(const PassKey& key) { return reinterpret_cast<const void*>(select_kernel(key).fn); }
 
-// Resident workgroups of a pass kernel, queried once per (kernel, device): the occupancy
+// Resident workgroups of a pass kernel, queried once per (kernel, device, LDS): the occupancy
 // query costs more than a launch.
-int resident_grid(const void* kernel, int threads) {
+int resident_grid(const void* kernel, int threads, size_t dyn_lds) {
     int dev = 0;
     if (!kernel || hipGetDevice(&dev) != hipSuccess) return -1;
     static std::mutex mu;
-    static std::map<std::pair<const void*, int>, int> cache;
-    const std::pair<const void*, int> id{kernel, dev};
+    static std::map<std::tuple<const void*, int, size_t>, int> cache;
+    const std::tuple<const void*, int, size_t> id{kernel, dev, dyn_lds};
     {
         std::lock_guard<std::mutex> lk(mu);
         const auto it = cache.find(id);
@@ -59,7 +60,7 @@ int resident_grid(const void* kernel, int threads) {
     int cus = 0, per_cu = 0;
     int res = -1;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) == hipSuccess && cus > 0)
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, dyn_lds) == hipSuccess && cus > 0)
         res = std::max(1, per_cu) * cus;
     std::lock_guard<std::mutex> lk(mu);
     cache[id] = res;

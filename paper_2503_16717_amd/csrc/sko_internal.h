@@ -88,8 +88,8 @@ int pass_strip_rows(const PassKey& key);
 // Largest useful grid for a pass variant on the current device (resident workgroups).
 int pass_grid_cap(const PassKey& key);
 // Workgroups of `threads` threads of `kernel` resident on the current device at once
-// (cached per kernel and device; -1 if the runtime cannot tell).
-int resident_grid(const void* kernel, int threads);
+// (cached per kernel, device and dynamic LDS bytes; -1 if the runtime cannot tell).
+int resident_grid(const void* kernel, int threads, size_t dyn_lds = 0);
 constexpr int kPassThreads = 256;
 constexpr int kMaxPassW = 16;
 constexpr int kMaxUpdCoef = 4096;   // pu * W update coefficients of one pass (p * w of one block step)
@@ -127,6 +127,10 @@ struct SmallArgs {
     double* Rbar;
     int ldrbar;
     int rbar_col0;
+    // OP_SKETCH_BCGS2, optional with Rbar: the same columns in the packed form of Rpk, for a
+    // packed factor of rpk_w columns in all
+    double* Rbar_pk;
+    int rpk_w;
     // assembly after OP_CHOL (assemble != 0):
     //   Rhat = Ra * Rb (w x w), Rdiag = R * Rhat, Rproj = C1 + C2 * Rhat (p x w)
     // (r_identity != 0: the R of this reduction is replaced by the identity in Rdiag)
@@ -219,6 +223,17 @@ hipError_t launch_wide_rowop_reduce(int64_t n, int W, bool f32, const void* Y, i
                                     int64_t ldqu, int pu, const double* Cu, const double* Rpk, void* X, int64_t ldx,
                                     const void* E, int64_t lde, int me, double* partials, int* grid_out,
                                     hipStream_t st, const BatchReloc* br = nullptr);
+
+// X = Y - Q C for wide blocks (W <= 64), with the per-workgroup partials of the Gram matrix
+// X^T X (stride W * W, upper tiles) when `partials` is given.  Needs wide_update_fits (C and
+// the staging in 64 KiB of LDS).  One system: the grid is chosen and returned in *grid.
+// Batched: *grid workgroups per system, those past a system's ceil(n / kUpdateUnitRows) write
+// nothing.
+constexpr int kUpdateUnitRows = 128;
+bool wide_update_fits(int W, int p, bool gram);
+hipError_t launch_wide_update(int64_t n, int W, bool f32, const void* Y, int64_t ldy, const void* Q, int64_t ldq,
+                              int p, const double* C, void* X, int64_t ldx, double* partials, int* grid,
+                              hipStream_t stream, const BatchReloc* br = nullptr);
 
 // Row-wise X = (Y - Qu Cu) * R^{-1} for wide blocks (w <= 64); used by the big-panel
 // close of the two-stage scheme.  Rpk is R in the packed form of SmallArgs::Rpk (null: no

@@ -414,7 +414,14 @@ __device__ void sketch_bcgs2(const SmallArgs& s, double* Z, double* E, double* Y
                 v = load_coherent(s.r + a + c * na);
             else
                 v = load_coherent(s.R + (a - na) + c * w);
-            s.Rbar[a + (int64_t)(s.rbar_col0 + c) * s.ldrbar] = v;
+            const int cg = s.rbar_col0 + c;
+            s.Rbar[a + (int64_t)cg * s.ldrbar] = v;
+            if (s.Rbar_pk && a <= cg) {
+                if (a == cg)
+                    s.Rbar_pk[cg] = 1.0 / v;
+                else
+                    s.Rbar_pk[s.rpk_w + cg * (cg - 1) / 2 + a] = v;
+            }
         }
     }
     __syncthreads();
@@ -579,6 +586,7 @@ __global__ void __launch_bounds__(RT) small_step_kernel_batched(const SmallArgs 
     m.Yacc = batch_ptr(br, sys, d, t.Yacc);
     m.r = batch_ptr(br, sys, d, t.r);
     m.Rbar = batch_ptr(br, sys, d, t.Rbar);
+    m.Rbar_pk = batch_ptr(br, sys, d, t.Rbar_pk);
     m.Ra = batch_ptr(br, sys, d, t.Ra);
     m.Rb = batch_ptr(br, sys, d, t.Rb);
     m.C1 = batch_ptr(br, sys, d, t.C1);
