@@ -175,12 +175,14 @@ struct Engine {
     // X = (Y - Qu Cu) R^{-1} (rowop) and, in the same sweep over X, C = E^T X (E: me <= 64
     // tall columns, solve only) or the Gram X^T X (E null), reduced into `small` as
     // gemm_reduction does.  An update without a solve takes the MFMA update kernel with its
-    // Gram matrix (36 columns on 36, n = 2^24: %UPD%).  Row solves wider than kFusedMaxW
+    // Gram matrix (36 columns on 36, n = 2^24: 2.77 ms in one sweep, 3.34 + 1.11 ms as the row
+    // operation and a Gram sweep).  Row solves wider than kFusedMaxW
     // keep the two sweeps apart (the row and the accumulators no longer fit two waves'
-    // registers), and so do projections on more than 48 columns.
+    // registers), and so do projections on more than 48 columns.  Rpk2: a second factor; X null:
+    // the rows are not stored (Gram only; both for panels of up to kFusedMaxW columns).
     sko_status rowop_reduction(int Wd, const void* Y, int64_t ldy, const void* Qu, int64_t ldqu, int pu,
                                const double* Cu, const double* Rpk, void* X, int64_t ldx, const void* E, int64_t lde,
-                               int me, SmallArgs small, int64_t ldo) {
+                               int me, SmallArgs small, int64_t ldo, const double* Rpk2 = nullptr) {
         if (pu > 0 && !Rpk && !E && wide_update_fits(Wd, pu, true)) {
             int G = br ? (int)std::max<int64_t>(1, std::min<int64_t>(gemm_grid(true, Wd, Wd),
                                                                      (n + kUpdateUnitRows - 1) / kUpdateUnitRows))
@@ -192,6 +194,7 @@ struct Engine {
             return wide_reduce(small, Wd, Wd, G, ldo, kUpdateUnitRows);
         }
         if (pu > 0 || Wd > kFusedMaxW || (E && me > 48)) {
+            if (Rpk2 || !X) return SKO_EINVAL;
             sko_status s = rowop(Wd, Y, ldy, Qu, ldqu, pu, Cu, Rpk, X, ldx);
             if (s) return s;
             return E ? gemm_reduction(E, lde, me, X, ldx, Wd, small, ldo) : gemm_reduction(X, ldx, Wd, X, ldx, Wd, small, ldo);
@@ -205,18 +208,19 @@ struct Engine {
         const int ev = pbegin(
             [&] {
                 return std::string("wide_rowop+") + (E ? "proj" : "gram") + " f" + (f32 ? "32" : "64") +
-                       (pu > 0 ? " upd" : "") + (Rpk ? " trsm" : "");
+                       (Rpk2 ? " trsm2" : " trsm") + (X ? "" : " no write");
             },
-            rows_bytes * (2 * Wd + pu + (E ? me : 0)) * (f32 ? 4.0 : 8.0));
-        SKO_HIP(launch_wide_rowop_reduce(n, Wd, f32, Y, ldy, Qu, ldqu, pu, Cu, Rpk, X, ldx, E, lde, me, partials, &G,
-                                         st, br));
+            rows_bytes * ((X ? 2 : 1) * Wd + (E ? me : 0)) * (f32 ? 4.0 : 8.0));
+        SKO_HIP(launch_wide_rowop_reduce(n, Wd, f32, Y, ldy, Rpk, Rpk2, X, ldx, E, lde, me, partials, &G, st, br));
         pend(ev);
         return wide_reduce(small, ma, Wd, G, ldo, kFusedUnitRows);
     }
 
     // Rpk: the triangular factor packed by the Cholesky step that produced it (SmallArgs::Rpk)
+    // (Rpk2, Rpk3: further factors of a chain of solves, panels of up to kFusedMaxW columns)
     sko_status rowop(int Wd, const void* Y, int64_t ldy, const void* Qu, int64_t ldqu, int pu, const double* Cu,
-                     const double* Rpk, void* X, int64_t ldx) {
+                     const double* Rpk, void* X, int64_t ldx, const double* Rpk2 = nullptr,
+                     const double* Rpk3 = nullptr) {
         const int ev = pbegin(
             [&] {
                 return std::string("wide_rowop f") + (f32 ? "32" : "64") + (pu > 0 ? " upd" : "") + (Rpk ? " trsm" : "");
@@ -227,7 +231,7 @@ struct Engine {
             int G = (int)((n + 8 * kUpdateUnitRows - 1) / (8 * kUpdateUnitRows));
             SKO_HIP(launch_wide_update(n, Wd, f32, Y, ldy, Qu, ldqu, pu, Cu, X, ldx, nullptr, &G, st, br));
         } else {
-            SKO_HIP(launch_wide_rowop(n, Wd, f32, Y, ldy, Qu, ldqu, pu, Cu, Rpk, X, ldx, st, br));
+            SKO_HIP(launch_wide_rowop(n, Wd, f32, Y, ldy, Qu, ldqu, pu, Cu, Rpk, X, ldx, st, br, Rpk2, Rpk3));
         }
         pend(ev);
         return SKO_OK;

@@ -687,6 +687,7 @@ sko_status two_stage_blocks(sko_ctx c, int64_t n, int32_t nb, int32_t w, const v
     const size_t o_Rh = ar.reserve(sizeof(double) * (size_t)Wb * Wb);
     const size_t o_Rt = ar.reserve(sizeof(double) * (size_t)Wb * Wb);
     const size_t o_Rpk = ar.reserve(sizeof(double) * (size_t)Wb * (Wb + 1) / 2);
+    const size_t o_Rpk2 = ar.reserve(sizeof(double) * (size_t)Wb * (Wb + 1) / 2);
     const size_t o_Rbp = ar.reserve(sizeof(double) * (size_t)Wb * (Wb + 1) / 2);
     const size_t o_Rf = ar.reserve(sizeof(double) * (size_t)N * N);
     const size_t o_st = ar.reserve(256);
@@ -709,7 +710,8 @@ sko_status two_stage_blocks(sko_ctx c, int64_t n, int32_t nb, int32_t w, const v
     double* Gb = ar.at<double>(o_G);
     double* Rh = ar.at<double>(o_Rh);
     double* Rt = ar.at<double>(o_Rt);
-    double* Rpk = ar.at<double>(o_Rpk);  // packed copy of Rh, then of Rt, for the row solves
+    double* Rpk = ar.at<double>(o_Rpk);    // packed copies of Rh and Rt, for the row solves
+    double* Rpk2 = ar.at<double>(o_Rpk2);
     double* Rbpk = ar.at<double>(o_Rbp);  // packed copy of Rbar
     double* Rfull = ar.at<double>(o_Rf);
     SKO_HIP(launch_zero(e.status, 256, c->stream));
@@ -868,7 +870,7 @@ sko_status two_stage_blocks(sko_ctx c, int64_t n, int32_t nb, int32_t w, const v
         chol2.col0 = p_old;
         chol2.out = Gb;
         chol2.R = Rt;
-        chol2.Rpk = Rpk;
+        chol2.Rpk = Rpk2;
         chol2.assemble = 1;
         chol2.Ra = Rh;
         chol2.Rb = Rbar;
@@ -877,7 +879,8 @@ sko_status two_stage_blocks(sko_ctx c, int64_t n, int32_t nb, int32_t w, const v
         chol2.p = p_old;
         chol2.Rout = Rfull + (int64_t)p_old * N;
         chol2.ldr = N;
-        const bool fuse_proj = reorth && p_old > 0 && p_old <= 64;
+        const bool chain = !pip && Wb <= kFusedMaxW;
+        const bool fuse_proj = reorth && p_old > 0 && p_old <= (chain ? 48 : 64);
         {
             SmallArgs sm{};
             sm.op = OP_CHOL;
@@ -896,29 +899,38 @@ sko_status two_stage_blocks(sko_ctx c, int64_t n, int32_t nb, int32_t w, const v
                 sm.Rout = Rfull + (int64_t)p_old * N;
                 sm.ldr = N;
             }
+            // chain: the rows are solved again from V_hat (the same arithmetic) instead of being
+            // stored between the sweeps, since the solves cost less than the traffic (36 columns
+            // at n = 2^24: 0.9 ms for a write or a read, about 0.3 ms for a solve)
             if (pip) {
                 if ((s = e.gemm_reduction(Qb, ldq, Wb, Qb, ldq, Wb, sm, Wb))) return s;
             } else {
                 // Q_bar = V_hat Rbar^{-1} and its Gram matrix
-                if ((s = e.rowop_reduction(Wb, Vh, ldvh, nullptr, 0, 0, nullptr, Rbpk, Qb, ldq, nullptr, 0, 0, sm, Wb)))
+                if ((s = e.rowop_reduction(Wb, Vh, ldvh, nullptr, 0, 0, nullptr, Rbpk, chain ? nullptr : Qb, ldq, nullptr,
+                                           0, 0, sm, Wb)))
                     return s;
             }
+            // Q_hat = Q_bar R_h^{-1}: from Q_bar, or from V_hat through both factors
+            const void* Ysrc = chain ? Vh : Qb;
+            const int64_t ldys = chain ? ldvh : ldq;
+            const double* F1 = chain ? Rbpk : Rpk;
+            const double* F2 = chain ? Rpk : nullptr;
             if (reorth && p_old == 0) {
-                // Q_b = Q_bar R_h^{-1} and its Gram matrix -> R_t
-                if ((s = e.rowop_reduction(Wb, Qb, ldq, nullptr, 0, 0, nullptr, Rpk, Qb, ldq, nullptr, 0, 0, chol2,
-                                           Wb)))
+                // its Gram matrix -> R_t
+                if ((s = e.rowop_reduction(Wb, Ysrc, ldys, nullptr, 0, 0, nullptr, F1, chain ? nullptr : Qb, ldq, nullptr,
+                                           0, 0, chol2, Wb, F2)))
                     return s;
             } else if (fuse_proj) {
-                // Q_b = Q_bar R_h^{-1} and C_2 = Q_old^T Q_b
+                // stored, and C_2 = Q_old^T Q_hat
                 SmallArgs sp2{};
                 sp2.op = OP_STORE;
                 sp2.w = Wb;
                 sp2.out = C2;
-                if ((s = e.rowop_reduction(Wb, Qb, ldq, nullptr, 0, 0, nullptr, Rpk, Qb, ldq, Q, ldq, p_old, sp2,
-                                           p_old)))
+                if ((s = e.rowop_reduction(Wb, Ysrc, ldys, nullptr, 0, 0, nullptr, F1, Qb, ldq, Q, ldq, p_old, sp2, p_old,
+                                           F2)))
                     return s;
             } else {
-                if ((s = e.rowop(Wb, Qb, ldq, nullptr, 0, 0, nullptr, Rpk, Qb, ldq))) return s;
+                if ((s = e.rowop(Wb, Ysrc, ldys, nullptr, 0, 0, nullptr, F1, Qb, ldq, F2))) return s;
             }
         }
         if (reorth) {
@@ -940,7 +952,11 @@ sko_status two_stage_blocks(sko_ctx c, int64_t n, int32_t nb, int32_t w, const v
                                            Wb)))
                     return s;
             }
-            if ((s = e.rowop(Wb, Qb, ldq, nullptr, 0, 0, nullptr, Rpk, Qb, ldq))) return s;
+            if (chain && p_old == 0) {
+                if ((s = e.rowop(Wb, Vh, ldvh, nullptr, 0, 0, nullptr, Rbpk, Qb, ldq, Rpk, Rpk2))) return s;
+            } else {
+                if ((s = e.rowop(Wb, Qb, ldq, nullptr, 0, 0, nullptr, Rpk2, Qb, ldq))) return s;
+            }
         }
     }
     double* Rhost = nullptr;

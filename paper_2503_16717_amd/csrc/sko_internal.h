@@ -211,18 +211,17 @@ int skinny_gemm_grid_cap();
 // are resident at once (-1 if the runtime cannot tell).
 int skinny_gemm_resident(bool sym, bool f32, int ma, int nb);
 
-// The wide row operation with the following reduction in the same sweep: X as
-// launch_wide_rowop (W <= kFusedMaxW; the solve only, no update), plus the per-workgroup partials of E^T X (E: n x me tall, me <= 48; stride me * W)
-// or, with E null, of the Gram X^T X (upper tiles; stride W * W).  One system: the grid
-// (workgroups = partial blocks, at most skinny_gemm_grid_cap()) is returned in *grid_out.
-// Batched (br): *grid_out workgroups per system are launched, and those past a system's
-// ceil(n / kFusedUnitRows) write no partials.
+// The wide row solve X = Y R^{-1} [R2^{-1}] (W <= kFusedMaxW) with the following reduction in
+// the same sweep: the per-workgroup partials of E^T X (E: n x me tall, me <= 48; stride me * W)
+// or, with E null, of the Gram X^T X (upper tiles; stride W * W).  X null: not stored (Gram
+// only).  One system: the grid (workgroups = partial blocks, at most skinny_gemm_grid_cap()) is
+// returned in *grid_out.  Batched (br; one factor, X stored): *grid_out workgroups per system
+// are launched, and those past a system's ceil(n / kFusedUnitRows) write no partials.
 constexpr int kFusedMaxW = 40;
 constexpr int kFusedUnitRows = 256;
-hipError_t launch_wide_rowop_reduce(int64_t n, int W, bool f32, const void* Y, int64_t ldy, const void* Qu,
-                                    int64_t ldqu, int pu, const double* Cu, const double* Rpk, void* X, int64_t ldx,
-                                    const void* E, int64_t lde, int me, double* partials, int* grid_out,
-                                    hipStream_t st, const BatchReloc* br = nullptr);
+hipError_t launch_wide_rowop_reduce(int64_t n, int W, bool f32, const void* Y, int64_t ldy, const double* Rpk,
+                                    const double* Rpk2, void* X, int64_t ldx, const void* E, int64_t lde, int me,
+                                    double* partials, int* grid_out, hipStream_t st, const BatchReloc* br = nullptr);
 
 // X = Y - Q C for wide blocks (W <= 64), with the per-workgroup partials of the Gram matrix
 // X^T X (stride W * W, upper tiles) when `partials` is given.  Needs wide_update_fits (C and
@@ -237,11 +236,12 @@ hipError_t launch_wide_update(int64_t n, int W, bool f32, const void* Y, int64_t
 
 // Row-wise X = (Y - Qu Cu) * R^{-1} for wide blocks (w <= 64); used by the big-panel
 // close of the two-stage scheme.  Rpk is R in the packed form of SmallArgs::Rpk (null: no
-// solve).
+// solve); Rpk2 and Rpk3 (W <= kFusedMaxW, no update, one system) are solved with after it.
 hipError_t launch_wide_rowop(int64_t n, int W, bool f32, const void* Y, int64_t ldy,
                              const void* Qu, int64_t ldqu, int pu, const double* Cu,
                              const double* Rpk, void* X, int64_t ldx, hipStream_t stream,
-                             const BatchReloc* br = nullptr);
+                             const BatchReloc* br = nullptr, const double* Rpk2 = nullptr,
+                             const double* Rpk3 = nullptr);
 
 // Zero `rows` runs of `width` bytes, consecutive runs `pitch` bytes apart (pointer, pitch
 // and width multiples of 4 bytes).  A kernel rather than hipMemsetAsync, so the work is an

@@ -42,6 +42,9 @@ struct RowopArgs {
                          // strictly upper entries at w + c(c-1)/2
     void* X;
     int64_t ldx;
+    // further factors, solved with after Rpk in this order (same packed form)
+    const double* Rpk2 = nullptr;
+    const double* Rpk3 = nullptr;
 };
 
 // v - sum_{q < c} x[q] Rc[q] for column c of a triangular solve, the factor entries loaded
@@ -79,6 +82,15 @@ __device__ __forceinline__ void solve_cols(double (&x)[WB], CD Rs, int w, const 
             x[C] = solve_col<WB, C>(x, Rs + w + C * (C - 1) / 2, x[C]) * sD[C];
             solve_cols<WB, C + 1>(x, Rs, w, sD);
         }
+    }
+}
+
+// The reciprocal diagonals of the TRSM factors of ra into LDS, WB apart.
+template <int WB, int TRSM>
+__device__ __forceinline__ void stage_diagonals(const RowopArgs& ra, double* sD) {
+    for (int i = threadIdx.x; i < TRSM * WB; i += ROW_NT) {
+        const int t = i / WB, c = i - t * WB;
+        if (c < ra.w) sD[i] = (t == 0 ? ra.Rpk : t == 1 ? ra.Rpk2 : ra.Rpk3)[c];
     }
 }
 

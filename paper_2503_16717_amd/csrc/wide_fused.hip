@@ -1,7 +1,8 @@
 // The big-panel row operation with the next reduction fused into it (Fig. 6: the BCGS
 // projection of the panel just written on the previous big panels, or the Gram matrix of
-// the second CholQR).  One sweep computes X = (Y - Qu Cu) R^{-1} row by row, as the plain
-// row operation does, writes X, and accumulates per-workgroup partial sums of
+// the next CholQR).  One sweep computes X = Y R^{-1} (or Y R^{-1} R2^{-1}) row by row, as the
+// plain row operation does, writes X where a later sweep reads it, and accumulates
+// per-workgroup partial sums of
 //     X^T X   (Gram, output tiles on or above the diagonal), or
 //     E^T X   (projection on a tall E of at most 48 columns, read here once)
 // on FP64 MFMA 16 x 16 x 4 tiles.  X is never read back from HBM for the reduction.
@@ -43,7 +44,7 @@ __device__ __forceinline__ void wave_sync() {
 // TE = 0: Gram; 1..3: tiles of E's columns (ceil(me / 16)).  At least two waves per SIMD:
 // the row's values and the tile accumulators are live together, and up to 40 columns with up
 // to three tiles of E fit 256 VGPRs without spilling (wider panels keep the two sweeps apart).
-template <int WB, typename T, bool UPD, bool TRSM, int TE>
+template <int WB, typename T, int TRSM, bool WRITE, int TE>
 __device__ __forceinline__ void rowop_red_body(const FusedArgs& fa, const int wg, const int nwg) {
     constexpr int TX = (WB + 15) / 16;  // 16-column tiles of X
     constexpr bool GRAM = TE == 0;
@@ -52,21 +53,18 @@ __device__ __forceinline__ void rowop_red_body(const FusedArgs& fa, const int wg
     constexpr int SW = 16 * TX * SLD;  // doubles staged per wave
     static_assert(NW * SW >= 4 * 64 * NW, "the staging area also holds the cross-wave sums");
     __shared__ double stage[NW * SW];
-    __shared__ double sD[TRSM ? WB : 1];
+    __shared__ double sD[TRSM * WB];
     const RowopArgs& ra = fa.ra;
     const int64_t n = ra.n;
-    const int w0 = ra.w, pu = ra.pu;
+    const int w0 = ra.w;
     const T* __restrict__ Y = static_cast<const T*>(ra.Y);
-    const T* __restrict__ Qu = static_cast<const T*>(ra.Qu);
     T* X = static_cast<T*>(ra.X);
     const T* E = static_cast<const T*>(fa.E);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, ci = lane & 15, g = lane >> 4;
     const uint32_t lane_bytes = (uint32_t)tid * (uint32_t)sizeof(T);
-    if constexpr (TRSM) {
-        for (int i = tid; i < w0; i += ROW_NT) sD[i] = ra.Rpk[i];
-        __syncthreads();
-    }
-    const CD R0 = as_uniform(ra.Rpk), C0 = as_uniform(ra.Cu);
+    stage_diagonals<WB, TRSM>(ra, sD);
+    __syncthreads();
+    const CD R0 = as_uniform(ra.Rpk), R20 = as_uniform(ra.Rpk2);
     double* st = stage + wave * SW;
     double4_t acc[TA][TX];
 #pragma unroll
@@ -76,23 +74,23 @@ __device__ __forceinline__ void rowop_red_body(const FusedArgs& fa, const int wg
 
     for (int64_t r0 = (int64_t)wg * ROW_NT; r0 < n; r0 += (int64_t)nwg * ROW_NT) {
         const int64_t row = r0 + tid;
-        double xa[1][WB];
-        double(&x)[WB] = xa[0];
+        double x[WB];
         if (row < n) {
-            const CD Rs = per_strip(R0), Cs = per_strip(C0);
-            const int64_t ldy = per_strip(ra.ldy), ldx = per_strip(ra.ldx), ldqu = per_strip(ra.ldqu);
+            const int64_t ldy = per_strip(ra.ldy), ldx = per_strip(ra.ldx);
             const int w = per_strip(w0);
 #pragma unroll
             for (int c = 0; c < WB; ++c)
                 x[c] = ldv_nt(lane_elem(Y + r0 + (int64_t)(c < w ? c : w - 1) * ldy, lane_bytes));
-            if constexpr (UPD) update_rows<WB, 1, T>(xa, Qu + row, ldqu, pu, Cs, w);
-            if constexpr (TRSM) solve_cols<WB, 0>(x, Rs, w, sD);
+            solve_cols<WB, 0>(x, per_strip(R0), w, sD);
+            if constexpr (TRSM >= 2) solve_cols<WB, 0>(x, per_strip(R20), w, sD + WB);
+            if constexpr (WRITE) {
 #pragma unroll
-            for (int c = 0; c < WB; ++c) {
-                if (c < w) {
-                    const T v = static_cast<T>(x[c]);
-                    stv_nt(lane_elem(X + r0 + (int64_t)c * ldx, lane_bytes), v);
-                    x[c] = static_cast<double>(v);  // reduce what was stored (FP32 storage: rounded)
+                for (int c = 0; c < WB; ++c) {
+                    if (c < w) {
+                        const T v = static_cast<T>(x[c]);
+                        stv_nt(lane_elem(X + r0 + (int64_t)c * ldx, lane_bytes), v);
+                        x[c] = static_cast<double>(v);  // reduce what was stored (FP32 storage: rounded)
+                    }
                 }
             }
         } else {
@@ -167,15 +165,15 @@ __device__ __forceinline__ void rowop_red_body(const FusedArgs& fa, const int wg
         }
 }
 
-template <int WB, typename T, bool UPD, bool TRSM, int TE>
+template <int WB, typename T, int TRSM, bool WRITE, int TE>
 __global__ void __launch_bounds__(ROW_NT, 2) wide_rowop_red_kernel(const FusedArgs fa) {
-    rowop_red_body<WB, T, UPD, TRSM, TE>(fa, blockIdx.x, gridDim.x);
+    rowop_red_body<WB, T, TRSM, WRITE, TE>(fa, blockIdx.x, gridDim.x);
 }
 
 // Many systems at once (blockIdx.y): workgroup x walks strips x, x + gridDim.x, ... of its
 // system; workgroups past the system's strips write no partial sums (the batched reduction
 // reads the first ceil(n / ROW_NT) of them).
-template <int WB, typename T, bool UPD, bool TRSM, int TE>
+template <int WB, typename T, int TRSM, bool WRITE, int TE>
 __global__ void __launch_bounds__(ROW_NT, 2) wide_rowop_red_kernel_batched(const FusedArgs t, const BatchReloc br) {
     const int sys = batch_system(br);
     const BatchSys& d = br.sys[sys];
@@ -184,68 +182,77 @@ __global__ void __launch_bounds__(ROW_NT, 2) wide_rowop_red_kernel_batched(const
     fa.ra.n = d.n;
     fa.ra.Y = batch_ptr(br, sys, d, t.ra.Y);
     fa.ra.ldy = batch_ld(br, d, t.ra.ldy);
-    fa.ra.Qu = batch_ptr(br, sys, d, t.ra.Qu);
-    fa.ra.ldqu = batch_ld(br, d, t.ra.ldqu);
-    fa.ra.Cu = batch_ptr(br, sys, d, t.ra.Cu);
     fa.ra.Rpk = batch_ptr(br, sys, d, t.ra.Rpk);
     fa.ra.X = batch_ptr(br, sys, d, t.ra.X);
     fa.ra.ldx = batch_ld(br, d, t.ra.ldx);
     fa.E = batch_ptr(br, sys, d, t.E);
     fa.lde = batch_ld(br, d, t.lde);
     fa.partials = batch_ptr(br, sys, d, t.partials);
-    rowop_red_body<WB, T, UPD, TRSM, TE>(fa, blockIdx.x, gridDim.x);
+    rowop_red_body<WB, T, TRSM, WRITE, TE>(fa, blockIdx.x, gridDim.x);
 }
 
-template <int WB, typename T, bool UPD, bool TRSM, int TE>
+template <int WB, typename T, int TRSM, bool WRITE, int TE>
 int fused_resident() {
-    return resident_grid(reinterpret_cast<const void*>(&wide_rowop_red_kernel<WB, T, UPD, TRSM, TE>), ROW_NT);
+    return resident_grid(reinterpret_cast<const void*>(&wide_rowop_red_kernel<WB, T, TRSM, WRITE, TE>), ROW_NT);
 }
 
 // One system: as many workgroups as are resident (at most the partial-sum capacity), the
 // grid returned in *grid.  Batched (br): *grid workgroups per system, given by the caller.
-template <int WB, typename T, bool UPD, bool TRSM, int TE>
-hipError_t fused_launch(const FusedArgs& fa, int* grid, hipStream_t st, const BatchReloc* br) {
-    if (br) {
-        hipLaunchKernelGGL((wide_rowop_red_kernel_batched<WB, T, UPD, TRSM, TE>), dim3(*grid, br->nact), dim3(ROW_NT),
-                           0, st, fa, *br);
-        return hipGetLastError();
-    }
+template <int WB, typename T, int TRSM, bool WRITE, int TE>
+hipError_t fused_launch1(const FusedArgs& fa, int* grid, hipStream_t st) {
     const int64_t strips = (fa.ra.n + ROW_NT - 1) / ROW_NT;
     int64_t cap = skinny_gemm_grid_cap();  // the partial-sum buffers hold this many workgroups
-    const int res = fused_resident<WB, T, UPD, TRSM, TE>();
+    const int res = fused_resident<WB, T, TRSM, WRITE, TE>();
     if (res > 0) cap = std::min<int64_t>(cap, res);
     *grid = (int)std::max<int64_t>(1, std::min<int64_t>(strips, cap));
-    hipLaunchKernelGGL((wide_rowop_red_kernel<WB, T, UPD, TRSM, TE>), dim3(*grid), dim3(ROW_NT), 0, st, fa);
+    hipLaunchKernelGGL((wide_rowop_red_kernel<WB, T, TRSM, WRITE, TE>), dim3(*grid), dim3(ROW_NT), 0, st, fa);
+    return hipGetLastError();
+}
+
+// One solve and the write: also batched (*grid workgroups per system, given by the caller).
+template <int WB, typename T, int TE>
+hipError_t fused_launch(const FusedArgs& fa, int* grid, hipStream_t st, const BatchReloc* br) {
+    if (!br) return fused_launch1<WB, T, 1, true, TE>(fa, grid, st);
+    hipLaunchKernelGGL((wide_rowop_red_kernel_batched<WB, T, 1, true, TE>), dim3(*grid, br->nact), dim3(ROW_NT), 0, st,
+                       fa, *br);
     return hipGetLastError();
 }
 
 template <int WB, typename T>
-hipError_t fused_dispatch(const FusedArgs& fa, int* grid_out, hipStream_t st, const BatchReloc* br) {
-    const bool upd = fa.ra.pu > 0, trsm = fa.ra.Rpk != nullptr;
-    if (fa.E) {
-        if (upd || !trsm) return hipErrorInvalidValue;
-        switch ((fa.me + 15) / 16) {
-            case 1: return fused_launch<WB, T, false, true, 1>(fa, grid_out, st, br);
-            case 2: return fused_launch<WB, T, false, true, 2>(fa, grid_out, st, br);
-            default: return fused_launch<WB, T, false, true, 3>(fa, grid_out, st, br);
+hipError_t fused_dispatch(const FusedArgs& fa, int* grid, hipStream_t st, const BatchReloc* br) {
+    const bool two = fa.ra.Rpk2 != nullptr, write = fa.ra.X != nullptr;
+    if (!fa.ra.Rpk || ((two || !write) && br)) return hipErrorInvalidValue;
+    const int te = fa.E ? (fa.me + 15) / 16 : 0;
+    if (!two && write) {
+        switch (te) {
+            case 0: return fused_launch<WB, T, 0>(fa, grid, st, br);
+            case 1: return fused_launch<WB, T, 1>(fa, grid, st, br);
+            case 2: return fused_launch<WB, T, 2>(fa, grid, st, br);
+            default: return fused_launch<WB, T, 3>(fa, grid, st, br);
         }
     }
-    // the update form (upd && !trsm) is not fused: measured slower than two sweeps
-    if (!upd && trsm) return fused_launch<WB, T, false, true, 0>(fa, grid_out, st, br);
-    return hipErrorInvalidValue;
+    if (two && write) {
+        switch (te) {
+            case 1: return fused_launch1<WB, T, 2, true, 1>(fa, grid, st);
+            case 2: return fused_launch1<WB, T, 2, true, 2>(fa, grid, st);
+            case 3: return fused_launch1<WB, T, 2, true, 3>(fa, grid, st);
+            default: return hipErrorInvalidValue;
+        }
+    }
+    if (te) return hipErrorInvalidValue;
+    return two ? fused_launch1<WB, T, 2, false, 0>(fa, grid, st) : fused_launch1<WB, T, 1, false, 0>(fa, grid, st);
 }
 
 }  // namespace
 
-hipError_t launch_wide_rowop_reduce(int64_t n, int W, bool f32, const void* Y, int64_t ldy, const void* Qu,
-                                    int64_t ldqu, int pu, const double* Cu, const double* Rpk, void* X, int64_t ldx,
-                                    const void* E, int64_t lde, int me, double* partials, int* grid_out,
-                                    hipStream_t st, const BatchReloc* br) {
+hipError_t launch_wide_rowop_reduce(int64_t n, int W, bool f32, const void* Y, int64_t ldy, const double* Rpk,
+                                    const double* Rpk2, void* X, int64_t ldx, const void* E, int64_t lde, int me,
+                                    double* partials, int* grid_out, hipStream_t st, const BatchReloc* br) {
     if (W < 1 || W > kFusedMaxW || n < 1 || !grid_out || !partials) return hipErrorInvalidValue;
     if (br && (br->nact < 1 || *grid_out < 1)) return hipErrorInvalidValue;
     if (E && (me < 1 || me > 48)) return hipErrorInvalidValue;
-    const FusedArgs fa{RowopArgs{n, W, Y, ldy, Qu, ldqu, pu, Cu, Rpk, X, ldx}, E, lde, E ? me : 0, partials,
-                       (int64_t)(E ? me : W) * W};
+    const FusedArgs fa{RowopArgs{n, W, Y, ldy, nullptr, 0, 0, nullptr, Rpk, X, ldx, Rpk2, nullptr}, E, lde, E ? me : 0,
+                       partials, (int64_t)(E ? me : W) * W};
     if (W <= 16) return f32 ? fused_dispatch<16, float>(fa, grid_out, st, br) : fused_dispatch<16, double>(fa, grid_out, st, br);
     if (W <= 24) return f32 ? fused_dispatch<24, float>(fa, grid_out, st, br) : fused_dispatch<24, double>(fa, grid_out, st, br);
     if (W <= 32) return f32 ? fused_dispatch<32, float>(fa, grid_out, st, br) : fused_dispatch<32, double>(fa, grid_out, st, br);

@@ -32,25 +32,25 @@ using namespace wide;
 // One row per thread, grid-stride over strips of ROW_NT rows.  The factor R and the update
 // coefficients are read through the scalar cache (every lane uses the same entry), loaded
 // again per strip; only the diagonal reciprocals sit in LDS.
-template <int WB, typename T, bool UPD, bool TRSM>
+template <int WB, typename T, bool UPD, int TRSM>
 __device__ __forceinline__ void rowop_body(const RowopArgs& ra, const int wg, const int nwg) {
     const int64_t n = ra.n;
     const int w0 = ra.w, pu = ra.pu;
     const T* __restrict__ Y = static_cast<const T*>(ra.Y);
     const T* __restrict__ Qu = static_cast<const T*>(ra.Qu);
     T* X = static_cast<T*>(ra.X);
-    __shared__ double sD[TRSM ? WB : 1];
+    __shared__ double sD[TRSM ? TRSM * WB : 1];
     const int tid = threadIdx.x;
     const uint32_t lane_bytes = (uint32_t)tid * (uint32_t)sizeof(T);
-    if constexpr (TRSM) {
-        for (int i = tid; i < w0; i += ROW_NT) sD[i] = ra.Rpk[i];
+    if constexpr (TRSM > 0) {
+        stage_diagonals<WB, TRSM>(ra, sD);
         __syncthreads();
     }
-    const CD R0 = as_uniform(ra.Rpk), C0 = as_uniform(ra.Cu);
+    const CD R0 = as_uniform(ra.Rpk), C0 = as_uniform(ra.Cu), R20 = as_uniform(ra.Rpk2), R30 = as_uniform(ra.Rpk3);
     for (int64_t r0 = (int64_t)wg * ROW_NT; r0 < n; r0 += (int64_t)nwg * ROW_NT) {
         const int64_t row = r0 + tid;
         if (row >= n) continue;
-        const CD Rs = per_strip(R0), Cs = per_strip(C0);
+        const CD Cs = per_strip(C0);
         // column offsets from leading dimensions re-derived per strip (held for the sweep,
         // 64 of them would not fit the SGPRs)
         const int64_t ldy = per_strip(ra.ldy), ldx = per_strip(ra.ldx), ldqu = per_strip(ra.ldqu);
@@ -64,19 +64,21 @@ __device__ __forceinline__ void rowop_body(const RowopArgs& ra, const int wg, co
 #pragma unroll
         for (int c = 0; c < WB; ++c) x[c] = ldv_nt(lane_elem(Y + r0 + (int64_t)(c < w ? c : w - 1) * ldy, lane_bytes));
         if constexpr (UPD) update_rows<WB, 1, T>(xa, Qu + row, ldqu, pu, Cs, w);
-        if constexpr (TRSM) solve_cols<WB, 0>(x, Rs, w, sD);
+        if constexpr (TRSM >= 1) solve_cols<WB, 0>(x, per_strip(R0), w, sD);
+        if constexpr (TRSM >= 2) solve_cols<WB, 0>(x, per_strip(R20), w, sD + WB);
+        if constexpr (TRSM >= 3) solve_cols<WB, 0>(x, per_strip(R30), w, sD + 2 * WB);
 #pragma unroll
         for (int c = 0; c < WB; ++c)
             if (c < w) stv_nt(lane_elem(X + r0 + (int64_t)c * ldx, lane_bytes), static_cast<T>(x[c]));
     }
 }
 
-template <int WB, typename T, bool UPD, bool TRSM>
+template <int WB, typename T, bool UPD, int TRSM>
 __global__ void __launch_bounds__(ROW_NT) wide_rowop_kernel(const RowopArgs ra) {
     rowop_body<WB, T, UPD, TRSM>(ra, blockIdx.x, gridDim.x);
 }
 
-template <int WB, typename T, bool UPD, bool TRSM>
+template <int WB, typename T, bool UPD, int TRSM>
 __global__ void __launch_bounds__(ROW_NT) wide_rowop_kernel_batched(const RowopArgs t, const BatchReloc br) {
     const int sys = batch_system(br);
     const BatchSys& d = br.sys[sys];
@@ -176,32 +178,46 @@ __global__ void __launch_bounds__(GT) wide_gemm_tn_kernel_batched(const GemmArgs
     gemm_body<T, SYM, TA, TB>(ga);
 }
 
-template <int WB, typename T, bool UPD, bool TRSM>
-void rowop_launch(const RowopArgs& ra, hipStream_t st, const BatchReloc* br) {
+// One system: the resident workgroups only, each walking its strips.
+template <int WB, typename T, bool UPD, int TRSM>
+void rowop_launch1(const RowopArgs& ra, hipStream_t st) {
     const int64_t strips = (ra.n + ROW_NT - 1) / ROW_NT;
-    if (br) {
-        // many systems at once: each workgroup takes up to 8 strips of its system
-        const int grid = (int)((strips + 7) / 8);
-        hipLaunchKernelGGL((wide_rowop_kernel_batched<WB, T, UPD, TRSM>), dim3(grid, br->nact), dim3(ROW_NT), 0, st,
-                           ra, *br);
-        return;
-    }
-    // resident workgroups only: each walks its strips
     int cap = resident_grid(reinterpret_cast<const void*>(&wide_rowop_kernel<WB, T, UPD, TRSM>), ROW_NT);
     if (cap < 1) cap = 1024;
     const int grid = (int)std::min<int64_t>(strips, cap);
     hipLaunchKernelGGL((wide_rowop_kernel<WB, T, UPD, TRSM>), dim3(grid), dim3(ROW_NT), 0, st, ra);
 }
 
+template <int WB, typename T, bool UPD, int TRSM>
+void rowop_launch(const RowopArgs& ra, hipStream_t st, const BatchReloc* br) {
+    if (br) {
+        // many systems at once: each workgroup takes up to 8 strips of its system
+        const int64_t strips = (ra.n + ROW_NT - 1) / ROW_NT;
+        const int grid = (int)((strips + 7) / 8);
+        hipLaunchKernelGGL((wide_rowop_kernel_batched<WB, T, UPD, TRSM>), dim3(grid, br->nact), dim3(ROW_NT), 0, st,
+                           ra, *br);
+        return;
+    }
+    rowop_launch1<WB, T, UPD, TRSM>(ra, st);
+}
+
 template <int WB, typename T>
 hipError_t rowop_dispatch(const RowopArgs& ra, hipStream_t st, const BatchReloc* br) {
+    if (ra.pu > 0 && ra.Rpk2) return hipErrorInvalidValue;
     if (ra.pu > 0 && ra.Rpk)
-        rowop_launch<WB, T, true, true>(ra, st, br);
+        rowop_launch<WB, T, true, 1>(ra, st, br);
     else if (ra.pu > 0)
-        rowop_launch<WB, T, true, false>(ra, st, br);
-    else if (ra.Rpk)
-        rowop_launch<WB, T, false, true>(ra, st, br);
-    else
+        rowop_launch<WB, T, true, 0>(ra, st, br);
+    else if (ra.Rpk && !ra.Rpk2)
+        rowop_launch<WB, T, false, 1>(ra, st, br);
+    else if constexpr (WB <= kFusedMaxW) {
+        // chains of solves: one system, panels whose reductions are fused with the solves
+        if (!ra.Rpk || br) return hipErrorInvalidValue;
+        if (ra.Rpk3)
+            rowop_launch1<WB, T, false, 3>(ra, st);
+        else
+            rowop_launch1<WB, T, false, 2>(ra, st);
+    } else
         return hipErrorInvalidValue;
     return hipGetLastError();
 }
@@ -259,10 +275,11 @@ void gemm_launch(const GemmArgs& ga, int grid, hipStream_t st, const BatchReloc*
 
 hipError_t launch_wide_rowop(int64_t n, int W, bool f32, const void* Y, int64_t ldy, const void* Qu, int64_t ldqu,
                              int pu, const double* Cu, const double* Rpk, void* X, int64_t ldx, hipStream_t st,
-                             const BatchReloc* br) {
+                             const BatchReloc* br, const double* Rpk2, const double* Rpk3) {
     if (W < 1 || W > 64 || n < 1) return hipErrorInvalidValue;
     if (br && br->nact < 1) return hipErrorInvalidValue;
-    const RowopArgs ra{n, W, Y, ldy, Qu, ldqu, pu, Cu, Rpk, X, ldx};
+    if (Rpk3 && !Rpk2) return hipErrorInvalidValue;
+    const RowopArgs ra{n, W, Y, ldy, Qu, ldqu, pu, Cu, Rpk, X, ldx, Rpk2, Rpk3};
     if (W <= 16) return f32 ? rowop_dispatch<16, float>(ra, st, br) : rowop_dispatch<16, double>(ra, st, br);
     if (W <= 24) return f32 ? rowop_dispatch<24, float>(ra, st, br) : rowop_dispatch<24, double>(ra, st, br);
     if (W <= 32) return f32 ? rowop_dispatch<32, float>(ra, st, br) : rowop_dispatch<32, double>(ra, st, br);
