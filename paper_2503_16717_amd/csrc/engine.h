@@ -77,12 +77,16 @@ struct Engine {
     }
 
     // One reduction: `first` pass (may update/solve/write), then identity passes over
-    // Xsrc for the remaining reduction rows, then the reduce kernel with `small`.
+    // Xsrc for the remaining reduction rows (projections that write nothing run again as they
+    // are), then the reduce kernel with `small`; ldo: leading dimension of its output (0:
+    // contiguous).
     sko_status reduction(PassKey first, PassArgs a, int rows_total, const void* Xsrc, int64_t ldxs,
-                         const void* Qp, int64_t ldqp, SmallArgs small, double scale) {
+                         const void* Qp, int64_t ldqp, SmallArgs small, double scale, int64_t ldo = 0) {
         const int rpl = pass_rows_per_launch(W, first.red);
         if (first.red == RED_PROJ || first.red == RED_SKETCH_SPARSE) first.tiles = (std::min(rpl, rows_total) + 15) / 16;
         PassKey rest{W, first.f32, first.red, false, 0, false, first.tiles};
+        const bool again = first.pair == PAIR_PROJ || first.pair == SOLO_PROJ;
+        if (again) rest = first;
         if (first.panel) {
             // the remaining rows read the (updated) FP64 panel: a projection still against
             // the FP32 basis, a sketch of the panel alone in FP64
@@ -104,8 +108,10 @@ struct Engine {
             PassKey key = first;
             if (r0 > 0) {
                 key = rest;
-                b.Y = Xsrc;
-                b.ldy = ldxs;
+                if (!again) {
+                    b.Y = Xsrc;
+                    b.ldy = ldxs;
+                }
             }
             b.red_row0 = r0;
             b.red_rows = std::min(rpl, rows_total - r0);
@@ -124,11 +130,11 @@ struct Engine {
         ra.partials = partials;
         ra.stride = part_stride;
         ra.G = G;
-        ra.count = rows_total * W;
+        ra.count = rows_total * pass_red_cols(first);
         ra.scale = scale;
         ra.counter = counter;
-        ra.rows = ra.count;
-        ra.ldo = ra.count;
+        ra.rows = ldo ? rows_total : ra.count;
+        ra.ldo = ldo ? ldo : ra.count;
         ra.small = small;
         ra.small.status = status;
         ra.unit_rows = kPassThreads;  // a strip is at least this many rows
@@ -277,9 +283,13 @@ struct Engine {
         const int mt = k.red == RED_PROJ ? (k.tiles >= 1 && k.tiles <= 4 ? 4 : k.tiles >= 5 && k.tiles <= 6 ? 6 : 8) : 0;
         char tl[16] = "";
         if (mt) snprintf(tl, sizeof tl, "/mt%d", mt);
+        static const char* pairs[] = {"", " pair", " pair", " lead", " solo", " solo"};
         const char* ty = k.panel == 1 ? "f64|f32" : k.panel == 2 ? "f64>f32" : k.f32 ? "f32" : "f64";
-        snprintf(buf, sizeof buf, "pass W=%d %s red=%s%s upd=%d trsm=%d write=%d", k.W, ty, reds[k.red], tl,
-                 (int)k.upd, k.ntrsm, (int)k.write);
+        const bool upd = k.upd || k.pair == PAIR_UPD || k.pair == PAIR_LEAD || k.pair == SOLO_UPD;
+        const bool write = k.write || (k.pair && k.pair != PAIR_PROJ && k.pair != SOLO_PROJ);
+        const int trsm = k.pair ? (k.pair == PAIR_LEAD ? 1 : 2) : k.ntrsm;
+        snprintf(buf, sizeof buf, "pass W=%d %s red=%s%s upd=%d trsm=%d write=%d%s", k.W, ty, reds[k.red], tl,
+                 (int)upd, trsm, (int)write, pairs[k.pair]);
         return buf;
     }
     // Algorithmic HBM bytes of one launch: every tall operand once (read or written).
@@ -287,6 +297,13 @@ struct Engine {
         const double eq = k.f32 ? 4.0 : 8.0;               // basis operand
         const double ey = k.panel ? 8.0 : eq;              // input block
         const double ex = k.panel == 1 ? 8.0 : eq;         // written block
+        if (k.pair) {
+            const bool two = k.pair == PAIR_PROJ || k.pair == PAIR_UPD || k.pair == PAIR_LEAD;
+            const int written = (k.pair == PAIR_PROJ || k.pair == SOLO_PROJ) ? 0 : (two && a.X2) ? 2 : 1;
+            const int basis = k.red == RED_PROJ ? a.red_rows : a.pu;
+            return (W * ((two ? 2 : 1) + written) + basis) * eq * rows_bytes +
+                   (k.red == RED_SKETCH_DENSE ? 8.0 * a.red_rows * rows_bytes : 0.0);
+        }
         double per_row = W * ey + (k.write ? W * ex : 0.0) +
                          ((k.upd ? a.pu : 0) + (k.red == RED_PROJ ? a.red_rows : 0)) * eq +
                          (k.red == RED_SKETCH_DENSE ? 8.0 * a.red_rows : 0.0);

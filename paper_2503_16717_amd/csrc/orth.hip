@@ -12,10 +12,25 @@
 //   P2  Vh = V - Q C1 (written), sketch Y = Theta^T Vh (or Gram Vh^T Vh for CholQR2)
 //                                                     reduce -> R1 = HH(Y) (or chol)
 //   P3  Qb = Vh R1^{-1} (not stored), G2 = Qb^T Qb    reduce -> R2 = chol(G2)
-//   P4  Qh = Vh R1^{-1} R2^{-1} (written), C2 = Q^T Qh reduce -> C2
-//   P5  Vb = Qh - Q C2 (written), G3 = Vb^T Vb        reduce -> R3 = chol(G3), assemble R
+//   P4  Qh = Vh R1^{-1} R2^{-1} (not stored), C2 = Q^T Qh reduce -> C2
+//   P5  Vb = Qh - Q C2 (Qh solved again; written), G3 = Vb^T Vb
+//                                                     reduce -> R3 = chol(G3), assemble R
 //   P6  Qj = Vb R3^{-1} (written)
-// With p = 0 the projections vanish: P2 reads V directly, P4 accumulates G3 = Qh^T Qh.
+// With p = 0 the projections vanish: P2 reads V directly, P4 writes Qh and accumulates
+// G3 = Qh^T Qh.  Per row: 4p + 9w columns.
+//
+// A whole matrix (orth_blocks) knows the next block while it works on this one, and reads Q
+// once for both (one_stage_lookahead):
+//   L   Qj-1 = Vb R3^{-1} (written), Vh = V' - Qj-1 c (written), sketch (or Gram) of Vh
+//   P3  as above
+//   P4  [C2 C1'] = Q^T [Qh Vj+1]
+//   P5  Vb = Qh - Q C2 and V' = Vj+1 - Q C1' (both written), [G3 X] = Vb^T [Vb V']
+//       reduce -> R3, c = R3^{-T} X = Qj^T V', assemble R (C1 of block j+1 is [C1'; c])
+// so 2p + 11w columns per block instead of 4p + 9w.  V' = (I - Q Q^T) V is projected on Qj
+// where the single step projects V itself: the same C1 in exact arithmetic, and block-wise
+// modified instead of classical Gram-Schmidt for its last w rows.  FP32 storage would round V'
+// once more, so there P5 leaves Vj+1 alone (X = Vb^T Vj+1) and L applies all of [C1'; c]:
+// 3p + 10w columns.
 #include <algorithm>
 #include <cmath>
 #include <cstdio>
@@ -34,6 +49,45 @@ namespace sko {
 sko_status one_stage_block_recursive(Engine& e, const BlockBufs& b, int p, const void* Q, int64_t ldq,
                                      const void* V, int64_t ldv, void* Qo, int64_t ldqo, double* Rcol,
                                      int64_t ldr, int col0);
+
+namespace {
+
+// P5 of a block: Vb = Vh R1^{-1} R2^{-1} - Q C2 written to Qo, G3, R3, and the block's R.
+sko_status solo_update(Engine& e, const BlockBufs& b, int p, const void* Q, int64_t ldq, const void* Vh, int64_t ldvh,
+                       void* Qo, int64_t ldqo, const double* C1, int64_t ldc1, const double* C2, double* Rcol,
+                       int64_t ldr, int col0) {
+    PassArgs a{};
+    a.Y = Vh;
+    a.ldy = ldvh;
+    a.R1 = b.R1;
+    a.R2 = b.R2;
+    a.Qu = Q;
+    a.ldqu = ldq;
+    a.pu = p;
+    a.Cu = C2;
+    a.X = Qo;
+    a.ldx = ldqo;
+    SmallArgs sm{};
+    sm.op = OP_CHOL;
+    sm.w = e.W;
+    sm.col0 = col0;
+    sm.out = b.G3;
+    sm.R = b.R3;
+    sm.assemble = 1;
+    sm.Ra = b.R2;
+    sm.Rb = b.R1;
+    sm.C1 = C1;
+    sm.ldc1 = ldc1;
+    sm.C2 = C2;
+    sm.p = p;
+    sm.Rout = Rcol;
+    sm.ldr = ldr;
+    PassKey key{e.W, e.f32, RED_GRAM, false, 0, false};
+    key.pair = SOLO_UPD;
+    return e.reduction(key, a, e.W, nullptr, 0, nullptr, 0, sm, 1.0);
+}
+
+}  // namespace
 
 sko_status one_stage_block(Engine& e, const BlockBufs& b, int intra, int p, const void* Q, int64_t ldq,
                            const void* V, int64_t ldv, void* Qo, int64_t ldqo, double* Rcol, int64_t ldr,
@@ -112,23 +166,26 @@ sko_status one_stage_block(Engine& e, const BlockBufs& b, int intra, int p, cons
             return SKO_EUNSUPPORTED;
         }
     }
-    // P4: Qh = Vh R1^{-1} R2^{-1} written to Qo; C2 = Q^T Qh (or G3 = Qh^T Qh when p = 0)
+    // P4: Qh = Vh R1^{-1} R2^{-1}; C2 = Q^T Qh (Qh not stored), or with p = 0 Qh written to Qo
+    // and G3 = Qh^T Qh
     {
         PassArgs a{};
         a.Y = Vh;
         a.ldy = ldvh;
         a.R1 = b.R1;
         a.R2 = b.R2;
-        a.X = Qo;
-        a.ldx = ldqo;
         SmallArgs sm{};
         sm.w = W;
         sm.col0 = col0;
         if (p > 0) {
             sm.op = OP_STORE;
             sm.out = b.C2;
-            if ((s = e.reduction({W, f32, RED_PROJ, false, 2, true}, a, p, Qo, ldqo, Q, ldq, sm, 1.0))) return s;
+            PassKey key{W, f32, RED_PROJ, false, 0, false};
+            key.pair = SOLO_PROJ;
+            if ((s = e.reduction(key, a, p, nullptr, 0, Q, ldq, sm, 1.0))) return s;
         } else {
+            a.X = Qo;
+            a.ldx = ldqo;
             sm.op = OP_CHOL;
             sm.out = b.G3;
             sm.R = b.R3;
@@ -142,33 +199,8 @@ sko_status one_stage_block(Engine& e, const BlockBufs& b, int intra, int p, cons
                 return s;
         }
     }
-    // P5: Vb = Qh - Q C2 written in place; G3 = Vb^T Vb; R3 = chol(G3); assemble R
-    if (p > 0) {
-        PassArgs a{};
-        a.Y = Qo;
-        a.ldy = ldqo;
-        a.Qu = Q;
-        a.ldqu = ldq;
-        a.pu = p;
-        a.Cu = b.C2;
-        a.X = Qo;
-        a.ldx = ldqo;
-        SmallArgs sm{};
-        sm.op = OP_CHOL;
-        sm.w = W;
-        sm.col0 = col0;
-        sm.out = b.G3;
-        sm.R = b.R3;
-        sm.assemble = 1;
-        sm.Ra = b.R2;
-        sm.Rb = b.R1;
-        sm.C1 = b.C1;
-        sm.C2 = b.C2;
-        sm.p = p;
-        sm.Rout = Rcol;
-        sm.ldr = ldr;
-        if ((s = e.reduction({W, f32, RED_GRAM, true, 0, true}, a, W, Qo, ldqo, nullptr, 0, sm, 1.0))) return s;
-    }
+    // P5: Vb = Qh - Q C2 written to Qo; G3 = Vb^T Vb; R3 = chol(G3); assemble R
+    if (p > 0 && (s = solo_update(e, b, p, Q, ldq, Vh, ldvh, Qo, ldqo, b.C1, p, b.C2, Rcol, ldr, col0))) return s;
     // P6: Qj = Vb R3^{-1}
     {
         PassArgs a{};
@@ -180,6 +212,144 @@ sko_status one_stage_block(Engine& e, const BlockBufs& b, int intra, int p, cons
         if ((s = e.plain({W, f32, RED_NONE, false, 1, true}, a))) return s;
     }
     return SKO_OK;
+}
+
+// One-stage BCGS2 of all nb >= 2 blocks of V, reading Q once for a block and the next one (the
+// schedule at the top of this file).  D: two buffers of N x 2W doubles (block j's [C2 C1'] with
+// the rows of c below C1', leading dimension (j + 1) W, in D + (j & 1) N 2W); Gx: W x 2W.
+sko_status one_stage_lookahead(Engine& e, const BlockBufs& b, int intra, int nb, const void* V, int64_t ldv, void* Q,
+                               int64_t ldq, double* R, double* D, double* Gx) {
+    const int W = e.W, N = nb * W;
+    const bool f32 = e.f32;
+    const bool rand = intra == SKO_INTRA_RANDCHOLQR;
+    const SketchPlan sp = sketch_plan(e.sk);
+    const int red_first = rand ? sp.red : RED_GRAM;
+    const int rows_first = rand ? sp.rows : W;
+    auto block = [&](void* M, int64_t ld, int j) { return offset_elems(M, (int64_t)j * W * ld, f32); };
+    auto cblock = [&](const void* M, int64_t ld, int j) { return offset_elems(M, (int64_t)j * W * ld, f32); };
+    sko_status s;
+    for (int j = 0; j < nb; ++j) {
+        const int p = j * W;
+        const int64_t ldd = p + W;  // leading dimension of this block's D
+        double* Dj = D + (int64_t)(j & 1) * N * 2 * W;
+        // C1 of this block, p x W with leading dimension p, from the block before
+        const double* C1 = j ? D + (int64_t)((j - 1) & 1) * N * 2 * W + (int64_t)W * p : nullptr;
+        double* Rcol = R + (int64_t)p * N;
+        void* Qj = block(Q, ldq, j);
+        const void* Vh = j ? static_cast<const void*>(Qj) : V;
+        const int64_t ldvh = j ? ldq : ldv;
+        {   // L (block 0: the reduction of V itself)
+            PassArgs a{};
+            PassKey key{W, f32, red_first, false, 0, false};
+            a.Y = Vh;
+            a.ldy = ldvh;
+            if (j) {
+                key.pair = PAIR_LEAD;
+                void* Qp = block(Q, ldq, j - 1);
+                a.Y = Qp;
+                a.ldy = ldq;
+                a.R1 = b.R3;
+                a.X = Qp;
+                a.ldx = ldq;
+                const bool raw = f32 || j == 1;  // y is still V_j itself
+                a.Y2 = raw ? cblock(V, ldv, j) : Qj;
+                a.ldy2 = raw ? ldv : ldq;
+                a.X2 = Qj;
+                a.ldx2 = ldq;
+                a.Qu = Q;
+                a.ldqu = ldq;
+                a.pu = f32 ? p - W : 0;
+                a.Cu = C1;
+                a.Cx = C1 + (p - W);
+                a.ldcu = p;
+            }
+            SmallArgs sm{};
+            sm.op = rand ? OP_HH : OP_CHOL;
+            sm.w = W;
+            sm.k = rand ? sp.k : W;
+            sm.col0 = p;
+            sm.out = b.Ysk;
+            sm.R = b.R1;
+            if (rand) sketch_small(sm, sp);
+            if ((s = e.reduction(key, a, rows_first, Vh, ldvh, nullptr, 0, sm, rand ? sp.scale : 1.0))) return s;
+        }
+        {   // P3
+            PassArgs a{};
+            a.Y = Vh;
+            a.ldy = ldvh;
+            a.R1 = b.R1;
+            SmallArgs sm{};
+            sm.op = OP_CHOL;
+            sm.w = W;
+            sm.col0 = p;
+            sm.out = b.G2;
+            sm.R = b.R2;
+            if ((s = e.reduction({W, f32, RED_GRAM, false, 1, false}, a, W, nullptr, 0, nullptr, 0, sm, 1.0))) return s;
+        }
+        PassArgs a{};
+        a.Y = Vh;
+        a.ldy = ldvh;
+        a.R1 = b.R1;
+        a.R2 = b.R2;
+        const bool last = j == nb - 1;
+        if (!last) {
+            a.Y2 = cblock(V, ldv, j + 1);
+            a.ldy2 = ldv;
+        }
+        if (p > 0) {  // P4
+            SmallArgs sm{};
+            sm.op = OP_STORE;
+            sm.w = W;
+            sm.out = Dj;
+            PassKey key{W, f32, RED_PROJ, false, 0, false};
+            key.pair = last ? SOLO_PROJ : PAIR_PROJ;
+            if ((s = e.reduction(key, a, p, nullptr, 0, Q, ldq, sm, 1.0, last ? p : ldd))) return s;
+        }
+        if (last) {
+            if ((s = solo_update(e, b, p, Q, ldq, Vh, ldvh, Qj, ldq, C1, p, Dj, Rcol, N, p))) return s;
+            break;
+        }
+        // P5
+        a.Qu = Q;
+        a.ldqu = ldq;
+        a.pu = p;
+        a.Cu = Dj;
+        a.ldcu = (int)ldd;
+        a.X = Qj;
+        a.ldx = ldq;
+        if (!f32 && p > 0) {
+            a.X2 = block(Q, ldq, j + 1);
+            a.ldx2 = ldq;
+        }
+        SmallArgs sm{};
+        sm.op = OP_CHOL;
+        sm.w = W;
+        sm.col0 = p;
+        sm.out = Gx;
+        sm.R = b.R3;
+        sm.cross_out = Dj + (int64_t)W * ldd + p;
+        sm.ldcross = ldd;
+        sm.assemble = 1;
+        sm.Ra = b.R2;
+        sm.Rb = b.R1;
+        sm.C1 = C1;
+        sm.ldc1 = p;
+        sm.C2 = p > 0 ? Dj : nullptr;
+        sm.ldc2 = ldd;
+        sm.p = p;
+        sm.Rout = Rcol;
+        sm.ldr = N;
+        PassKey key{W, f32, RED_GRAM, false, 0, false};
+        key.pair = PAIR_UPD;
+        if ((s = e.reduction(key, a, W, nullptr, 0, nullptr, 0, sm, 1.0))) return s;
+    }
+    PassArgs a{};
+    a.Y = block(Q, ldq, nb - 1);
+    a.ldy = ldq;
+    a.R1 = b.R3;
+    a.X = block(Q, ldq, nb - 1);
+    a.ldx = ldq;
+    return e.plain({W, f32, RED_NONE, false, 1, true}, a);
 }
 
 namespace {
@@ -389,25 +559,42 @@ namespace {
 
 // Workspace sizing shared by the one-stage entry points.
 struct OneStageLayout {
-    size_t partials, small, rfull, status, total;
+    size_t partials, small, rfull, status, pair, total;
     int64_t part_stride;
     int gmax;
 };
 
-OneStageLayout layout_one_stage(sko_ctx c, int64_t n, int W, int pmax, int k, int N) {
+// ahead: with the two-block passes of one_stage_lookahead.
+OneStageLayout layout_one_stage(sko_ctx c, int64_t n, int W, int pmax, int k, int N, bool ahead = false) {
     OneStageLayout L{};
     Arena ar(c);
     const int64_t nstrips = (n + kPassThreads - 1) / kPassThreads;
     L.gmax = (int)std::min<int64_t>(nstrips, (int64_t)std::max(1, c->cus) * 8);
     int64_t rows = std::max({(int64_t)pmax, (int64_t)k, (int64_t)W});
+    if (ahead) rows = std::max(rows, 2 * std::max<int64_t>(pmax, W));
     L.part_stride = ((rows * W + 31) / 32) * 32;
     L.partials = ar.reserve(sizeof(double) * L.part_stride * L.gmax);
     const int64_t cw = std::max<int64_t>(1, (int64_t)pmax * W);
     L.small = ar.reserve(sizeof(double) * (2 * cw + (int64_t)std::max(k, W) * W + 7 * W * W));
     L.rfull = ar.reserve(sizeof(double) * (int64_t)std::max(1, N) * std::max(1, N));
     L.status = ar.reserve(256);
+    L.pair = ahead ? ar.reserve(sizeof(double) * ((size_t)4 * N * W + 2 * (size_t)W * W)) : 0;
     L.total = ar.used();
     return L;
+}
+
+// Whether orth_blocks runs the look-ahead schedule: two or more blocks narrow enough for the
+// two-block passes, the plain intra-block steps, and V and Q either the same columns or apart
+// (the schedule writes columns of Q before the matching columns of V are finished with, which
+// a V shifted against Q would not survive).
+bool one_stage_looks_ahead(int64_t n, int nb, int w, bool f32, int intra, const void* V, int64_t ldv, const void* Q,
+                           int64_t ldq) {
+    if (nb < 2 || w > kMaxPairW || intra == SKO_INTRA_CHOLQR2_RECURSIVE) return false;
+    if (V == Q && ldv == ldq) return true;
+    const int64_t eb = f32 ? 4 : 8, N = (int64_t)nb * w;
+    const char *v0 = static_cast<const char*>(V), *q0 = static_cast<const char*>(Q);
+    const char *v1 = v0 + eb * (ldv * (N - 1) + n), *q1 = q0 + eb * (ldq * (N - 1) + n);
+    return v1 <= q0 || q1 <= v0;
 }
 
 BlockBufs carve(const Arena& ar, const OneStageLayout& L, int pmax, int k, int W) {
@@ -463,7 +650,8 @@ sko_status orth_blocks_impl(sko_ctx c, int64_t n, int32_t nb, int32_t w, const v
 
     const bool f32 = o->precision == SKO_MIXED_F32;
     const int k = rand ? sketch_plan(o->sketch).rows : w;
-    OneStageLayout L = layout_one_stage(c, n, w, N - w, k, N);
+    const bool ahead = one_stage_looks_ahead(n, nb, w, f32, o->intra, V, ldv, Q, ldq);
+    OneStageLayout L = layout_one_stage(c, n, w, N - w, k, N, ahead);
     sko_status s = ensure_workspace(c, L.total);
     if (s) return s;
     Arena ar(c);
@@ -477,7 +665,11 @@ sko_status orth_blocks_impl(sko_ctx c, int64_t n, int32_t nb, int32_t w, const v
     SKO_HIP(launch_zero(e.status, 256, c->stream));
     SKO_HIP(launch_zero(Rfull, sizeof(double) * (size_t)N * N, c->stream));
     BlockBufs bb = carve(ar, L, N - w, k, w);
-    for (int j = 0; j < nb; ++j) {
+    if (ahead) {
+        double* D = ar.at<double>(L.pair);
+        if ((s = one_stage_lookahead(e, bb, o->intra, nb, V, ldv, Q, ldq, Rfull, D, D + (size_t)4 * N * w))) return s;
+    }
+    for (int j = 0; !ahead && j < nb; ++j) {
         const int p = j * w;
         const void* Vj = offset_elems(V, (int64_t)p * ldv, f32);
         void* Qj = offset_elems(Q, (int64_t)p * ldq, f32);

@@ -126,7 +126,8 @@ struct Tys {
 };
 
 // One pass over the rows of `a` by workgroup wg of nwg.
-template <int W, typename TS, int RED, bool UPD, int NTRSM, bool WRITE, int MTX>
+// W columns per block; WR columns staged and reduced.
+template <int W, typename TS, int RED, bool UPD, int NTRSM, bool WRITE, int MTX, int PAIR = PAIR_NONE>
 __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const int nwg) {
     using TY = typename TS::TY;
     using TQ = typename TS::TQ;
@@ -136,23 +137,29 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
     constexpr bool F32 = sizeof(TY) == 4 && sizeof(TQ) == 4 && sizeof(TX) == 4;
     // rows per thread in phase A: two for float storage (8-byte accesses), except for wide
     // blocks with triangular solves or updates, whose two rows would not fit the registers
-    constexpr int RPT = (F32 && (W <= 8 || (NTRSM == 0 && !UPD))) ? 2 : 1;
+    constexpr bool TWO = PAIR == PAIR_PROJ || PAIR == PAIR_UPD || PAIR == PAIR_LEAD;
+    constexpr int WR = (PAIR == PAIR_PROJ || PAIR == PAIR_UPD) ? 2 * W : W;
+    // the Gram of a pair runs on MFMA tiles as a projection does, with its W rows read from LDS
+    constexpr bool GMF = PAIR == PAIR_UPD;
+    constexpr int RPT = PAIR != PAIR_NONE ? 1 : (F32 && (W <= 8 || (NTRSM == 0 && !UPD))) ? 2 : 1;
     constexpr int STRIP = NT * RPT;
     constexpr int LDX = STRIP + 1;  // padded LDS leading dimension of the strip
     constexpr int RPL = STRIP / 64;
     constexpr int MAXA = C::MAXA;
-    constexpr int MT = MTX > 0 ? MTX : C::MT;  // MFMA tiles held (fewer: more waves per SIMD)
-    constexpr bool MF = C::MF;
+    constexpr int MT = GMF ? 1 : MTX > 0 ? MTX : C::MT;  // MFMA tiles held (fewer: more waves per SIMD)
+    constexpr bool MF = C::MF || GMF;
     constexpr bool WAVE_LOCAL = C::SK;  // sketch tiles reduce each wave's own rows
     constexpr bool HAS_RED = RED != RED_NONE;
-    constexpr bool GRAM = RED == RED_GRAM;
+    constexpr bool GRAM = RED == RED_GRAM && !GMF;
     // the strip in LDS, in the storage type: float storage reduces the rounded values it
     // stores (and halves the LDS)
     using XS = typename std::conditional<sizeof(typename std::conditional<WRITE, TX, TY>::type) == 4, float,
                                          double>::type;
-    __shared__ XS xs[HAS_RED ? W * LDX : 1];
+    __shared__ XS xs[HAS_RED ? WR * LDX : 1];
     __shared__ uint64_t hs[RED == RED_SKETCH_SPARSE ? STRIP : 1];
-    __shared__ double pred[MF ? 4 * 64 * C::NWAVE : 1];  // cross-wave tile sums
+    constexpr int CB = (WR + 3) / 4;
+    constexpr int PC = CB > 4 ? CB : 4;
+    __shared__ double pred[MF ? PC * 64 * C::NWAVE : 1];  // cross-wave tile sums
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -161,7 +168,8 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
 
     // triangular factors (W x W, column-major) and update coefficients (pu x W)
     const CD gR0[2] = {as_uniform(a.R1), as_uniform(a.R2)};
-    const CD gC0 = as_uniform(a.Cu);
+    const CD gC0 = as_uniform(a.Cu), gCx0 = as_uniform(a.Cx);
+    const int ldcu = a.ldcu ? a.ldcu : a.pu;
     // their diagonals' reciprocals: in registers, or for wide blocks in LDS, read again per
     // strip (two solves of 11 columns would hold 44 registers of them for the whole sweep:
     // 144 against 101 VGPRs, 3 against 4 waves, for the FP32 solve + projection on 64 columns,
@@ -184,11 +192,11 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
 
     // Gram: this wave accumulates output rows [a_lo, a_lo + MAXA)
     const int a_lo = wave * MAXA;
-    double acc[GRAM ? MAXA : 1][W];
+    double acc[GRAM ? MAXA : 1][WR];
 #pragma unroll
     for (int i = 0; i < (GRAM ? MAXA : 1); ++i)
 #pragma unroll
-        for (int c = 0; c < W; ++c) acc[i][c] = 0.0;
+        for (int c = 0; c < WR; ++c) acc[i][c] = 0.0;
     // MFMA accumulators: tile m covers output rows 16m..16m+15 of this launch
     // The projection and dense sketch of blocks up to 12 columns run on v_mfma_f64_4x4x4 (four independent 4 x 4 x 4 blocks per instruction, the same FP64
     // rate as 16 x 16 x 4): a block covers 4 output rows x 4 columns of x, so narrow blocks
@@ -201,8 +209,7 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
     // l and, for launches of up to 128 rows, l + 64
     constexpr bool SPM = RED == RED_SKETCH_SPARSE;
     constexpr int SPR = MT / 4;
-    constexpr bool B4 = MF && !SPM && W <= 12;
-    constexpr int CB = (W + 3) / 4;
+    constexpr bool B4 = MF && !SPM && (W <= 12 || TWO);
     double4_t dacc[(MF && !SPM && !B4) ? MT : 1];
     double acc4[B4 ? MT * CB : 1];
 #pragma unroll
@@ -246,11 +253,12 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
         // wide blocks load the factor and coefficient entries again per strip (w(w-1)/2 per
         // factor would not fit the SGPRs for the whole sweep); narrow blocks may hold them
         CD gR[2] = {gR0[0], gR0[1]};
-        CD gC = gC0;
+        CD gC = gC0, gCx = gCx0;
         if constexpr (W >= 10) {
             gR[0] = per_strip(gR[0]);
             gR[1] = per_strip(gR[1]);
             gC = per_strip(gC);
+            gCx = per_strip(gCx);
         }
         const int ri0 = RINV_LDS ? per_strip(0) : 0;
         auto rdiag = [&](int i) {
@@ -260,7 +268,85 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
                 return rinv[i];
         };
         // ---------------- phase A: RPT consecutive rows per thread ----------------
-        if constexpr (RPT == 1)
+        if constexpr (PAIR != PAIR_NONE) {
+            // x solved (and rounded as a stored x would be), then the updates of both blocks
+            const int64_t row = base + tid;
+            constexpr int WZ = TWO ? 2 * W : W;
+            double za[1][WZ];
+            double(&z)[WZ] = za[0];
+            if (row < n) {
+                const TY* Y = static_cast<const TY*>(a.Y);
+#pragma unroll
+                for (int c = 0; c < W; ++c) z[c] = ldv(Y + row + c * a.ldy);
+                if constexpr (TWO) {
+                    const TY* Y2 = static_cast<const TY*>(a.Y2);
+#pragma unroll
+                    for (int c = 0; c < W; ++c) z[W + c] = ldv(Y2 + row + c * a.ldy2);
+                }
+#pragma unroll
+                for (int t = 0; t < NTRSM; ++t) {
+                    const CD R = gR[t];
+#pragma unroll
+                    for (int c = 0; c < W; ++c) {
+                        double v = z[c];
+#pragma unroll
+                        for (int q = 0; q < c; ++q) v -= z[q] * R[q + c * W];
+                        z[c] = v * rdiag(t * W + c);
+                    }
+                }
+                if constexpr (sizeof(TX) == 4) {
+#pragma unroll
+                    for (int c = 0; c < W; ++c) z[c] = static_cast<double>(static_cast<TX>(z[c]));
+                }
+                TX* X = static_cast<TX*>(a.X);
+                TX* X2 = static_cast<TX*>(a.X2);
+                const TQ* Qr = static_cast<const TQ*>(a.Qu) + row;
+                if constexpr (PAIR == PAIR_UPD && sizeof(TX) == 8) {
+                    update_rows<WZ, 1, TQ>(za, Qr, a.ldqu, a.pu, gC, ldcu);
+                } else if constexpr (PAIR == PAIR_UPD || PAIR == SOLO_UPD) {
+                    double xa[1][W];
+#pragma unroll
+                    for (int c = 0; c < W; ++c) xa[0][c] = z[c];
+                    update_rows<W, 1, TQ>(xa, Qr, a.ldqu, a.pu, gC, ldcu);
+#pragma unroll
+                    for (int c = 0; c < W; ++c) z[c] = xa[0][c];
+                } else if constexpr (PAIR == PAIR_LEAD) {
+                    double ya[1][W];
+#pragma unroll
+                    for (int c = 0; c < W; ++c) ya[0][c] = z[W + c];
+                    update_rows<W, 1, TQ>(ya, Qr, a.ldqu, a.pu, gC, ldcu);
+#pragma unroll
+                    for (int c = 0; c < W; ++c) {
+                        double v = ya[0][c];
+#pragma unroll
+                        for (int q = 0; q < W; ++q) v -= z[q] * gCx[q + c * ldcu];
+                        z[W + c] = v;
+                    }
+                }
+                if constexpr (WRITE) {
+#pragma unroll
+                    for (int c = 0; c < W; ++c) stv(X + row + c * a.ldx, z[c]);
+                }
+                if constexpr (PAIR == PAIR_LEAD) {
+#pragma unroll
+                    for (int c = 0; c < W; ++c) stv(X2 + row + c * a.ldx2, z[W + c]);
+                } else if constexpr (PAIR == PAIR_UPD && sizeof(TX) == 8) {
+                    if (X2) {
+#pragma unroll
+                        for (int c = 0; c < W; ++c) stv(X2 + row + c * a.ldx2, z[W + c]);
+                    }
+                }
+                if constexpr (RED == RED_SKETCH_SPARSE) hs[tid] = splitmix64(a.sk_seed, (uint64_t)row);
+            } else {
+#pragma unroll
+                for (int c = 0; c < WZ; ++c) z[c] = 0.0;
+                if constexpr (RED == RED_SKETCH_SPARSE) hs[tid] = 0;
+            }
+            constexpr int Z0 = PAIR == PAIR_LEAD ? W : 0;
+#pragma unroll
+            for (int c = 0; c < WR; ++c) xs[c * LDX + tid] = static_cast<XS>(z[Z0 + c]);
+        }
+        else if constexpr (RPT == 1)
         {
             const int64_t row = base + tid;
             double xa[1][W];
@@ -269,7 +355,7 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
                 const TY* Y = static_cast<const TY*>(a.Y);
 #pragma unroll
                 for (int c = 0; c < W; ++c) x[c] = ldv(Y + row + c * a.ldy);
-                if constexpr (UPD) update_rows<W, 1, TQ>(xa, static_cast<const TQ*>(a.Qu) + row, a.ldqu, a.pu, gC);
+                if constexpr (UPD) update_rows<W, 1, TQ>(xa, static_cast<const TQ*>(a.Qu) + row, a.ldqu, a.pu, gC, ldcu);
 #pragma unroll
                 for (int t = 0; t < NTRSM; ++t) {
                     const CD R = gR[t];
@@ -313,7 +399,7 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
                 if constexpr (UPD) {
                     // the last row alone (an odd n) updates its single row
                     if (row0 + RPT - 1 < n) {
-                        update_rows<W, RPT, TQ>(x, static_cast<const TQ*>(a.Qu) + row0, a.ldqu, a.pu, gC);
+                        update_rows<W, RPT, TQ>(x, static_cast<const TQ*>(a.Qu) + row0, a.ldqu, a.pu, gC, ldcu);
                     } else {
                         const TQ* Q = static_cast<const TQ*>(a.Qu) + row0;
                         for (int j = 0; j < a.pu; ++j) {
@@ -498,7 +584,7 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
                         for (int cb = 0; cb < CB; ++cb) {
                             const int col = 4 * cb + (lane & 3);
 #pragma unroll
-                            for (int u = 0; u < UR; ++u) bq[cb][u] = (col < W) ? xs[col * LDX + r0 + u] : XS(0);
+                            for (int u = 0; u < UR; ++u) bq[cb][u] = (col < WR) ? xs[col * LDX + r0 + u] : XS(0);
                         }
                     } else {
 #pragma unroll
@@ -537,7 +623,10 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
                             }
                             double av[4] = {0.0, 0.0, 0.0, 0.0};
                             if (col < a.red_rows) {
-                                if constexpr (RED == RED_PROJ)
+                                if constexpr (GMF) {
+#pragma unroll
+                                    for (int u = 0; u < 4; ++u) av[u] = (double)xs[ci * LDX + r0 + u];
+                                } else if constexpr (RED == RED_PROJ)
                                     load_col4(Qp + (int64_t)col * a.ldqp + base + r0, full, base + r0, n, av);
                                 else
                                     load_col4(Th + (int64_t)col * a.ldtheta + base + r0, full, base + r0, n, av);
@@ -562,16 +651,16 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
 #pragma unroll 2
                 for (int r = 0; r < RPL; ++r) {
                     const int rr = r * 64 + lane;
-                    double x[W];
+                    double x[WR];
 #pragma unroll
-                    for (int c = 0; c < W; ++c) x[c] = xs[c * LDX + rr];
+                    for (int c = 0; c < WR; ++c) x[c] = xs[c * LDX + rr];
 #pragma unroll
                     for (int i = 0; i < MAXA; ++i) {
                         const int al = a_lo + i;
                         if (al < a.red_rows) {
                             const double xa = xs[(a.red_row0 + al) * LDX + rr];
 #pragma unroll
-                            for (int c = 0; c < W; ++c) acc[i][c] += xa * x[c];
+                            for (int c = 0; c < WR; ++c) acc[i][c] += xa * x[c];
                         }
                     }
                 }
@@ -624,15 +713,15 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
         for (int m = 0; m < MT; ++m) {
             if (m >= ntiles) break;
 #pragma unroll
-            for (int cb = 0; cb < CB; ++cb) pred[(wave * 4 + cb) * 64 + lane] = acc4[m * CB + cb];
+            for (int cb = 0; cb < CB; ++cb) pred[(wave * PC + cb) * 64 + lane] = acc4[m * CB + cb];
             __syncthreads();
             if (wave == 0) {
 #pragma unroll
                 for (int cb = 0; cb < CB; ++cb) {
                     double v = 0.0;
-                    for (int w2 = 0; w2 < C::NWAVE; ++w2) v += pred[(w2 * 4 + cb) * 64 + lane];
+                    for (int w2 = 0; w2 < C::NWAVE; ++w2) v += pred[(w2 * PC + cb) * 64 + lane];
                     const int r = 16 * m + srow, c = 4 * cb + col;
-                    if (r < a.red_rows && c < W) out[(a.red_row0 + r) + (int64_t)c * a.part_rows_total] = v;
+                    if (r < a.red_rows && c < WR) out[(a.red_row0 + r) + (int64_t)c * a.part_rows_total] = v;
                 }
             }
             __syncthreads();
@@ -666,7 +755,7 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
         for (int i = 0; i < MAXA; ++i) {
             const int al = a_lo + i;
 #pragma unroll
-            for (int c = 0; c < W; ++c) {
+            for (int c = 0; c < WR; ++c) {
                 const double v = wave_sum(acc[i][c]);
                 if (lane == 0 && al < a.red_rows)
                     out[(a.red_row0 + al) + (int64_t)c * a.part_rows_total] = v;
@@ -722,6 +811,13 @@ __global__ void __launch_bounds__((Cfg<W, RED>::NT), (min_waves<W, T, RED, UPD, 
     pass_body<W, Tys<T, T, T>, RED, UPD, NTRSM, WRITE, MTX>(a, blockIdx.x, gridDim.x);
 }
 
+template <int W, typename T, int RED, int PAIR, int MTX = 0>
+__global__ void __launch_bounds__((Cfg<W, RED>::NT)) pass_kernel_pair(const PassArgs a) {
+    constexpr int NTRSM = PAIR == PAIR_LEAD ? 1 : 2;
+    constexpr bool WRITE = PAIR != PAIR_PROJ && PAIR != SOLO_PROJ;
+    pass_body<W, Tys<T, T, T>, RED, false, NTRSM, WRITE, MTX, PAIR>(a, blockIdx.x, gridDim.x);
+}
+
 using KernelPtr = void (*)(const PassArgs);
 using BatchedKernelPtr = void (*)(const PassArgs, const BatchReloc);
 
@@ -763,6 +859,32 @@ KernelPtr select_w(const PassKey& k) {
     if (r == RED_NONE && t == 1 && wr) {
         if (!u) return &pass_kernel<W, T, RED_NONE, false, 1, true>;
         return &pass_kernel<W, T, RED_NONE, true, 1, true>;
+    }
+    return nullptr;
+}
+
+// The two-block passes of the one-stage block QR and the solve-first passes of a single block.
+template <int W, typename T>
+KernelPtr select_w_pair(const PassKey& k) {
+    const int mt = (k.tiles >= 1 && k.tiles <= 4) ? 4 : (k.tiles >= 5 && k.tiles <= 6) ? 6 : 8;
+    if (k.pair == SOLO_PROJ && k.red == RED_PROJ)
+        return mt == 4   ? &pass_kernel_pair<W, T, RED_PROJ, SOLO_PROJ, 4>
+               : mt == 6 ? &pass_kernel_pair<W, T, RED_PROJ, SOLO_PROJ, 6>
+                         : &pass_kernel_pair<W, T, RED_PROJ, SOLO_PROJ>;
+    if (k.pair == SOLO_UPD && k.red == RED_GRAM) return &pass_kernel_pair<W, T, RED_GRAM, SOLO_UPD>;
+    if constexpr (W <= kMaxPairW) {
+        if (k.pair == PAIR_PROJ && k.red == RED_PROJ)
+            return mt == 4   ? &pass_kernel_pair<W, T, RED_PROJ, PAIR_PROJ, 4>
+                   : mt == 6 ? &pass_kernel_pair<W, T, RED_PROJ, PAIR_PROJ, 6>
+                             : &pass_kernel_pair<W, T, RED_PROJ, PAIR_PROJ>;
+        if (k.pair == PAIR_UPD && k.red == RED_GRAM) return &pass_kernel_pair<W, T, RED_GRAM, PAIR_UPD>;
+        if (k.pair == PAIR_LEAD) {
+            if (k.red == RED_GRAM) return &pass_kernel_pair<W, T, RED_GRAM, PAIR_LEAD>;
+            if (k.red == RED_SKETCH_DENSE) return &pass_kernel_pair<W, T, RED_SKETCH_DENSE, PAIR_LEAD>;
+            if (k.red == RED_SKETCH_SPARSE)
+                return mt == 4 ? &pass_kernel_pair<W, T, RED_SKETCH_SPARSE, PAIR_LEAD, 4>
+                               : &pass_kernel_pair<W, T, RED_SKETCH_SPARSE, PAIR_LEAD>;
+        }
     }
     return nullptr;
 }

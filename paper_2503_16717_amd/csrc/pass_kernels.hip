@@ -77,7 +77,7 @@ int pass_grid_cap(const PassKey& key) {
 hipError_t launch_pass(const PassKey& key, const PassArgs& args, int grid, hipStream_t stream, const BatchReloc* br) {
     PassSel s = select_kernel(key);
     if (!s.fn || (br && !s.fnb)) return hipErrorInvalidValue;
-    if (key.upd && args.pu * key.W > kMaxUpdCoef) return hipErrorInvalidValue;
+    if ((key.upd || key.pair) && args.pu * key.W > kMaxUpdCoef) return hipErrorInvalidValue;
     if (key.red != RED_NONE && args.red_rows > s.rows) return hipErrorInvalidValue;
     if (grid < 1) return hipErrorInvalidValue;
     if (br) {

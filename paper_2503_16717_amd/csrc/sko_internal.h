@@ -36,6 +36,20 @@ enum RedKind : int {
     RED_SKETCH_DENSE = 4,
 };
 
+// Passes of two blocks (PassKey::pair), x from Y and y from Y2, and the single-block passes
+// that solve before they update.  Each reads again what the pass before it would otherwise have
+// stored: the solves R1 [R2] of x are cheap next to a column of traffic.
+enum PairKind : int {
+    PAIR_NONE = 0,
+    PAIR_PROJ = 1,  // x R1^{-1} R2^{-1} and y, nothing written: Qp^T [x y]
+    PAIR_UPD = 2,   // x R1^{-1} R2^{-1} - Qu Cu -> X; FP64: y - Qu Cu' -> X2 (Cu' the next W
+                    // columns of Cu; X2 null: y as it is); reduces x^T [x y]
+    PAIR_LEAD = 3,  // x R1^{-1} -> X; y - Qu Cu - x Cx -> X2; reduces a sketch of y, or y^T y
+    SOLO_PROJ = 4,  // x R1^{-1} R2^{-1}, not written: Qp^T x
+    SOLO_UPD = 5,   // x R1^{-1} R2^{-1} - Qu Cu -> X; reduces x^T x
+};
+constexpr int kMaxPairW = 12;  // block width up to which the two-block passes exist
+
 struct PassArgs {
     int64_t n;
     const void* Y;            // input block, W columns
@@ -60,6 +74,12 @@ struct PassArgs {
     int32_t part_rows_total;  // rows of the whole reduction output
     int32_t sk_k;
     int32_t sk_zeta;
+    int32_t ldcu;             // leading dimension of Cu and Cx (0: pu)
+    const void* Y2;           // second block of a two-block pass
+    int64_t ldy2;
+    void* X2;
+    int64_t ldx2;
+    const double* Cx;         // PAIR_LEAD: coefficients of x, W x W
 };
 
 struct PassKey {
@@ -73,7 +93,11 @@ struct PassKey {
     // mixed-precision GMRES panel (f32 basis): 1 = FP64 panel Y read against the basis, FP64
     // X; 2 = FP64 panel Y, X written into the FP32 basis; 0 = one storage type throughout
     int panel = 0;
+    int pair = PAIR_NONE;  // the fields upd, ntrsm and write are then fixed by the kind
 };
+
+// Columns of the reduction of a pass: both blocks for the projection and the Gram of a pair.
+inline int pass_red_cols(const PassKey& k) { return (k.pair == PAIR_PROJ || k.pair == PAIR_UPD) ? 2 * k.W : k.W; }
 
 // Launch one pass over all n rows with `grid` workgroups (grid <= pass_grid_cap()).  With
 // `br`, one launch serves every active system of a batch (grid workgroups each).
@@ -141,6 +165,11 @@ struct SmallArgs {
     const double* C1;
     const double* C2;
     int p;
+    int64_t ldc1, ldc2;  // leading dimensions of C1 and C2 (0: p)
+    // OP_CHOL of a two-block pass: the reduced values are [G X] (w x 2w), and the coefficients
+    // R^{-T} X of the next block on this one go to cross_out (w x w, leading dimension ldcross)
+    double* cross_out;
+    int64_t ldcross;
     double* Rout;        // destination of [Rproj; Rdiag] columns in a big R (ld ldr)
     int64_t ldr;
     // Count-Gauss sketch (theta_g != null): the reduced values in `out` are the kc x w Count

@@ -336,10 +336,10 @@ __device__ void assemble(const SmallArgs& s, double* rh) {
         }
         for (int idx = tid; idx < s.p * w; idx += RT) {
             const int a = idx % s.p, c = idx / s.p;
-            double v = s.C1 ? s.C1[a + c * s.p] : 0.0;
+            double v = s.C1 ? s.C1[a + c * (s.ldc1 ? s.ldc1 : s.p)] : 0.0;
             if (s.C2) {
                 double t2 = 0.0;
-                for (int t = 0; t <= c; ++t) t2 += s.C2[a + t * s.p] * load_coherent(rh + t + c * w);
+                for (int t = 0; t <= c; ++t) t2 += s.C2[a + t * (s.ldc2 ? s.ldc2 : s.p)] * load_coherent(rh + t + c * w);
                 v += t2;
             }
             s.Rout[a + c * s.ldr] = v;
@@ -522,6 +522,20 @@ __device__ __forceinline__ void small_step(const SmallArgs& s) {
         __syncthreads();
         if (tid < 64) cholesky_wave(G, s.w, s.R, s.Rpk, s.status, s.col0, scal);
         __syncthreads();
+        if (s.cross_out) {
+            // column c of R^{-T} X by forward substitution, one thread each (w <= 16)
+            __threadfence();
+            if (tid < s.w) {
+                double v[16];
+                for (int i = 0; i < s.w; ++i) {
+                    double t = load_coherent(s.out + s.w * s.w + i + tid * s.w);
+                    for (int q = 0; q < i; ++q) t -= load_coherent(s.R + q + i * s.w) * v[q];
+                    v[i] = t / load_coherent(s.R + i + i * s.w);
+                    s.cross_out[i + (int64_t)tid * s.ldcross] = v[i];
+                }
+            }
+            __syncthreads();
+        }
         if (s.assemble) {
             __threadfence();
             assemble(s, s.out);  // Rhat overwrites the consumed Gram matrix

@@ -112,14 +112,14 @@ __device__ __forceinline__ RawRows<R, T> load_raw(const T* p) {
 
 // x[r][c] -= sum_{u<G} Q(r, j + u) C(j + u, c): one group of G update columns.
 template <int W, int R, typename T, int G>
-__device__ __forceinline__ void update_group(double (&x)[R][W], const RawRows<R, T> (&q)[G], CD C, int j, int pu,
+__device__ __forceinline__ void update_group(double (&x)[R][W], const RawRows<R, T> (&q)[G], CD C, int j, int ldc,
                                              int w) {
 #pragma unroll
     for (int c = 0; c < W; ++c) {
         if (c < w) {
             double cu[G];
 #pragma unroll
-            for (int u = 0; u < G; ++u) cu[u] = C[j + u + c * pu];
+            for (int u = 0; u < G; ++u) cu[u] = C[j + u + c * ldc];
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 double v = x[r][c];
@@ -141,11 +141,11 @@ __device__ __forceinline__ void load_group(RawRows<R, T> (&q)[G], const T* Q, in
 
 // x[r][c] -= Q(r, j) C(j, c) for one loaded column j.
 template <int W, int R, typename T>
-__device__ __forceinline__ void update_col(double (&x)[R][W], const RawRows<R, T>& q, CD C, int j, int pu, int w) {
+__device__ __forceinline__ void update_col(double (&x)[R][W], const RawRows<R, T>& q, CD C, int j, int ldc, int w) {
 #pragma unroll
     for (int c = 0; c < W; ++c) {
         if (c < w) {
-            const double cj = C[j + c * pu];
+            const double cj = C[j + c * ldc];
 #pragma unroll
             for (int r = 0; r < R; ++r) x[r][c] -= static_cast<double>(q.v[r]) * cj;
         }
@@ -153,7 +153,7 @@ __device__ __forceinline__ void update_col(double (&x)[R][W], const RawRows<R, T
 }
 
 // x[r][c] -= sum_j Q(r, j) C(j, c) over the pu columns of Q for the w <= W live columns of
-// x (Q points at this thread's first row; all R rows lie below n).  Columns go in groups of
+// x (Q points at this thread's first row; all R rows lie below n; C has leading dimension ldc).  Columns go in groups of
 // G, and the next group's loads are issued before the current group's FMAs (two register
 // buffers in turn), so each wave keeps a group of loads in flight while it computes; the
 // pu mod G remaining columns follow one by one.  Every column is loaded once: non-temporal
@@ -162,7 +162,7 @@ __device__ __forceinline__ void update_col(double (&x)[R][W], const RawRows<R, T
 // double one, so twice as many are kept in flight.  The subtraction order (j ascending per
 // output column) is the same as in the generic path and does not depend on G.
 template <int W, int R, typename T>
-__device__ __forceinline__ void update_rows(double (&x)[R][W], const T* Q, int64_t ldq, int pu, CD C, int w = W) {
+__device__ __forceinline__ void update_rows(double (&x)[R][W], const T* Q, int64_t ldq, int pu, CD C, int ldc, int w = W) {
     constexpr int G = (sizeof(T) == 4 && R == 1) ? 8 : 4;
     int j = 0;
     if (pu >= G) {
@@ -171,17 +171,17 @@ __device__ __forceinline__ void update_rows(double (&x)[R][W], const T* Q, int64
         while (true) {
             const bool more = j + 2 * G <= pu;
             if (more) load_group<R, T, G>(qb, Q, ldq, j + G);
-            update_group<W, R, T, G>(x, qa, C, j, pu, w);
+            update_group<W, R, T, G>(x, qa, C, j, ldc, w);
             j += G;
             if (!more) break;
             const bool more2 = j + 2 * G <= pu;
             if (more2) load_group<R, T, G>(qa, Q, ldq, j + G);
-            update_group<W, R, T, G>(x, qb, C, j, pu, w);
+            update_group<W, R, T, G>(x, qb, C, j, ldc, w);
             j += G;
             if (!more2) break;
         }
     }
-    for (; j < pu; ++j) update_col<W, R, T>(x, load_raw<R>(Q + (int64_t)j * ldq), C, j, pu, w);
+    for (; j < pu; ++j) update_col<W, R, T>(x, load_raw<R>(Q + (int64_t)j * ldq), C, j, ldc, w);
 }
 
 }  // namespace sko

@@ -63,7 +63,7 @@ __device__ __forceinline__ void rowop_body(const RowopArgs& ra, const int wg, co
         // that load, inside the branch, one column at a time.
 #pragma unroll
         for (int c = 0; c < WB; ++c) x[c] = ldv_nt(lane_elem(Y + r0 + (int64_t)(c < w ? c : w - 1) * ldy, lane_bytes));
-        if constexpr (UPD) update_rows<WB, 1, T>(xa, Qu + row, ldqu, pu, Cs, w);
+        if constexpr (UPD) update_rows<WB, 1, T>(xa, Qu + row, ldqu, pu, Cs, pu, w);
         if constexpr (TRSM >= 1) solve_cols<WB, 0>(x, per_strip(R0), w, sD);
         if constexpr (TRSM >= 2) solve_cols<WB, 0>(x, per_strip(R20), w, sD + WB);
         if constexpr (TRSM >= 3) solve_cols<WB, 0>(x, per_strip(R30), w, sD + 2 * WB);
