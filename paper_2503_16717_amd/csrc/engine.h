@@ -188,7 +188,7 @@ struct Engine {
     // the rows are not stored (Gram only; both for panels of up to kFusedMaxW columns).
     sko_status rowop_reduction(int Wd, const void* Y, int64_t ldy, const void* Qu, int64_t ldqu, int pu,
                                const double* Cu, const double* Rpk, void* X, int64_t ldx, const void* E, int64_t lde,
-                               int me, SmallArgs small, int64_t ldo, const double* Rpk2 = nullptr) {
+                               int me, SmallArgs small, int64_t ldo, const double* Rpk2 = nullptr, int pw = 0) {
         if (pu > 0 && !Rpk && !E && wide_update_fits(Wd, pu, true)) {
             int G = br ? (int)std::max<int64_t>(1, std::min<int64_t>(gemm_grid(true, Wd, Wd),
                                                                      (n + kUpdateUnitRows - 1) / kUpdateUnitRows))
@@ -201,7 +201,7 @@ struct Engine {
         }
         if (pu > 0 || Wd > kFusedMaxW || (E && me > 48)) {
             if (Rpk2 || !X) return SKO_EINVAL;
-            sko_status s = rowop(Wd, Y, ldy, Qu, ldqu, pu, Cu, Rpk, X, ldx);
+            sko_status s = rowop(Wd, Y, ldy, Qu, ldqu, pu, Cu, Rpk, X, ldx, nullptr, nullptr, pw);
             if (s) return s;
             return E ? gemm_reduction(E, lde, me, X, ldx, Wd, small, ldo) : gemm_reduction(X, ldx, Wd, X, ldx, Wd, small, ldo);
         }
@@ -217,7 +217,8 @@ struct Engine {
                        (Rpk2 ? " trsm2" : " trsm") + (X ? "" : " no write");
             },
             rows_bytes * ((X ? 2 : 1) * Wd + (E ? me : 0)) * (f32 ? 4.0 : 8.0));
-        SKO_HIP(launch_wide_rowop_reduce(n, Wd, f32, Y, ldy, Rpk, Rpk2, X, ldx, E, lde, me, partials, &G, st, br));
+        SKO_HIP(launch_wide_rowop_reduce(n, Wd, f32, Y, ldy, Rpk, Rpk2, X, ldx, E, lde, me, partials, &G, st, br,
+                                         pw));
         pend(ev);
         return wide_reduce(small, ma, Wd, G, ldo, kFusedUnitRows);
     }
@@ -226,7 +227,7 @@ struct Engine {
     // (Rpk2, Rpk3: further factors of a chain of solves, panels of up to kFusedMaxW columns)
     sko_status rowop(int Wd, const void* Y, int64_t ldy, const void* Qu, int64_t ldqu, int pu, const double* Cu,
                      const double* Rpk, void* X, int64_t ldx, const double* Rpk2 = nullptr,
-                     const double* Rpk3 = nullptr) {
+                     const double* Rpk3 = nullptr, int pw = 0) {
         const int ev = pbegin(
             [&] {
                 return std::string("wide_rowop f") + (f32 ? "32" : "64") + (pu > 0 ? " upd" : "") + (Rpk ? " trsm" : "");
@@ -237,7 +238,7 @@ struct Engine {
             int G = (int)((n + 8 * kUpdateUnitRows - 1) / (8 * kUpdateUnitRows));
             SKO_HIP(launch_wide_update(n, Wd, f32, Y, ldy, Qu, ldqu, pu, Cu, X, ldx, nullptr, &G, st, br));
         } else {
-            SKO_HIP(launch_wide_rowop(n, Wd, f32, Y, ldy, Qu, ldqu, pu, Cu, Rpk, X, ldx, st, br, Rpk2, Rpk3));
+            SKO_HIP(launch_wide_rowop(n, Wd, f32, Y, ldy, Qu, ldqu, pu, Cu, Rpk, X, ldx, st, br, Rpk2, Rpk3, pw));
         }
         pend(ev);
         return SKO_OK;
@@ -283,11 +284,11 @@ struct Engine {
         const int mt = k.red == RED_PROJ ? (k.tiles >= 1 && k.tiles <= 4 ? 4 : k.tiles >= 5 && k.tiles <= 6 ? 6 : 8) : 0;
         char tl[16] = "";
         if (mt) snprintf(tl, sizeof tl, "/mt%d", mt);
-        static const char* pairs[] = {"", " pair", " pair", " lead", " solo", " solo"};
+        static const char* pairs[] = {"", " pair", " pair", " lead", " solo", " solo", " cross"};
         const char* ty = k.panel == 1 ? "f64|f32" : k.panel == 2 ? "f64>f32" : k.f32 ? "f32" : "f64";
         const bool upd = k.upd || k.pair == PAIR_UPD || k.pair == PAIR_LEAD || k.pair == SOLO_UPD;
         const bool write = k.write || (k.pair && k.pair != PAIR_PROJ && k.pair != SOLO_PROJ);
-        const int trsm = k.pair ? (k.pair == PAIR_LEAD ? 1 : 2) : k.ntrsm;
+        const int trsm = k.pair ? (k.pair == PAIR_LEAD || k.pair == PAIR_CROSS ? 1 : 2) : k.ntrsm;
         snprintf(buf, sizeof buf, "pass W=%d %s red=%s%s upd=%d trsm=%d write=%d%s", k.W, ty, reds[k.red], tl,
                  (int)upd, trsm, (int)write, pairs[k.pair]);
         return buf;
@@ -298,7 +299,7 @@ struct Engine {
         const double ey = k.panel ? 8.0 : eq;              // input block
         const double ex = k.panel == 1 ? 8.0 : eq;         // written block
         if (k.pair) {
-            const bool two = k.pair == PAIR_PROJ || k.pair == PAIR_UPD || k.pair == PAIR_LEAD;
+            const bool two = k.pair != SOLO_PROJ && k.pair != SOLO_UPD;
             const int written = (k.pair == PAIR_PROJ || k.pair == SOLO_PROJ) ? 0 : (two && a.X2) ? 2 : 1;
             const int basis = k.red == RED_PROJ ? a.red_rows : a.pu;
             return (W * ((two ? 2 : 1) + written) + basis) * eq * rows_bytes +

@@ -29,8 +29,9 @@
 // so 2p + 11w columns per block instead of 4p + 9w.  V' = (I - Q Q^T) V is projected on Qj
 // where the single step projects V itself: the same C1 in exact arithmetic, and block-wise
 // modified instead of classical Gram-Schmidt for its last w rows.  FP32 storage would round V'
-// once more, so there P5 leaves Vj+1 alone (X = Vb^T Vj+1) and L applies all of [C1'; c]:
-// 3p + 10w columns.
+// once more, so there only P4 looks ahead: P6 of a block also reduces c = Qj^T Vj+1, P2 of the
+// next applies all of [C1'; c], and every stored value is rounded where the single step rounds
+// it: 3p + 10w columns.
 #include <algorithm>
 #include <cmath>
 #include <cstdio>
@@ -54,8 +55,8 @@ namespace {
 
 // P5 of a block: Vb = Vh R1^{-1} R2^{-1} - Q C2 written to Qo, G3, R3, and the block's R.
 sko_status solo_update(Engine& e, const BlockBufs& b, int p, const void* Q, int64_t ldq, const void* Vh, int64_t ldvh,
-                       void* Qo, int64_t ldqo, const double* C1, int64_t ldc1, const double* C2, double* Rcol,
-                       int64_t ldr, int col0) {
+                       void* Qo, int64_t ldqo, const double* C1, int64_t ldc1, const double* C2, int ldc2,
+                       double* Rcol, int64_t ldr, int col0) {
     PassArgs a{};
     a.Y = Vh;
     a.ldy = ldvh;
@@ -65,6 +66,7 @@ sko_status solo_update(Engine& e, const BlockBufs& b, int p, const void* Q, int6
     a.ldqu = ldq;
     a.pu = p;
     a.Cu = C2;
+    a.ldcu = ldc2;
     a.X = Qo;
     a.ldx = ldqo;
     SmallArgs sm{};
@@ -79,6 +81,7 @@ sko_status solo_update(Engine& e, const BlockBufs& b, int p, const void* Q, int6
     sm.C1 = C1;
     sm.ldc1 = ldc1;
     sm.C2 = C2;
+    sm.ldc2 = ldc2;
     sm.p = p;
     sm.Rout = Rcol;
     sm.ldr = ldr;
@@ -200,7 +203,7 @@ sko_status one_stage_block(Engine& e, const BlockBufs& b, int intra, int p, cons
         }
     }
     // P5: Vb = Qh - Q C2 written to Qo; G3 = Vb^T Vb; R3 = chol(G3); assemble R
-    if (p > 0 && (s = solo_update(e, b, p, Q, ldq, Vh, ldvh, Qo, ldqo, b.C1, p, b.C2, Rcol, ldr, col0))) return s;
+    if (p > 0 && (s = solo_update(e, b, p, Q, ldq, Vh, ldvh, Qo, ldqo, b.C1, p, b.C2, p, Rcol, ldr, col0))) return s;
     // P6: Qj = Vb R3^{-1}
     {
         PassArgs a{};
@@ -233,17 +236,45 @@ sko_status one_stage_lookahead(Engine& e, const BlockBufs& b, int intra, int nb,
         const int64_t ldd = p + W;  // leading dimension of this block's D
         double* Dj = D + (int64_t)(j & 1) * N * 2 * W;
         // C1 of this block, p x W with leading dimension p, from the block before
-        const double* C1 = j ? D + (int64_t)((j - 1) & 1) * N * 2 * W + (int64_t)W * p : nullptr;
+        double* C1 = j ? D + (int64_t)((j - 1) & 1) * N * 2 * W + (int64_t)W * p : nullptr;
         double* Rcol = R + (int64_t)p * N;
         void* Qj = block(Q, ldq, j);
         const void* Vh = j ? static_cast<const void*>(Qj) : V;
         const int64_t ldvh = j ? ldq : ldv;
-        {   // L (block 0: the reduction of V itself)
+        if (f32 && j) {  // P6 of the block before, c
+            void* Qp = block(Q, ldq, j - 1);
+            PassArgs a{};
+            a.Y = Qp;
+            a.ldy = ldq;
+            a.R1 = b.R3;
+            a.X = Qp;
+            a.ldx = ldq;
+            a.Y2 = cblock(V, ldv, j);
+            a.ldy2 = ldv;
+            SmallArgs sm{};
+            sm.op = OP_STORE;
+            sm.w = W;
+            sm.out = C1 + (p - W);
+            PassKey key{W, f32, RED_GRAM, false, 0, false};
+            key.pair = PAIR_CROSS;
+            if ((s = e.reduction(key, a, W, nullptr, 0, nullptr, 0, sm, 1.0, p))) return s;
+        }
+        {   // L; FP32: P2; block 0: the reduction of V itself
             PassArgs a{};
             PassKey key{W, f32, red_first, false, 0, false};
             a.Y = Vh;
             a.ldy = ldvh;
-            if (j) {
+            if (j && f32) {
+                key.upd = key.write = true;
+                a.Y = cblock(V, ldv, j);
+                a.ldy = ldv;
+                a.Qu = Q;
+                a.ldqu = ldq;
+                a.pu = p;
+                a.Cu = C1;
+                a.X = Qj;
+                a.ldx = ldq;
+            } else if (j) {
                 key.pair = PAIR_LEAD;
                 void* Qp = block(Q, ldq, j - 1);
                 a.Y = Qp;
@@ -251,16 +282,12 @@ sko_status one_stage_lookahead(Engine& e, const BlockBufs& b, int intra, int nb,
                 a.R1 = b.R3;
                 a.X = Qp;
                 a.ldx = ldq;
-                const bool raw = f32 || j == 1;  // y is still V_j itself
-                a.Y2 = raw ? cblock(V, ldv, j) : Qj;
-                a.ldy2 = raw ? ldv : ldq;
+                // V' of the first block behind block 0 is V itself
+                a.Y2 = j == 1 ? cblock(V, ldv, j) : Qj;
+                a.ldy2 = j == 1 ? ldv : ldq;
                 a.X2 = Qj;
                 a.ldx2 = ldq;
-                a.Qu = Q;
-                a.ldqu = ldq;
-                a.pu = f32 ? p - W : 0;
-                a.Cu = C1;
-                a.Cx = C1 + (p - W);
+                a.Cu = C1 + (p - W);
                 a.ldcu = p;
             }
             SmallArgs sm{};
@@ -305,11 +332,28 @@ sko_status one_stage_lookahead(Engine& e, const BlockBufs& b, int intra, int nb,
             key.pair = last ? SOLO_PROJ : PAIR_PROJ;
             if ((s = e.reduction(key, a, p, nullptr, 0, Q, ldq, sm, 1.0, last ? p : ldd))) return s;
         }
-        if (last) {
-            if ((s = solo_update(e, b, p, Q, ldq, Vh, ldvh, Qj, ldq, C1, p, Dj, Rcol, N, p))) return s;
-            break;
+        if (last || (f32 && p > 0)) {  // P5 of this block alone
+            if ((s = solo_update(e, b, p, Q, ldq, Vh, ldvh, Qj, ldq, C1, p, Dj, last ? p : (int)ldd, Rcol, N, p))) return s;
+            continue;
         }
-        // P5
+        if (f32) {  // block 0: Qh written, G3
+            a.X = Qj;
+            a.ldx = ldq;
+            SmallArgs sm{};
+            sm.op = OP_CHOL;
+            sm.w = W;
+            sm.col0 = p;
+            sm.out = b.G3;
+            sm.R = b.R3;
+            sm.assemble = 1;
+            sm.Ra = b.R2;
+            sm.Rb = b.R1;
+            sm.Rout = Rcol;
+            sm.ldr = N;
+            if ((s = e.reduction({W, f32, RED_GRAM, false, 2, true}, a, W, nullptr, 0, nullptr, 0, sm, 1.0))) return s;
+            continue;
+        }
+        // P5 of both blocks
         a.Qu = Q;
         a.ldqu = ldq;
         a.pu = p;
@@ -317,7 +361,7 @@ sko_status one_stage_lookahead(Engine& e, const BlockBufs& b, int intra, int nb,
         a.ldcu = (int)ldd;
         a.X = Qj;
         a.ldx = ldq;
-        if (!f32 && p > 0) {
+        if (p > 0) {
             a.X2 = block(Q, ldq, j + 1);
             a.ldx2 = ldq;
         }
@@ -1099,7 +1143,7 @@ sko_status two_stage_blocks(sko_ctx c, int64_t n, int32_t nb, int32_t w, const v
             } else {
                 // Q_bar = V_hat Rbar^{-1} and its Gram matrix
                 if ((s = e.rowop_reduction(Wb, Vh, ldvh, nullptr, 0, 0, nullptr, Rbpk, chain ? nullptr : Qb, ldq, nullptr,
-                                           0, 0, sm, Wb)))
+                                           0, 0, sm, Wb, nullptr, w)))
                     return s;
             }
             // Q_hat = Q_bar R_h^{-1}: from Q_bar, or from V_hat through both factors
@@ -1107,10 +1151,11 @@ sko_status two_stage_blocks(sko_ctx c, int64_t n, int32_t nb, int32_t w, const v
             const int64_t ldys = chain ? ldvh : ldq;
             const double* F1 = chain ? Rbpk : Rpk;
             const double* F2 = chain ? Rpk : nullptr;
+            const int pw = chain ? w : 0;
             if (reorth && p_old == 0) {
                 // its Gram matrix -> R_t
                 if ((s = e.rowop_reduction(Wb, Ysrc, ldys, nullptr, 0, 0, nullptr, F1, chain ? nullptr : Qb, ldq, nullptr,
-                                           0, 0, chol2, Wb, F2)))
+                                           0, 0, chol2, Wb, F2, pw)))
                     return s;
             } else if (fuse_proj) {
                 // stored, and C_2 = Q_old^T Q_hat
@@ -1119,10 +1164,10 @@ sko_status two_stage_blocks(sko_ctx c, int64_t n, int32_t nb, int32_t w, const v
                 sp2.w = Wb;
                 sp2.out = C2;
                 if ((s = e.rowop_reduction(Wb, Ysrc, ldys, nullptr, 0, 0, nullptr, F1, Qb, ldq, Q, ldq, p_old, sp2, p_old,
-                                           F2)))
+                                           F2, pw)))
                     return s;
             } else {
-                if ((s = e.rowop(Wb, Ysrc, ldys, nullptr, 0, 0, nullptr, F1, Qb, ldq, F2))) return s;
+                if ((s = e.rowop(Wb, Ysrc, ldys, nullptr, 0, 0, nullptr, F1, Qb, ldq, F2, nullptr, pw))) return s;
             }
         }
         if (reorth) {
@@ -1145,7 +1190,7 @@ sko_status two_stage_blocks(sko_ctx c, int64_t n, int32_t nb, int32_t w, const v
                     return s;
             }
             if (chain && p_old == 0) {
-                if ((s = e.rowop(Wb, Vh, ldvh, nullptr, 0, 0, nullptr, Rbpk, Qb, ldq, Rpk, Rpk2))) return s;
+                if ((s = e.rowop(Wb, Vh, ldvh, nullptr, 0, 0, nullptr, Rbpk, Qb, ldq, Rpk, Rpk2, w))) return s;
             } else {
                 if ((s = e.rowop(Wb, Qb, ldq, nullptr, 0, 0, nullptr, Rpk2, Qb, ldq))) return s;
             }

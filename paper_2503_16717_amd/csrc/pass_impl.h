@@ -137,10 +137,13 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
     constexpr bool F32 = sizeof(TY) == 4 && sizeof(TQ) == 4 && sizeof(TX) == 4;
     // rows per thread in phase A: two for float storage (8-byte accesses), except for wide
     // blocks with triangular solves or updates, whose two rows would not fit the registers
-    constexpr bool TWO = PAIR == PAIR_PROJ || PAIR == PAIR_UPD || PAIR == PAIR_LEAD;
+    constexpr bool TWO = PAIR == PAIR_PROJ || PAIR == PAIR_UPD || PAIR == PAIR_LEAD || PAIR == PAIR_CROSS;
     constexpr int WR = (PAIR == PAIR_PROJ || PAIR == PAIR_UPD) ? 2 * W : W;
     // the Gram of a pair runs on MFMA tiles as a projection does, with its W rows read from LDS
-    constexpr bool GMF = PAIR == PAIR_UPD;
+    // (PAIR_CROSS stages x as well, behind the reduced columns y)
+    constexpr bool GMF = PAIR == PAIR_UPD || PAIR == PAIR_CROSS;
+    constexpr int WS = PAIR == PAIR_CROSS ? 2 * W : WR;
+    constexpr int GA0 = PAIR == PAIR_CROSS ? W : 0;  // staged column of the Gram's first row
     constexpr int RPT = PAIR != PAIR_NONE ? 1 : (F32 && (W <= 8 || (NTRSM == 0 && !UPD))) ? 2 : 1;
     constexpr int STRIP = NT * RPT;
     constexpr int LDX = STRIP + 1;  // padded LDS leading dimension of the strip
@@ -155,7 +158,7 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
     // stores (and halves the LDS)
     using XS = typename std::conditional<sizeof(typename std::conditional<WRITE, TX, TY>::type) == 4, float,
                                          double>::type;
-    __shared__ XS xs[HAS_RED ? WR * LDX : 1];
+    __shared__ XS xs[HAS_RED ? WS * LDX : 1];
     __shared__ uint64_t hs[RED == RED_SKETCH_SPARSE ? STRIP : 1];
     constexpr int CB = (WR + 3) / 4;
     constexpr int PC = CB > 4 ? CB : 4;
@@ -168,7 +171,7 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
 
     // triangular factors (W x W, column-major) and update coefficients (pu x W)
     const CD gR0[2] = {as_uniform(a.R1), as_uniform(a.R2)};
-    const CD gC0 = as_uniform(a.Cu), gCx0 = as_uniform(a.Cx);
+    const CD gC0 = as_uniform(a.Cu);
     const int ldcu = a.ldcu ? a.ldcu : a.pu;
     // their diagonals' reciprocals: in registers, or for wide blocks in LDS, read again per
     // strip (two solves of 11 columns would hold 44 registers of them for the whole sweep:
@@ -253,12 +256,11 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
         // wide blocks load the factor and coefficient entries again per strip (w(w-1)/2 per
         // factor would not fit the SGPRs for the whole sweep); narrow blocks may hold them
         CD gR[2] = {gR0[0], gR0[1]};
-        CD gC = gC0, gCx = gCx0;
+        CD gC = gC0;
         if constexpr (W >= 10) {
             gR[0] = per_strip(gR[0]);
             gR[1] = per_strip(gR[1]);
             gC = per_strip(gC);
-            gCx = per_strip(gCx);
         }
         const int ri0 = RINV_LDS ? per_strip(0) : 0;
         auto rdiag = [&](int i) {
@@ -301,9 +303,9 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
                 TX* X = static_cast<TX*>(a.X);
                 TX* X2 = static_cast<TX*>(a.X2);
                 const TQ* Qr = static_cast<const TQ*>(a.Qu) + row;
-                if constexpr (PAIR == PAIR_UPD && sizeof(TX) == 8) {
+                if constexpr (PAIR == PAIR_UPD) {
                     update_rows<WZ, 1, TQ>(za, Qr, a.ldqu, a.pu, gC, ldcu);
-                } else if constexpr (PAIR == PAIR_UPD || PAIR == SOLO_UPD) {
+                } else if constexpr (PAIR == SOLO_UPD) {
                     double xa[1][W];
 #pragma unroll
                     for (int c = 0; c < W; ++c) xa[0][c] = z[c];
@@ -311,15 +313,11 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
 #pragma unroll
                     for (int c = 0; c < W; ++c) z[c] = xa[0][c];
                 } else if constexpr (PAIR == PAIR_LEAD) {
-                    double ya[1][W];
-#pragma unroll
-                    for (int c = 0; c < W; ++c) ya[0][c] = z[W + c];
-                    update_rows<W, 1, TQ>(ya, Qr, a.ldqu, a.pu, gC, ldcu);
 #pragma unroll
                     for (int c = 0; c < W; ++c) {
-                        double v = ya[0][c];
+                        double v = z[W + c];
 #pragma unroll
-                        for (int q = 0; q < W; ++q) v -= z[q] * gCx[q + c * ldcu];
+                        for (int q = 0; q < W; ++q) v -= z[q] * gC[q + c * ldcu];
                         z[W + c] = v;
                     }
                 }
@@ -330,7 +328,7 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
                 if constexpr (PAIR == PAIR_LEAD) {
 #pragma unroll
                     for (int c = 0; c < W; ++c) stv(X2 + row + c * a.ldx2, z[W + c]);
-                } else if constexpr (PAIR == PAIR_UPD && sizeof(TX) == 8) {
+                } else if constexpr (PAIR == PAIR_UPD) {
                     if (X2) {
 #pragma unroll
                         for (int c = 0; c < W; ++c) stv(X2 + row + c * a.ldx2, z[W + c]);
@@ -342,9 +340,9 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
                 for (int c = 0; c < WZ; ++c) z[c] = 0.0;
                 if constexpr (RED == RED_SKETCH_SPARSE) hs[tid] = 0;
             }
-            constexpr int Z0 = PAIR == PAIR_LEAD ? W : 0;
+            constexpr int Z0 = PAIR == PAIR_LEAD || PAIR == PAIR_CROSS ? W : 0;
 #pragma unroll
-            for (int c = 0; c < WR; ++c) xs[c * LDX + tid] = static_cast<XS>(z[Z0 + c]);
+            for (int c = 0; c < WS; ++c) xs[c * LDX + tid] = static_cast<XS>(z[(Z0 + c) % WZ]);
         }
         else if constexpr (RPT == 1)
         {
@@ -563,7 +561,7 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
                 // FP32 basis on 4 x 4 x 4 blocks: a 4-byte piece load moves half the bytes of a
                 // double one, so each lane loads two per column, as many bytes in flight as the
                 // FP64 form (the staged operand stays in float until its MFMA)
-                constexpr int UR = (RED == RED_PROJ && sizeof(TQ) == 4 && sizeof(XS) == 4 && B4) ? 8 : 4;
+                constexpr int UR = (RED == RED_PROJ && sizeof(TQ) == 4 && sizeof(XS) == 4 && B4 && !TWO) ? 8 : 4;
                 constexpr int GR = 4 * UR;
                 constexpr int GPW = STRIP / GR / C::NWAVE;  // row groups per wave
                 static_assert(STRIP % (GR * C::NWAVE) == 0, "row groups must tile the strip");
@@ -578,13 +576,15 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
                     // B operands: 16 x 16 x 4 tiles take column ci of the 4 rows; 4 x 4 x 4 blocks
                     // take column 4cb + lane % 4
                     double bv[B4 ? 1 : 4];
-                    XS bq[B4 ? CB : 1][UR];
+                    // (the two-block passes' 2W columns meet every tile: converted once)
+                    using BT = typename std::conditional<TWO, double, XS>::type;
+                    BT bq[B4 ? CB : 1][UR];
                     if constexpr (B4) {
 #pragma unroll
                         for (int cb = 0; cb < CB; ++cb) {
                             const int col = 4 * cb + (lane & 3);
 #pragma unroll
-                            for (int u = 0; u < UR; ++u) bq[cb][u] = (col < WR) ? xs[col * LDX + r0 + u] : XS(0);
+                            for (int u = 0; u < UR; ++u) bq[cb][u] = (col < WR) ? (BT)xs[col * LDX + r0 + u] : BT(0);
                         }
                     } else {
 #pragma unroll
@@ -625,7 +625,7 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
                             if (col < a.red_rows) {
                                 if constexpr (GMF) {
 #pragma unroll
-                                    for (int u = 0; u < 4; ++u) av[u] = (double)xs[ci * LDX + r0 + u];
+                                    for (int u = 0; u < 4; ++u) av[u] = (double)xs[(GA0 + ci) * LDX + r0 + u];
                                 } else if constexpr (RED == RED_PROJ)
                                     load_col4(Qp + (int64_t)col * a.ldqp + base + r0, full, base + r0, n, av);
                                 else
@@ -811,9 +811,16 @@ __global__ void __launch_bounds__((Cfg<W, RED>::NT), (min_waves<W, T, RED, UPD, 
     pass_body<W, Tys<T, T, T>, RED, UPD, NTRSM, WRITE, MTX>(a, blockIdx.x, gridDim.x);
 }
 
+// Waves per SIMD asked of a two-block projection: 11 columns on 7 and 8 tiles take 182 VGPRs in
+// FP32 when left alone (two waves: 3.58 ms on 105 columns at 2^24 rows; three: %MT8%).
+template <int W, int PAIR, int MTX>
+constexpr int min_waves_pair() {
+    return PAIR == PAIR_PROJ && W >= 9 && MTX != 4 ? 3 : 1;
+}
+
 template <int W, typename T, int RED, int PAIR, int MTX = 0>
-__global__ void __launch_bounds__((Cfg<W, RED>::NT)) pass_kernel_pair(const PassArgs a) {
-    constexpr int NTRSM = PAIR == PAIR_LEAD ? 1 : 2;
+__global__ void __launch_bounds__((Cfg<W, RED>::NT), (min_waves_pair<W, PAIR, MTX>())) pass_kernel_pair(const PassArgs a) {
+    constexpr int NTRSM = PAIR == PAIR_LEAD || PAIR == PAIR_CROSS ? 1 : 2;
     constexpr bool WRITE = PAIR != PAIR_PROJ && PAIR != SOLO_PROJ;
     pass_body<W, Tys<T, T, T>, RED, false, NTRSM, WRITE, MTX, PAIR>(a, blockIdx.x, gridDim.x);
 }
@@ -877,6 +884,10 @@ KernelPtr select_w_pair(const PassKey& k) {
             return mt == 4   ? &pass_kernel_pair<W, T, RED_PROJ, PAIR_PROJ, 4>
                    : mt == 6 ? &pass_kernel_pair<W, T, RED_PROJ, PAIR_PROJ, 6>
                              : &pass_kernel_pair<W, T, RED_PROJ, PAIR_PROJ>;
+        if constexpr (sizeof(T) == 4) {
+            if (k.pair == PAIR_CROSS && k.red == RED_GRAM) return &pass_kernel_pair<W, T, RED_GRAM, PAIR_CROSS>;
+            return nullptr;
+        }
         if (k.pair == PAIR_UPD && k.red == RED_GRAM) return &pass_kernel_pair<W, T, RED_GRAM, PAIR_UPD>;
         if (k.pair == PAIR_LEAD) {
             if (k.red == RED_GRAM) return &pass_kernel_pair<W, T, RED_GRAM, PAIR_LEAD>;

@@ -42,11 +42,12 @@ enum RedKind : int {
 enum PairKind : int {
     PAIR_NONE = 0,
     PAIR_PROJ = 1,  // x R1^{-1} R2^{-1} and y, nothing written: Qp^T [x y]
-    PAIR_UPD = 2,   // x R1^{-1} R2^{-1} - Qu Cu -> X; FP64: y - Qu Cu' -> X2 (Cu' the next W
-                    // columns of Cu; X2 null: y as it is); reduces x^T [x y]
-    PAIR_LEAD = 3,  // x R1^{-1} -> X; y - Qu Cu - x Cx -> X2; reduces a sketch of y, or y^T y
+    PAIR_UPD = 2,   // (FP64) x R1^{-1} R2^{-1} - Qu Cu -> X, y - Qu Cu' -> X2 (Cu' the next W
+                    // columns of Cu; X2 null: not stored); reduces x^T [x y]
+    PAIR_LEAD = 3,  // (FP64) x R1^{-1} -> X; y - x Cu -> X2; reduces a sketch of y, or y^T y
     SOLO_PROJ = 4,  // x R1^{-1} R2^{-1}, not written: Qp^T x
     SOLO_UPD = 5,   // x R1^{-1} R2^{-1} - Qu Cu -> X; reduces x^T x
+    PAIR_CROSS = 6, // (FP32) x R1^{-1} -> X; y as it is; reduces x^T y
 };
 constexpr int kMaxPairW = 12;  // block width up to which the two-block passes exist
 
@@ -74,12 +75,11 @@ struct PassArgs {
     int32_t part_rows_total;  // rows of the whole reduction output
     int32_t sk_k;
     int32_t sk_zeta;
-    int32_t ldcu;             // leading dimension of Cu and Cx (0: pu)
+    int32_t ldcu;             // leading dimension of Cu (0: pu)
     const void* Y2;           // second block of a two-block pass
     int64_t ldy2;
     void* X2;
     int64_t ldx2;
-    const double* Cx;         // PAIR_LEAD: coefficients of x, W x W
 };
 
 struct PassKey {
@@ -250,7 +250,8 @@ constexpr int kFusedMaxW = 40;
 constexpr int kFusedUnitRows = 256;
 hipError_t launch_wide_rowop_reduce(int64_t n, int W, bool f32, const void* Y, int64_t ldy, const double* Rpk,
                                     const double* Rpk2, void* X, int64_t ldx, const void* E, int64_t lde, int me,
-                                    double* partials, int* grid_out, hipStream_t st, const BatchReloc* br = nullptr);
+                                    double* partials, int* grid_out, hipStream_t st, const BatchReloc* br = nullptr,
+                                    int pw = 0);
 
 // X = Y - Q C for wide blocks (W <= 64), with the per-workgroup partials of the Gram matrix
 // X^T X (stride W * W, upper tiles) when `partials` is given.  Needs wide_update_fits (C and
@@ -265,12 +266,13 @@ hipError_t launch_wide_update(int64_t n, int W, bool f32, const void* Y, int64_t
 
 // Row-wise X = (Y - Qu Cu) * R^{-1} for wide blocks (w <= 64); used by the big-panel
 // close of the two-stage scheme.  Rpk is R in the packed form of SmallArgs::Rpk (null: no
-// solve); Rpk2 and Rpk3 (W <= kFusedMaxW, no update, one system) are solved with after it.
+// solve); Rpk2 and Rpk3 (W <= kFusedMaxW, no update, one system) are solved with after it.  pw (here and above, FP32 storage): panel
+// width of Rpk's columns, whose values are rounded to FP32 panel by panel.
 hipError_t launch_wide_rowop(int64_t n, int W, bool f32, const void* Y, int64_t ldy,
                              const void* Qu, int64_t ldqu, int pu, const double* Cu,
                              const double* Rpk, void* X, int64_t ldx, hipStream_t stream,
                              const BatchReloc* br = nullptr, const double* Rpk2 = nullptr,
-                             const double* Rpk3 = nullptr);
+                             const double* Rpk3 = nullptr, int pw = 0);
 
 // Zero `rows` runs of `width` bytes, consecutive runs `pitch` bytes apart (pointer, pitch
 // and width multiples of 4 bytes).  A kernel rather than hipMemsetAsync, so the work is an

@@ -81,8 +81,7 @@ __device__ __forceinline__ void rowop_red_body(const FusedArgs& fa, const int wg
 #pragma unroll
             for (int c = 0; c < WB; ++c)
                 x[c] = ldv_nt(lane_elem(Y + r0 + (int64_t)(c < w ? c : w - 1) * ldy, lane_bytes));
-            solve_cols<WB, 0>(x, per_strip(R0), w, sD);
-            if constexpr (TRSM >= 2) solve_cols<WB, 0>(x, per_strip(R20), w, sD + WB);
+            solve_chain<T, WB, TRSM>(x, R0, R20, R20, w, sD, ra.pw);
             if constexpr (WRITE) {
 #pragma unroll
                 for (int c = 0; c < WB; ++c) {
@@ -92,6 +91,8 @@ __device__ __forceinline__ void rowop_red_body(const FusedArgs& fa, const int wg
                         x[c] = static_cast<double>(v);  // reduce what was stored (FP32 storage: rounded)
                     }
                 }
+            } else {
+                round_cols<T, WB, WB>(x);
             }
         } else {
 #pragma unroll
@@ -247,11 +248,11 @@ hipError_t fused_dispatch(const FusedArgs& fa, int* grid, hipStream_t st, const 
 
 hipError_t launch_wide_rowop_reduce(int64_t n, int W, bool f32, const void* Y, int64_t ldy, const double* Rpk,
                                     const double* Rpk2, void* X, int64_t ldx, const void* E, int64_t lde, int me,
-                                    double* partials, int* grid_out, hipStream_t st, const BatchReloc* br) {
+                                    double* partials, int* grid_out, hipStream_t st, const BatchReloc* br, int pw) {
     if (W < 1 || W > kFusedMaxW || n < 1 || !grid_out || !partials) return hipErrorInvalidValue;
     if (br && (br->nact < 1 || *grid_out < 1)) return hipErrorInvalidValue;
     if (E && (me < 1 || me > 48)) return hipErrorInvalidValue;
-    const FusedArgs fa{RowopArgs{n, W, Y, ldy, nullptr, 0, 0, nullptr, Rpk, X, ldx, Rpk2, nullptr}, E, lde, E ? me : 0,
+    const FusedArgs fa{RowopArgs{n, W, Y, ldy, nullptr, 0, 0, nullptr, Rpk, X, ldx, Rpk2, nullptr, pw}, E, lde, E ? me : 0,
                        partials, (int64_t)(E ? me : W) * W};
     if (W <= 16) return f32 ? fused_dispatch<16, float>(fa, grid_out, st, br) : fused_dispatch<16, double>(fa, grid_out, st, br);
     if (W <= 24) return f32 ? fused_dispatch<24, float>(fa, grid_out, st, br) : fused_dispatch<24, double>(fa, grid_out, st, br);

@@ -64,9 +64,7 @@ __device__ __forceinline__ void rowop_body(const RowopArgs& ra, const int wg, co
 #pragma unroll
         for (int c = 0; c < WB; ++c) x[c] = ldv_nt(lane_elem(Y + r0 + (int64_t)(c < w ? c : w - 1) * ldy, lane_bytes));
         if constexpr (UPD) update_rows<WB, 1, T>(xa, Qu + row, ldqu, pu, Cs, pu, w);
-        if constexpr (TRSM >= 1) solve_cols<WB, 0>(x, per_strip(R0), w, sD);
-        if constexpr (TRSM >= 2) solve_cols<WB, 0>(x, per_strip(R20), w, sD + WB);
-        if constexpr (TRSM >= 3) solve_cols<WB, 0>(x, per_strip(R30), w, sD + 2 * WB);
+        solve_chain<T, WB, TRSM>(x, R0, R20, R30, w, sD, ra.pw);
 #pragma unroll
         for (int c = 0; c < WB; ++c)
             if (c < w) stv_nt(lane_elem(X + r0 + (int64_t)c * ldx, lane_bytes), static_cast<T>(x[c]));
@@ -275,11 +273,11 @@ void gemm_launch(const GemmArgs& ga, int grid, hipStream_t st, const BatchReloc*
 
 hipError_t launch_wide_rowop(int64_t n, int W, bool f32, const void* Y, int64_t ldy, const void* Qu, int64_t ldqu,
                              int pu, const double* Cu, const double* Rpk, void* X, int64_t ldx, hipStream_t st,
-                             const BatchReloc* br, const double* Rpk2, const double* Rpk3) {
+                             const BatchReloc* br, const double* Rpk2, const double* Rpk3, int pw) {
     if (W < 1 || W > 64 || n < 1) return hipErrorInvalidValue;
     if (br && br->nact < 1) return hipErrorInvalidValue;
     if (Rpk3 && !Rpk2) return hipErrorInvalidValue;
-    const RowopArgs ra{n, W, Y, ldy, Qu, ldqu, pu, Cu, Rpk, X, ldx, Rpk2, Rpk3};
+    const RowopArgs ra{n, W, Y, ldy, Qu, ldqu, pu, Cu, Rpk, X, ldx, Rpk2, Rpk3, pw};
     if (W <= 16) return f32 ? rowop_dispatch<16, float>(ra, st, br) : rowop_dispatch<16, double>(ra, st, br);
     if (W <= 24) return f32 ? rowop_dispatch<24, float>(ra, st, br) : rowop_dispatch<24, double>(ra, st, br);
     if (W <= 32) return f32 ? rowop_dispatch<32, float>(ra, st, br) : rowop_dispatch<32, double>(ra, st, br);
