@@ -32,6 +32,12 @@ namespace passk {
 
 typedef double double4_t __attribute__((ext_vector_type(4)));
 
+// Block width from which the Gram matrix runs on MFMA tiles: below, the vector form's W / 4
+// accumulator rows per wave are few; at 11 columns they take 66 VGPRs and 14 LDS reads per 64
+// rows and wave (FP64 after one solve, 1 000 003 rows: 36.8 us vector, 21.6 us MFMA; FP32 behind
+// the update on 66 columns, 2^24 rows: 1.35 and 1.27 ms).
+constexpr int kGramMfmaW = 9;
+
 // Per-(width, reduction) launch configuration.
 template <int W, int RED>
 struct Cfg {
@@ -72,6 +78,24 @@ __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
     return v;
+}
+
+// Four consecutive staged rows of one column (16-byte aligned).
+template <typename D>
+__device__ __forceinline__ void lds4(const double* p, D* v) {
+    const double2 a = reinterpret_cast<const double2*>(p)[0], b = reinterpret_cast<const double2*>(p)[1];
+    v[0] = (D)a.x;
+    v[1] = (D)a.y;
+    v[2] = (D)b.x;
+    v[3] = (D)b.y;
+}
+template <typename D>
+__device__ __forceinline__ void lds4(const float* p, D* v) {
+    const float4 a = *reinterpret_cast<const float4*>(p);
+    v[0] = (D)a.x;
+    v[1] = (D)a.y;
+    v[2] = (D)a.z;
+    v[3] = (D)a.w;
 }
 
 // Loads rows row0..row0+3 of one operand column (Q or a dense Theta) into av; rows at or
@@ -141,12 +165,14 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
     constexpr int WR = (PAIR == PAIR_PROJ || PAIR == PAIR_UPD) ? 2 * W : W;
     // the Gram of a pair runs on MFMA tiles as a projection does, with its W rows read from LDS
     // (PAIR_CROSS stages x as well, behind the reduced columns y)
-    constexpr bool GMF = PAIR == PAIR_UPD || PAIR == PAIR_CROSS;
+    // and so does the Gram of a block of 9 or more columns, except in FP32 without an update
+    // (11 columns after one solve, 2^24 rows: 0.245 ms vector, 0.257 ms MFMA)
+    constexpr bool GMF = PAIR == PAIR_UPD || PAIR == PAIR_CROSS ||
+                         (RED == RED_GRAM && W >= kGramMfmaW && (!F32 || UPD || PAIR == SOLO_UPD));
     constexpr int WS = PAIR == PAIR_CROSS ? 2 * W : WR;
     constexpr int GA0 = PAIR == PAIR_CROSS ? W : 0;  // staged column of the Gram's first row
     constexpr int RPT = PAIR != PAIR_NONE ? 1 : (F32 && (W <= 8 || (NTRSM == 0 && !UPD))) ? 2 : 1;
     constexpr int STRIP = NT * RPT;
-    constexpr int LDX = STRIP + 1;  // padded LDS leading dimension of the strip
     constexpr int RPL = STRIP / 64;
     constexpr int MAXA = C::MAXA;
     constexpr int MT = GMF ? 1 : MTX > 0 ? MTX : C::MT;  // MFMA tiles held (fewer: more waves per SIMD)
@@ -158,9 +184,16 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
     // stores (and halves the LDS)
     using XS = typename std::conditional<sizeof(typename std::conditional<WRITE, TX, TY>::type) == 4, float,
                                          double>::type;
-    __shared__ XS xs[HAS_RED ? WS * LDX : 1];
+    // padded LDS leading dimension of the strip: columns 16 bytes apart modulo the banks, so the
+    // MFMA operands read four rows of 16 columns as 16-byte vectors without bank conflicts
+    constexpr int LDX = STRIP + 16 / (int)sizeof(XS);
+    __shared__ __align__(16) XS xs[HAS_RED ? WS * LDX : 1];
     __shared__ uint64_t hs[RED == RED_SKETCH_SPARSE ? STRIP : 1];
-    constexpr int CB = (WR + 3) / 4;
+    // two-block projections of 16 to 24 columns: one 16 x 16 x 4 tile column for the first 16, 4 x
+    // 4 x 4 blocks for the others (a B operand register per row and 16 columns instead of four)
+    constexpr bool HYB = PAIR == PAIR_PROJ && WR >= 16;
+    constexpr int C16 = HYB ? 16 : 0;           // columns on 16 x 16 x 4
+    constexpr int CB = (WR - C16 + 3) / 4;      // 4-column blocks
     constexpr int PC = CB > 4 ? CB : 4;
     __shared__ double pred[MF ? PC * 64 * C::NWAVE : 1];  // cross-wave tile sums
 
@@ -213,10 +246,10 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
     constexpr bool SPM = RED == RED_SKETCH_SPARSE;
     constexpr int SPR = MT / 4;
     constexpr bool B4 = MF && !SPM && (W <= 12 || TWO);
-    double4_t dacc[(MF && !SPM && !B4) ? MT : 1];
-    double acc4[B4 ? MT * CB : 1];
+    double4_t dacc[(MF && !SPM && (!B4 || HYB)) ? MT : 1];
+    double acc4[B4 && CB > 0 ? MT * CB : 1];
 #pragma unroll
-    for (int i = 0; i < (B4 ? MT * CB : 1); ++i) acc4[i] = 0.0;
+    for (int i = 0; i < (B4 && CB > 0 ? MT * CB : 1); ++i) acc4[i] = 0.0;
     const int ntiles = (a.red_rows + 15) / 16;
 #pragma unroll
     for (int m = 0; m < (MF ? MT : 1); ++m) dacc[m] = double4_t{0.0, 0.0, 0.0, 0.0};
@@ -561,7 +594,7 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
                 // FP32 basis on 4 x 4 x 4 blocks: a 4-byte piece load moves half the bytes of a
                 // double one, so each lane loads two per column, as many bytes in flight as the
                 // FP64 form (the staged operand stays in float until its MFMA)
-                constexpr int UR = (RED == RED_PROJ && sizeof(TQ) == 4 && sizeof(XS) == 4 && B4 && !TWO) ? 8 : 4;
+                constexpr int UR = (RED == RED_PROJ && sizeof(TQ) == 4 && sizeof(XS) == 4 && B4) ? 8 : 4;
                 constexpr int GR = 4 * UR;
                 constexpr int GPW = STRIP / GR / C::NWAVE;  // row groups per wave
                 static_assert(STRIP % (GR * C::NWAVE) == 0, "row groups must tile the strip");
@@ -575,20 +608,30 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
                     const bool gfull = base + (gam + 1) * GR <= n;  // the whole group lies below n
                     // B operands: 16 x 16 x 4 tiles take column ci of the 4 rows; 4 x 4 x 4 blocks
                     // take column 4cb + lane % 4
-                    double bv[B4 ? 1 : 4];
+                    double bv[B4 && !HYB ? 1 : UR];
                     // (the two-block passes' 2W columns meet every tile: converted once)
                     using BT = typename std::conditional<TWO, double, XS>::type;
-                    BT bq[B4 ? CB : 1][UR];
+                    BT bq[B4 && CB > 0 ? CB : 1][UR];
+                    if constexpr (HYB) {
+#pragma unroll
+                        for (int u = 0; u < UR; u += 4) lds4(xs + ci * LDX + r0 + u, bv + u);
+                    }
                     if constexpr (B4) {
 #pragma unroll
                         for (int cb = 0; cb < CB; ++cb) {
-                            const int col = 4 * cb + (lane & 3);
+                            const int col = C16 + 4 * cb + (lane & 3);
 #pragma unroll
-                            for (int u = 0; u < UR; ++u) bq[cb][u] = (col < WR) ? (BT)xs[col * LDX + r0 + u] : BT(0);
+                            for (int u = 0; u < UR; u += 4) {
+                                if (col < WR) {
+                                    lds4(xs + col * LDX + r0 + u, &bq[cb][u]);
+                                } else {
+                                    bq[cb][u] = bq[cb][u + 1] = bq[cb][u + 2] = bq[cb][u + 3] = BT(0);
+                                }
+                            }
                         }
                     } else {
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) bv[u] = (ci < W) ? xs[ci * LDX + r0 + u] : 0.0;
+                        bv[0] = bv[1] = bv[2] = bv[3] = 0.0;
+                        if (ci < W) lds4(xs + ci * LDX + r0, bv);
                     }
 #pragma unroll
                     for (int m = 0; m < MT; ++m) {
@@ -613,19 +656,21 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
                                     }
                                 }
 #pragma unroll
-                                for (int u = 0; u < 8; ++u)
+                                for (int u = 0; u < 8; ++u) {
+                                    const double au = (double)(u < 4 ? v0[u & 3] : v1[u & 3]);
+                                    if constexpr (HYB)
+                                        dacc[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(au, bv[u], dacc[m], 0, 0, 0);
 #pragma unroll
                                     for (int cb = 0; cb < CB; ++cb)
                                         acc4[m * CB + cb] = __builtin_amdgcn_mfma_f64_4x4x4f64(
-                                            (double)(u < 4 ? v0[u & 3] : v1[u & 3]), (double)bq[cb][u], acc4[m * CB + cb],
-                                            0, 0, 0);
+                                            au, (double)bq[cb][u], acc4[m * CB + cb], 0, 0, 0);
+                                }
                                 continue;
                             }
                             double av[4] = {0.0, 0.0, 0.0, 0.0};
                             if (col < a.red_rows) {
                                 if constexpr (GMF) {
-#pragma unroll
-                                    for (int u = 0; u < 4; ++u) av[u] = (double)xs[(GA0 + ci) * LDX + r0 + u];
+                                    lds4(xs + (GA0 + ci) * LDX + r0, av);
                                 } else if constexpr (RED == RED_PROJ)
                                     load_col4(Qp + (int64_t)col * a.ldqp + base + r0, full, base + r0, n, av);
                                 else
@@ -633,11 +678,14 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
                             }
                             if constexpr (B4) {
 #pragma unroll
-                                for (int u = 0; u < 4; ++u)
+                                for (int u = 0; u < 4; ++u) {
+                                    if constexpr (HYB)
+                                        dacc[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[u], bv[u], dacc[m], 0, 0, 0);
 #pragma unroll
                                     for (int cb = 0; cb < CB; ++cb)
                                         acc4[m * CB + cb] = __builtin_amdgcn_mfma_f64_4x4x4f64(
                                             av[u], (double)bq[cb][u], acc4[m * CB + cb], 0, 0, 0);
+                                }
                             } else {
 #pragma unroll
                                 for (int u = 0; u < 4; ++u)
@@ -701,53 +749,47 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
                 __syncthreads();
             }
         }
-    } else if constexpr (B4) {
-        // v_mfma_f64_4x4x4 output layout (measured on gfx950): D[i][j] of block b sits in lane
-        // 4b + j + 16i, so lane l holds output row 16m + 4((l % 16) / 4) + l / 16 and column
-        // 4cb + l % 4 of instruction (m, cb).  The waves' values are summed through LDS in wave
-        // order.
-        double* out = a.partials + (int64_t)wg * a.part_stride;
-        const int srow = 4 * ((lane & 15) >> 2) + (lane >> 4);
-        const int col = lane & 3;
-#pragma unroll
-        for (int m = 0; m < MT; ++m) {
-            if (m >= ntiles) break;
-#pragma unroll
-            for (int cb = 0; cb < CB; ++cb) pred[(wave * PC + cb) * 64 + lane] = acc4[m * CB + cb];
-            __syncthreads();
-            if (wave == 0) {
-#pragma unroll
-                for (int cb = 0; cb < CB; ++cb) {
-                    double v = 0.0;
-                    for (int w2 = 0; w2 < C::NWAVE; ++w2) v += pred[(w2 * PC + cb) * 64 + lane];
-                    const int r = 16 * m + srow, c = 4 * cb + col;
-                    if (r < a.red_rows && c < WR) out[(a.red_row0 + r) + (int64_t)c * a.part_rows_total] = v;
-                }
-            }
-            __syncthreads();
-        }
     } else if constexpr (MF) {
-        // v_mfma_f64_16x16x4 output layout (measured on gfx950): D[i][j] of a tile sits in
-        // lane j + 16 * (i % 4), element i / 4.  The waves' tiles are summed through LDS in
-        // wave order.
+        // Output layouts (measured on gfx950).  v_mfma_f64_4x4x4: D[i][j] of block b sits in lane
+        // 4b + j + 16i, so lane l holds output row 16m + 4((l % 16) / 4) + l / 16 and column
+        // 4cb + l % 4 of instruction (m, cb).  v_mfma_f64_16x16x4: D[i][j] of a tile sits in lane
+        // j + 16 * (i % 4), element i / 4.  The waves' values are summed through LDS in wave order.
         double* out = a.partials + (int64_t)wg * a.part_stride;
-        const int j = lane & 15;
+        // K values per lane summed over the waves; put(k, value) on wave 0
+        auto wave_sums = [&](auto kc, auto&& val, auto&& put) {
+            constexpr int K = decltype(kc)::value;
 #pragma unroll
-        for (int m = 0; m < MT; ++m) {
-            if (m >= ntiles) break;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) pred[(wave * 4 + r) * 64 + lane] = dacc[m][r];
+            for (int k = 0; k < K; ++k) pred[(wave * PC + k) * 64 + lane] = val(k);
             __syncthreads();
             if (wave == 0) {
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
+                for (int k = 0; k < K; ++k) {
                     double v = 0.0;
-                    for (int w2 = 0; w2 < C::NWAVE; ++w2) v += pred[(w2 * 4 + r) * 64 + lane];
-                    const int col = 16 * m + (lane >> 4) + 4 * r;
-                    if (col < a.red_rows && j < W) out[(a.red_row0 + col) + (int64_t)j * a.part_rows_total] = v;
+                    for (int w2 = 0; w2 < C::NWAVE; ++w2) v += pred[(w2 * PC + k) * 64 + lane];
+                    put(k, v);
                 }
             }
             __syncthreads();
+        };
+#pragma unroll
+        for (int m = 0; m < MT; ++m) {
+            if (m >= ntiles) break;
+            if constexpr (B4 && CB > 0) {
+                const int r = 16 * m + 4 * ((lane & 15) >> 2) + (lane >> 4);
+                wave_sums(std::integral_constant<int, CB>{}, [&](int k) { return acc4[m * CB + k]; },
+                          [&](int k, double v) {
+                              const int c = C16 + 4 * k + (lane & 3);
+                              if (r < a.red_rows && c < WR) out[(a.red_row0 + r) + (int64_t)c * a.part_rows_total] = v;
+                          });
+            }
+            if constexpr (!B4 || HYB) {
+                const int c = lane & 15;
+                wave_sums(std::integral_constant<int, 4>{}, [&](int k) { return dacc[m][k]; },
+                          [&](int k, double v) {
+                              const int r = 16 * m + (lane >> 4) + 4 * k;
+                              if (r < a.red_rows && c < WR) out[(a.red_row0 + r) + (int64_t)c * a.part_rows_total] = v;
+                          });
+            }
         }
     } else if constexpr (GRAM) {
         double* out = a.partials + (int64_t)wg * a.part_stride;
@@ -811,15 +853,8 @@ __global__ void __launch_bounds__((Cfg<W, RED>::NT), (min_waves<W, T, RED, UPD, 
     pass_body<W, Tys<T, T, T>, RED, UPD, NTRSM, WRITE, MTX>(a, blockIdx.x, gridDim.x);
 }
 
-// Waves per SIMD asked of a two-block projection: 11 columns on 7 and 8 tiles take 182 VGPRs in
-// FP32 when left alone (two waves: 3.58 ms on 105 columns at 2^24 rows; three: %MT8%).
-template <int W, int PAIR, int MTX>
-constexpr int min_waves_pair() {
-    return PAIR == PAIR_PROJ && W >= 9 && MTX != 4 ? 3 : 1;
-}
-
 template <int W, typename T, int RED, int PAIR, int MTX = 0>
-__global__ void __launch_bounds__((Cfg<W, RED>::NT), (min_waves_pair<W, PAIR, MTX>())) pass_kernel_pair(const PassArgs a) {
+__global__ void __launch_bounds__((Cfg<W, RED>::NT)) pass_kernel_pair(const PassArgs a) {
     constexpr int NTRSM = PAIR == PAIR_LEAD || PAIR == PAIR_CROSS ? 1 : 2;
     constexpr bool WRITE = PAIR != PAIR_PROJ && PAIR != SOLO_PROJ;
     pass_body<W, Tys<T, T, T>, RED, false, NTRSM, WRITE, MTX, PAIR>(a, blockIdx.x, gridDim.x);
@@ -886,15 +921,15 @@ KernelPtr select_w_pair(const PassKey& k) {
                              : &pass_kernel_pair<W, T, RED_PROJ, PAIR_PROJ>;
         if constexpr (sizeof(T) == 4) {
             if (k.pair == PAIR_CROSS && k.red == RED_GRAM) return &pass_kernel_pair<W, T, RED_GRAM, PAIR_CROSS>;
-            return nullptr;
-        }
-        if (k.pair == PAIR_UPD && k.red == RED_GRAM) return &pass_kernel_pair<W, T, RED_GRAM, PAIR_UPD>;
-        if (k.pair == PAIR_LEAD) {
-            if (k.red == RED_GRAM) return &pass_kernel_pair<W, T, RED_GRAM, PAIR_LEAD>;
-            if (k.red == RED_SKETCH_DENSE) return &pass_kernel_pair<W, T, RED_SKETCH_DENSE, PAIR_LEAD>;
-            if (k.red == RED_SKETCH_SPARSE)
-                return mt == 4 ? &pass_kernel_pair<W, T, RED_SKETCH_SPARSE, PAIR_LEAD, 4>
-                               : &pass_kernel_pair<W, T, RED_SKETCH_SPARSE, PAIR_LEAD>;
+        } else {
+            if (k.pair == PAIR_UPD && k.red == RED_GRAM) return &pass_kernel_pair<W, T, RED_GRAM, PAIR_UPD>;
+            if (k.pair == PAIR_LEAD) {
+                if (k.red == RED_GRAM) return &pass_kernel_pair<W, T, RED_GRAM, PAIR_LEAD>;
+                if (k.red == RED_SKETCH_DENSE) return &pass_kernel_pair<W, T, RED_SKETCH_DENSE, PAIR_LEAD>;
+                if (k.red == RED_SKETCH_SPARSE)
+                    return mt == 4 ? &pass_kernel_pair<W, T, RED_SKETCH_SPARSE, PAIR_LEAD, 4>
+                                   : &pass_kernel_pair<W, T, RED_SKETCH_SPARSE, PAIR_LEAD>;
+            }
         }
     }
     return nullptr;
