@@ -40,7 +40,10 @@ struct BatchSys {
     const double* dinv;      // Jacobi D^{-1} or null
     uint64_t seed;           // sparse-sign sketch seed
     int32_t kupd;            // basis vectors in the solution update at a cycle end
-    int32_t pad_;
+    int32_t nd;              // diagonals of the operator in diagonal storage (0: CSR)
+    const void* dia;
+    int64_t ldd;
+    int32_t off[16];
 };
 
 struct BatchReloc {

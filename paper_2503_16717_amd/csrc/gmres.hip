@@ -66,6 +66,7 @@ struct GmCtx {
     const BatchReloc* br = nullptr;
     double avg_nnz = 0.0;
     int64_t max_n = 0;
+    bool dia_batch = false;  // every system's operator is stored by diagonals
     double rows_bytes = 0.0, nnz_bytes = 0.0;  // active totals for the byte accounting
     int spmv_cap = 0;
     PhaseTimer* pt = nullptr;  // phase times (sko_gmres_opts::phase_timing)
@@ -169,10 +170,13 @@ sko_status mpk(GmCtx& g, int from, int s) {
     const double rows = g.br ? g.rows_bytes : (double)g.n;
     g.phase(PhaseTimer::SPMV);
     for (int i = 1; i <= s; ++i) {
-        const int ev = g.c->prof.begin(std::string("spmv ") + (g.f32 ? "f32" : "f64"),
-                                       nnz * (g.f32 ? 8.0 : 12.0) + rows * (g.f32 ? 12.0 : 20.0), g.st);
+        const bool dia = g.br ? g.dia_batch : g.A.dia.val != nullptr;
+        const double eb = g.f32 ? 4.0 : 8.0;
+        const double bytes = dia ? (g.br ? nnz : (double)g.A.dia.nd * rows) * eb + rows * 2.0 * eb
+                                 : nnz * (eb + 4.0) + rows * (2.0 * eb + 4.0);
+        const int ev = g.c->prof.begin(std::string(dia ? "spmv dia " : "spmv ") + (g.f32 ? "f32" : "f64"), bytes, g.st);
         if (g.br)
-            SKO_HIP(launch_spmv_batched(g.f32, g.avg_nnz, g.max_n, col_ptr(g, from + i - 1), col_ptr(g, from + i),
+            SKO_HIP(launch_spmv_batched(g.f32, g.avg_nnz, g.dia_batch, g.max_n, col_ptr(g, from + i - 1), col_ptr(g, from + i),
                                         g.spmv_cap, g.st, *g.br));
         else if (g.newton_on)  // step i - 1 of the Newton recurrence
             SKO_HIP(launch_spmv(g.A, g.f32, col_ptr(g, from + i - 1), col_ptr(g, from + i), g.grid_cap, g.st,
@@ -194,8 +198,11 @@ sko_status mpk_panel(GmCtx& g, int from, int s) {
     g.phase(PhaseTimer::SPMV);
     SKO_HIP(launch_widen(g.n, static_cast<const float*>(col_ptr(g, from)), P, g.grid_cap, g.st));
     for (int i = 1; i <= s; ++i) {
-        const int ev = g.c->prof.begin("spmv f32 values, f64 vectors",
-                                       (double)g.A.nnz * 8.0 + (double)g.n * 20.0, g.st);
+        const bool dia = g.A.dia.val != nullptr;
+        const int ev = g.c->prof.begin(dia ? "spmv dia f32 values, f64 vectors" : "spmv f32 values, f64 vectors",
+                                       dia ? (double)g.n * (4.0 * g.A.dia.nd + 16.0)
+                                           : (double)g.A.nnz * 8.0 + (double)g.n * 20.0,
+                                       g.st);
         if (g.newton_on)
             SKO_HIP(launch_spmv_panel(g.A, P + (int64_t)(i - 1) * g.ld, P + (int64_t)i * g.ld, g.grid_cap, g.st,
                                       g.newton + (i - 1), g.newton + g.s + (i - 1),
@@ -559,13 +566,32 @@ sko_status gmres_impl(sko_ctx c, const sko_csr* A, const double* b, double* x, c
     const int eb = g.f32 ? 4 : 8;
     const int k = sketch_rows(g), kr = sketch_rows(g, false);
 
+    EventPair ev_total;
+    SKO_HIP(ev_total.create());
+    SKO_HIP(hipEventRecord(ev_total.a, g.st));
+    // ---- CSR structure check before any kernel indexes through it, and the diagonal scan; its
+    // words stand at the start of the workspace until they are read
+    sko_status s = ensure_workspace(c, 256);
+    if (s) return s;
+    if ((s = ensure_pinned(c, 256))) return s;
+    if ((s = ensure_zerocopy(c))) return s;
+    DiaView dia;
+    {
+        int* words = static_cast<int*>(c->ws);
+        int32_t* host = static_cast<int32_t*>(c->pinned);
+        SKO_HIP(launch_zero(words, 256, g.st));
+        SKO_HIP(launch_csr_check(A->n, A->nnz, A->rowptr, A->colind, words, g.st));
+        SKO_HIP(hipMemcpyAsync(host, words, sizeof(int32_t) * kScanWords, hipMemcpyDeviceToHost, g.st));
+        SKO_HIP(hipStreamSynchronize(g.st));
+        if (host[0]) return SKO_EINVAL;
+        if (!scan_diagonals(host, A->n, A->nnz, eb, dia)) dia = DiaView{};
+    }
+
     // ---- workspace
     Arena ar(c);
     const size_t o_Q = ar.reserve((size_t)eb * g.ld * (m + 1));
     const bool panel64 = g.f32 && g.two;
     const size_t o_P = panel64 ? ar.reserve(sizeof(double) * g.ld * g.W) : 0;
-    const bool own_vals = g.jacobi || g.f32;
-    const size_t o_val = own_vals ? ar.reserve((size_t)eb * A->nnz) : 0;
     const size_t o_dinv = g.jacobi ? ar.reserve(sizeof(double) * A->n) : 0;
     const int64_t nstrips = (A->n + kPassThreads - 1) / kPassThreads;
     const int gmax = (int)std::min<int64_t>(nstrips, (int64_t)std::max(1, c->cus) * 8);
@@ -578,10 +604,21 @@ sko_status gmres_impl(sko_ctx c, const sko_csr* A, const double* b, double* x, c
     const SmallLayout L = small_layout(m, g.W, kr, k, g.Wb, g.two);
     const size_t o_small = ar.reserve(L.bytes);
     const size_t o_newton = ar.reserve(sizeof(double) * 2 * g.s);
-    sko_status s = ensure_workspace(c, ar.used());
+    // the matrix-powers operator: by diagonals, or (where that form does not pay or does not fit)
+    // the scaled or narrowed CSR values
+    const Arena rest = ar;
+    auto operator_bytes = [&]() -> size_t {
+        return dia.nd ? (size_t)eb * dia.ld * dia.nd : (g.jacobi || g.f32) ? (size_t)eb * A->nnz : 0;
+    };
+    size_t o_val = ar.reserve(operator_bytes());
+    s = ensure_workspace(c, ar.used());
+    if (s == SKO_ENOMEM && dia.nd) {
+        dia = DiaView{};
+        ar = rest;
+        o_val = ar.reserve(operator_bytes());
+        s = ensure_workspace(c, ar.used());
+    }
     if (s) return s;
-    if ((s = ensure_pinned(c, 64))) return s;
-    if ((s = ensure_zerocopy(c))) return s;
     g.host = static_cast<double*>(c->pinned);
     g.newton = ar.at<double>(o_newton);
     g.Q = ar.at<void>(o_Q);
@@ -589,28 +626,19 @@ sko_status gmres_impl(sko_ctx c, const sko_csr* A, const double* b, double* x, c
     g.dinv = g.jacobi ? ar.at<double>(o_dinv) : nullptr;
     carve_small(g, ar.at<char>(o_small), L, kr, k);
 
-    EventPair ev_total;
-    SKO_HIP(ev_total.create());
     PhaseTimer pt;
     pt.on = o->phase_timing != 0;
     g.pt = &pt;
-    SKO_HIP(hipEventRecord(ev_total.a, g.st));
     SKO_HIP(launch_zero(g.status, 256, g.st));
 
-    // ---- CSR structure check before any kernel indexes through it
-    {
-        int bad = 0;
-        SKO_HIP(launch_csr_check(A->n, A->nnz, A->rowptr, A->colind, g.status + 32, g.st));
-        SKO_HIP(hipMemcpyAsync(reinterpret_cast<int*>(g.host + 4), g.status + 32, sizeof(int), hipMemcpyDeviceToHost,
-                               g.st));
-        SKO_HIP(hipStreamSynchronize(g.st));
-        bad = *reinterpret_cast<int*>(g.host + 4);
-        if (bad) return SKO_EINVAL;
-    }
-    // ---- operator set-up: Jacobi scaling / float copy of the MPK values
-    g.A = CsrView{A->n, A->nnz, A->rowptr, A->colind, A->val, A->val};
+    // ---- operator set-up: diagonal form, or Jacobi scaling / float copy of the MPK values
+    g.A = CsrView{A->n, A->nnz, A->rowptr, A->colind, A->val, A->val, DiaView{}};
     if (g.jacobi) SKO_HIP(launch_jacobi_setup(A->n, A->nnz, A->rowptr, A->colind, A->val, g.dinv, g.status, g.st));
-    if (own_vals) {
+    if (dia.nd) {
+        dia.val = ar.at<void>(o_val);
+        SKO_HIP(launch_fill_diagonals(A->n, A->rowptr, A->colind, A->val, g.dinv, g.f32, dia, g.st));
+        g.A.dia = dia;
+    } else if (g.jacobi || g.f32) {
         void* vo = ar.at<void>(o_val);
         SKO_HIP(launch_scale_values(A->nnz, A->colind, A->val, g.dinv, g.f32, vo, g.st));
         g.A.val_op = vo;
@@ -835,14 +863,40 @@ sko_status gmres_batched_impl(sko_ctx c, int32_t nsys, const sko_csr* A, const d
     const size_t part_bytes = ((sizeof(double) * part_doubles + 255) / 256) * 256;
     const SmallLayout L = small_layout(m, g.W, kr, k, g.Wb, g.two);
 
-    // ---- workspace: per-system basis / operator values / D^{-1}, then the equal-sized small
-    // blocks, partial sums, the system table and the active list
+    EventPair ev_total;
+    SKO_HIP(ev_total.create());
+    SKO_HIP(hipEventRecord(ev_total.a, g.st));
+    // ---- per system: CSR check and diagonal scan, their words at the start of the workspace
+    sko_status s = ensure_workspace(c, sizeof(int32_t) * 32 * (size_t)nsys);
+    if (s) return s;
+    if ((s = ensure_pinned(c, sizeof(int32_t) * 32 * (size_t)nsys))) return s;
+    std::vector<DiaView> dia(nsys);
+    g.dia_batch = true;
+    {
+        int* words = static_cast<int*>(c->ws);
+        int32_t* host = static_cast<int32_t*>(c->pinned);
+        SKO_HIP(launch_zero(words, sizeof(int32_t) * 32 * (size_t)nsys, g.st));
+        for (int32_t i = 0; i < nsys; ++i)
+            SKO_HIP(launch_csr_check(A[i].n, A[i].nnz, A[i].rowptr, A[i].colind, words + 32 * i, g.st));
+        SKO_HIP(hipMemcpyAsync(host, words, sizeof(int32_t) * 32 * (size_t)nsys, hipMemcpyDeviceToHost, g.st));
+        SKO_HIP(hipStreamSynchronize(g.st));
+        for (int32_t i = 0; i < nsys; ++i) {
+            if (host[32 * i]) {
+                S[i].finished = true;
+                S[i].result = SKO_EINVAL;
+            } else if (!scan_diagonals(host + 32 * i, A[i].n, A[i].nnz, eb, dia[i])) {
+                g.dia_batch = false;  // one kernel serves every system: all by diagonals or none
+            }
+        }
+    }
+
+    // ---- workspace: per-system basis / D^{-1}, then the equal-sized small blocks, partial sums,
+    // the system table and the active list, and the per-system operator values
     Arena ar(c);
     std::vector<size_t> o_Q(nsys), o_val(nsys, 0), o_dinv(nsys, 0);
     for (int32_t i = 0; i < nsys; ++i) {
         const int64_t ldi = ((A[i].n + 63) / 64) * 64;
         o_Q[i] = ar.reserve((size_t)eb * ldi * (m + 1));
-        if (own_vals) o_val[i] = ar.reserve((size_t)eb * A[i].nnz);
         if (g.jacobi) o_dinv[i] = ar.reserve(sizeof(double) * A[i].n);
     }
     const size_t o_small = ar.reserve(L.bytes * nsys);
@@ -850,7 +904,22 @@ sko_status gmres_batched_impl(sko_ctx c, int32_t nsys, const sko_csr* A, const d
     const size_t o_tbl = ar.reserve(sizeof(BatchSys) * nsys);
     const size_t o_act = ar.reserve(sizeof(int) * nsys);
     const size_t o_blk = ar.reserve(sizeof(int) * (nsys + 1));
-    sko_status s = ensure_workspace(c, ar.used());
+    const Arena rest = ar;
+    auto reserve_operators = [&]() {
+        for (int32_t i = 0; i < nsys; ++i) {
+            if (g.dia_batch)
+                o_val[i] = ar.reserve((size_t)eb * dia[i].ld * dia[i].nd);
+            else if (own_vals)
+                o_val[i] = ar.reserve((size_t)eb * A[i].nnz);
+        }
+        return ensure_workspace(c, ar.used());
+    };
+    s = reserve_operators();
+    if (s == SKO_ENOMEM && g.dia_batch) {
+        g.dia_batch = false;
+        ar = rest;
+        s = reserve_operators();
+    }
     if (s) return s;
     const size_t pin_tbl = 0, pin_act = sizeof(BatchSys) * nsys, pin_dbl = pin_act + ((sizeof(int) * nsys + 63) / 64) * 64,
                  pin_int = pin_dbl + sizeof(double) * nsys, pin_blk = pin_int + ((sizeof(int) * nsys + 63) / 64) * 64,
@@ -883,12 +952,9 @@ sko_status gmres_batched_impl(sko_ctx c, int32_t nsys, const sko_csr* A, const d
     g.spmv_cap = (int)std::max<int64_t>(1, std::min<int64_t>((groups8 + 7) / 8, cap));
     const size_t st_off = (size_t)(reinterpret_cast<char*>(g.status) - small_of(0));
 
-    EventPair ev_total;
-    SKO_HIP(ev_total.create());
     PhaseTimer pt;
     pt.on = o->phase_timing != 0;
     g.pt = &pt;
-    SKO_HIP(hipEventRecord(ev_total.a, g.st));
     SKO_HIP(launch_zero_2d(small0 + st_off, L.bytes, 256, nsys, g.st));
 
     // strided reads of one double / one int of every system's small block
@@ -904,19 +970,7 @@ sko_status gmres_batched_impl(sko_ctx c, int32_t nsys, const sko_csr* A, const d
         return SKO_OK;
     };
 
-    // ---- per system: CSR check, operator set-up, ||b|| (single-system launches)
-    for (int32_t i = 0; i < nsys; ++i) {
-        int* st_i = reinterpret_cast<int*>(small_of(i) + st_off);
-        SKO_HIP(launch_csr_check(A[i].n, A[i].nnz, A[i].rowptr, A[i].colind, st_i + 32, g.st));
-    }
-    SKO_HIP(hipMemcpy2DAsync(int_h, sizeof(int), g.status + 32, L.bytes, sizeof(int), nsys, hipMemcpyDeviceToHost,
-                             g.st));
-    SKO_HIP(hipStreamSynchronize(g.st));
-    for (int32_t i = 0; i < nsys; ++i)
-        if (int_h[i]) {
-            S[i].finished = true;
-            S[i].result = SKO_EINVAL;
-        }
+    // ---- per system: operator set-up, ||b|| (single-system launches)
     for (int32_t i = 0; i < nsys; ++i) {
         const int64_t ldi = ((A[i].n + 63) / 64) * 64;
         BatchSys& d = tbl_h[i];
@@ -939,7 +993,14 @@ sko_status gmres_batched_impl(sko_ctx c, int32_t nsys, const sko_csr* A, const d
         if (g.jacobi)
             SKO_HIP(launch_jacobi_setup(A[i].n, A[i].nnz, A[i].rowptr, A[i].colind, A[i].val,
                                         const_cast<double*>(d.dinv), st_i, g.st));
-        if (own_vals) {
+        if (g.dia_batch) {
+            dia[i].val = ar.at<void>(o_val[i]);
+            SKO_HIP(launch_fill_diagonals(A[i].n, A[i].rowptr, A[i].colind, A[i].val, d.dinv, g.f32, dia[i], g.st));
+            d.dia = dia[i].val;
+            d.ldd = dia[i].ld;
+            d.nd = dia[i].nd;
+            std::copy(dia[i].off, dia[i].off + kMaxDiags, d.off);
+        } else if (own_vals) {
             void* vo = ar.at<void>(o_val[i]);
             SKO_HIP(launch_scale_values(A[i].nnz, A[i].colind, A[i].val, d.dinv, g.f32, vo, g.st));
             d.val_op = vo;
@@ -994,7 +1055,7 @@ sko_status gmres_batched_impl(sko_ctx c, int32_t nsys, const sko_csr* A, const d
                                          (int64_t)sizeof(int) * (nsys + 1)};
         if (!batch_regions_disjoint(br, shared, shared_bytes, 3)) return SKO_EINVAL;
     }
-    const int flat_unit = spmv_flat_unit(g.f32, g.avg_nnz);
+    const int flat_unit = spmv_flat_unit(g.f32, g.avg_nnz, g.dia_batch);
     g.br = &br;
 
     Engine e(c, max_n, g.W, g.f32, g.sk);

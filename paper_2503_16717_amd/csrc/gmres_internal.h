@@ -10,6 +10,27 @@
 
 namespace sko {
 
+// A matrix whose nonzeros lie on at most kMaxDiags diagonals, in diagonal storage: value k of
+// row i (column i + off[k], off ascending) at val[k * ld + i], zero where the row has none.
+constexpr int kMaxDiags = 16;
+struct DiaView {
+    const void* val = nullptr;  // MPK operator values (double or float); null: not in this form
+    int64_t ld = 0;
+    int nd = 0;
+    int32_t off[kMaxDiags] = {};
+};
+
+// Words csr_check writes: [0] nonzero if the structure is invalid, [1] nonzero if some row's
+// columns are not strictly ascending or there are more than kMaxDiags diagonals, [2..] the
+// diagonals' offsets plus 2^31 (unsigned) in no order, 0 where unused.  All zero before the
+// launch.
+constexpr int kScanWords = 2 + kMaxDiags;
+// Diagonals of a scanned matrix (ascending in d.off, d.nd of them); false where diagonal storage
+// does not pay: eb bytes a value on every row and diagonal against the CSR form's values,
+// column indices and row pointers.  A 7-point stencil moves 56 + 16 bytes per row instead of
+// 88 + 16 (FP64), a matrix with many part-filled diagonals would move more.
+bool scan_diagonals(const int32_t* words, int64_t n, int64_t nnz, int eb, DiaView& d);
+
 // CSR operand: structure + FP64 values of A (explicit residual) and the values used by
 // the matrix-powers kernel (A D^{-1} in double or float, or A itself).
 struct CsrView {
@@ -19,6 +40,7 @@ struct CsrView {
     const int32_t* colind;
     const double* val;     // A, double
     const void* val_op;    // MPK operator values (double or float)
+    DiaView dia;           // the same values by diagonals (dia.val null: not)
 };
 
 // y = A x, or with a Newton step (na != null) y = A x - (*na) x + (*nb) z (na, nb: device
@@ -35,8 +57,12 @@ hipError_t launch_residual(const CsrView& A, const double* x, const double* b, b
                            int grid, hipStream_t st);
 hipError_t launch_update(int64_t n, bool f32, const void* Q, int64_t ldq, int k, const double* y,
                          const double* dinv, double* x, hipStream_t st);
-hipError_t launch_csr_check(int64_t n, int64_t nnz, const int32_t* rowptr, const int32_t* colind, int* bad,
+// `words`: kScanWords ints, zero.
+hipError_t launch_csr_check(int64_t n, int64_t nnz, const int32_t* rowptr, const int32_t* colind, int* words,
                             hipStream_t st);
+// d.val from the CSR values (scaled by dinv[column] if given).
+hipError_t launch_fill_diagonals(int64_t n, const int32_t* rowptr, const int32_t* colind, const double* val,
+                                 const double* dinv, bool f32, const DiaView& d, hipStream_t st);
 hipError_t launch_jacobi_setup(int64_t n, int64_t nnz, const int32_t* rowptr, const int32_t* colind,
                                const double* val, double* dinv, int* status, hipStream_t st);
 hipError_t launch_scale_values(int64_t nnz, const int32_t* colind, const double* val, const double* dinv, bool f32,
@@ -85,8 +111,8 @@ hipError_t launch_ritz(const GmSmallArgs& a, int k, double* newton, hipStream_t 
 // basis addresses, partials and y template workspace addresses.
 // Rows one workgroup iteration of the batched SpMV covers for this value type and mean row
 // length; the flat launch's BatchReloc::chunk is a multiple of it.
-int spmv_flat_unit(bool f32, double avg_nnz);
-hipError_t launch_spmv_batched(bool f32, double avg_nnz, int64_t max_n, const void* x, void* y, int grid_cap,
+int spmv_flat_unit(bool f32, double avg_nnz, bool dia);
+hipError_t launch_spmv_batched(bool f32, double avg_nnz, bool dia, int64_t max_n, const void* x, void* y, int grid_cap,
                                hipStream_t st, const BatchReloc& br);
 hipError_t launch_residual_batched(bool f32, double avg_nnz, void* r, double* partials, int grid, hipStream_t st,
                                    const BatchReloc& br);

@@ -6,6 +6,7 @@
 //   * solution update x += D^{-1} Q y;
 //   * Jacobi set-up: D^{-1} and the column-scaled values of A D^{-1};
 //   * the small Hessenberg bookkeeping (T_in / T_out, Givens least squares).
+#include <algorithm>
 #include <cmath>
 
 #include "batch.h"
@@ -327,18 +328,179 @@ __global__ void __launch_bounds__(NT) update_kernel_batched(const T* Q0, const d
     update_body<T>(d.n, batch_ptr(br, sys, d, Q0), d.ld, d.kupd, batch_ptr(br, sys, d, y0), d.dinv, d.x);
 }
 
-// CSR structure check; touches rowptr[0..n] and colind[0..nnz) only by their own indices.
-__global__ void csr_check_kernel(int64_t n, int64_t nnz, const int32_t* __restrict__ rowptr,
-                                 const int32_t* __restrict__ colind, int* bad) {
+// Diagonal storage: y = A x with RPT consecutive rows per thread (row0 = base + RPT tid of NT RPT
+// rows).  Per row and diagonal one value streams in; x is read nd times, all but the first from
+// the caches.  The sum runs over the diagonals in ascending column order, as over a CSR row
+// (a diagonal the row lacks adds 0 x, so x must be finite there for the same sum).
+// ND: number of diagonals at compile time (all loads in flight together), 0: any.
+template <int ND, int RPT, typename TV, typename TX, typename TY>
+__device__ __forceinline__ void dia_rows(int64_t n, int64_t base, const TV* __restrict__ val, int64_t ldd, int nd_,
+                                         const int32_t* off, const TX* __restrict__ x, TY* __restrict__ y,
+                                         const NewtonStep<TX>& ns = NewtonStep<TX>{}) {
+    const int nd = ND > 0 ? ND : nd_;
+    const int64_t row0 = base + (int64_t)RPT * threadIdx.x;
+    constexpr int CH = ND > 0 ? ND : 4;  // diagonals whose loads are issued together
+    // every column of these rows lies inside the matrix: no bounds checks
+    const bool inner = base + off[0] >= 0 && base + NT * RPT <= n && base + NT * RPT + off[nd - 1] <= n;
+    double s[RPT];
+#pragma unroll
+    for (int r = 0; r < RPT; ++r) s[r] = 0.0;
+    if (inner) {
+        for (int k0 = 0; k0 < nd; k0 += CH) {
+            RawRows<RPT, TV> v[CH];
+            RawRows<RPT, TX> xv[CH];
+#pragma unroll
+            for (int u = 0; u < CH; ++u) {
+                if (ND > 0 || k0 + u < nd) {
+                    const TV* vp = val + (int64_t)(k0 + u) * ldd + row0;
+                    const TX* xp = x + row0 + off[k0 + u];
+                    if constexpr (RPT == 2) {
+                        typedef typename Unaligned<TV>::v2 V2;
+                        const V2 t = __builtin_nontemporal_load(reinterpret_cast<const V2*>(vp));
+                        v[u].v[0] = t.x;
+                        v[u].v[1] = t.y;
+                        const auto tx = *reinterpret_cast<const typename Unaligned<TX>::v2*>(xp);
+                        xv[u].v[0] = tx.x;
+                        xv[u].v[1] = tx.y;
+                    } else {
+                        v[u].v[0] = __builtin_nontemporal_load(vp);
+                        xv[u].v[0] = *xp;
+                    }
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < CH; ++u) {
+                if (ND > 0 || k0 + u < nd) {
+#pragma unroll
+                    for (int r = 0; r < RPT; ++r) s[r] += (double)v[u].v[r] * (double)xv[u].v[r];
+                }
+            }
+        }
+    } else {
+        for (int r = 0; r < RPT; ++r) {
+            const int64_t row = row0 + r;
+            if (row >= n) break;
+            for (int k = 0; k < nd; ++k) {
+                const int64_t c = row + off[k];
+                if (c >= 0 && c < n) s[r] += (double)val[(int64_t)k * ldd + row] * (double)x[c];
+            }
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < RPT; ++r)
+        if (row0 + r < n) s[r] += newton_term(ns, x, row0 + r);
+    if (inner && RPT == 2) {
+        typedef typename Unaligned<TY>::v2 V2;
+        *reinterpret_cast<V2*>(y + row0) = V2{static_cast<TY>(s[0]), static_cast<TY>(s[RPT - 1])};
+    } else {
+#pragma unroll
+        for (int r = 0; r < RPT; ++r)
+            if (row0 + r < n) y[row0 + r] = static_cast<TY>(s[r]);
+    }
+}
+
+template <int ND, int RPT, typename TV, typename TX, typename TY>
+__global__ void __launch_bounds__(NT) spmv_dia_kernel(int64_t n, const DiaView d, const TX* __restrict__ x,
+                                                      TY* __restrict__ y, const NewtonStep<TX> ns) {
+    dia_rows<ND, RPT, TV, TX, TY>(n, (int64_t)blockIdx.x * (NT * RPT), static_cast<const TV*>(d.val), d.ld, d.nd, d.off,
+                                  x, y, ns);
+}
+
+// Flat batched form: workgroup b serves rows [r0, r0 + chunk) of the system of its active slot.
+template <int ND, int RPT, typename TV, typename TX, typename TY>
+__global__ void __launch_bounds__(NT) spmv_dia_kernel_flat(const TX* x0, TY* y0, const BatchReloc br) {
+    const int slot = flat_slot(br);
+    const int sys = br.active[slot];
+    const BatchSys& d = br.sys[sys];
+    const TX* x = batch_ptr(br, sys, d, x0);
+    TY* y = batch_ptr(br, sys, d, y0);
+    const int64_t r0 = (int64_t)(blockIdx.x - br.blk0[slot]) * br.chunk;
+    const int64_t r1 = r0 + br.chunk < d.n ? r0 + br.chunk : d.n;
+    for (int64_t base = r0; base < r1; base += NT * RPT)
+        dia_rows<ND, RPT, TV, TX, TY>(d.n, base, static_cast<const TV*>(d.dia), d.ldd, d.nd, d.off, x, y);
+}
+
+constexpr int32_t kNoDiag = 0;  // words hold offset + kDiagBias, so 0 means unused
+constexpr int64_t kDiagBias = (int64_t)1 << 31;
+
+// CSR structure check and diagonal scan, one row per thread (a row is walked only where its
+// pointers are in range, so nothing outside colind is read).  The diagonals seen by a
+// workgroup collect in LDS first; each is then entered once in the global table.
+__global__ void __launch_bounds__(NT) csr_check_kernel(int64_t n, int64_t nnz, const int32_t* __restrict__ rowptr,
+                                                       const int32_t* __restrict__ colind, int* words) {
+    __shared__ unsigned tab[kMaxDiags];
+    __shared__ int flags[2];
+    if (threadIdx.x < kMaxDiags) tab[threadIdx.x] = 0u;
+    if (threadIdx.x < 2) flags[threadIdx.x] = 0;
+    __syncthreads();
+    auto enter = [](unsigned* t, unsigned key) {
+        for (int k = 0; k < kMaxDiags; ++k) {
+            const unsigned have = __hip_atomic_load(t + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (have == key) return true;
+            if (have == 0u) {
+                const unsigned was = atomicCAS(t + k, 0u, key);
+                if (was == 0u || was == key) return true;
+            }
+        }
+        return false;
+    };
     const int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
+    bool bad = false, many = false;
     if (i <= n) {
         const int32_t r = rowptr[i];
-        if (r < 0 || r > nnz || (i == 0 && r != 0) || (i == n && r != nnz)) atomicOr(bad, 1);
-        if (i < n && rowptr[i + 1] < r) atomicOr(bad, 1);
+        bad = r < 0 || r > nnz || (i == 0 && r != 0) || (i == n && r != nnz);
+        if (i < n) {
+            const int32_t r1 = rowptr[i + 1];
+            bad = bad || r1 < r || r1 > nnz;
+            if (!bad) {
+                int64_t prev = -1;
+                unsigned last = 0u;
+                for (int32_t e = r; e < r1; ++e) {
+                    const int32_t c = colind[e];
+                    bad = bad || c < 0 || c >= n;
+                    many = many || c <= prev;
+                    prev = c;
+                    // offset + 2^31 (never 0: offsets are above -2^31)
+                    const unsigned key = (unsigned)((int64_t)c - i + kDiagBias);
+                    if (!bad && !many && key != last) many = !enter(tab, key);
+                    last = key;
+                }
+            }
+        }
     }
-    for (int64_t e = i; e < nnz; e += (int64_t)gridDim.x * NT) {
-        const int32_t c = colind[e];
-        if (c < 0 || c >= n) atomicOr(bad, 1);
+    if (bad) flags[0] = 1;
+    if (many) flags[1] = 1;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        if (flags[0]) atomicOr(words, 1);
+        if (flags[1]) atomicOr(words + 1, 1);
+    }
+    if (threadIdx.x < kMaxDiags && tab[threadIdx.x] != 0u && !flags[1])
+        if (!enter(reinterpret_cast<unsigned*>(words + 2), tab[threadIdx.x])) atomicOr(words + 1, 1);
+}
+
+// d.val[k ld + row] = A(row, row + off[k]) (scaled by dinv[column]), 0 where the row has none;
+// one row per thread, its entries and the diagonals both in ascending column order.
+template <typename TV>
+__global__ void __launch_bounds__(NT) fill_diagonals_kernel(int64_t n, const int32_t* __restrict__ rowptr,
+                                                            const int32_t* __restrict__ colind,
+                                                            const double* __restrict__ val,
+                                                            const double* __restrict__ dinv, const DiaView d) {
+    const int64_t row = (int64_t)blockIdx.x * NT + threadIdx.x;
+    if (row >= n) return;
+    TV* out = static_cast<TV*>(const_cast<void*>(d.val)) + row;
+    int32_t e = rowptr[row];
+    const int32_t e1 = rowptr[row + 1];
+    for (int k = 0; k < d.nd; ++k) {
+        double v = 0.0;
+        if (e < e1) {
+            const int32_t c = colind[e];
+            if (c == row + d.off[k]) {
+                v = dinv ? val[e] * dinv[c] : val[e];
+                ++e;
+            }
+        }
+        out[(int64_t)k * d.ld] = static_cast<TV>(v);
     }
 }
 
@@ -813,25 +975,49 @@ hipError_t spmv_dispatch(int64_t n, int64_t nnz, double avg, const int32_t* rp, 
     return hipGetLastError();
 }
 
+// Rows per thread of the diagonal form: two (16-byte loads) once that still fills the chip; a
+// small matrix takes one, for twice the workgroups.
+constexpr int64_t kDiaTwoRows = 1 << 18;
+
+template <int RPT, typename TV, typename TX, typename TY>
+void dia_launch(int64_t n, const DiaView& d, const TX* x, TY* y, hipStream_t st, const NewtonStep<TX>& ns) {
+    const dim3 g((unsigned)((n + NT * RPT - 1) / (NT * RPT)));
+    if (d.nd == 5)
+        hipLaunchKernelGGL((spmv_dia_kernel<5, RPT, TV, TX, TY>), g, dim3(NT), 0, st, n, d, x, y, ns);
+    else if (d.nd == 7)
+        hipLaunchKernelGGL((spmv_dia_kernel<7, RPT, TV, TX, TY>), g, dim3(NT), 0, st, n, d, x, y, ns);
+    else
+        hipLaunchKernelGGL((spmv_dia_kernel<0, RPT, TV, TX, TY>), g, dim3(NT), 0, st, n, d, x, y, ns);
+}
+
+template <typename TV, typename TX, typename TY>
+hipError_t spmv_any(const CsrView& A, const TX* x, TY* y, int grid_cap, hipStream_t st, const NewtonStep<TX>& ns) {
+    if (A.dia.val) {
+        if (A.n >= kDiaTwoRows)
+            dia_launch<2, TV, TX, TY>(A.n, A.dia, x, y, st, ns);
+        else
+            dia_launch<1, TV, TX, TY>(A.n, A.dia, x, y, st, ns);
+        return hipGetLastError();
+    }
+    const double avg = (double)A.nnz / (double)std::max<int64_t>(1, A.n);
+    return spmv_dispatch<TV, TX, TY>(A.n, A.nnz, avg, A.rowptr, A.colind, static_cast<const TV*>(A.val_op), x, y,
+                                     grid_cap, st, ns);
+}
+
 }  // namespace
 
 hipError_t launch_spmv(const CsrView& A, bool f32, const void* x, void* y, int grid_cap, hipStream_t st,
                        const double* na, const double* nb, const void* z) {
-    const double avg = (double)A.nnz / (double)std::max<int64_t>(1, A.n);
     if (f32)
-        return spmv_dispatch<float, float, float>(A.n, A.nnz, avg, A.rowptr, A.colind, static_cast<const float*>(A.val_op),
-                                                  static_cast<const float*>(x), static_cast<float*>(y), grid_cap, st,
-                                                  NewtonStep<float>{na, nb, static_cast<const float*>(z)});
-    return spmv_dispatch<double, double, double>(A.n, A.nnz, avg, A.rowptr, A.colind, static_cast<const double*>(A.val_op),
-                                                 static_cast<const double*>(x), static_cast<double*>(y), grid_cap, st,
-                                                 NewtonStep<double>{na, nb, static_cast<const double*>(z)});
+        return spmv_any<float, float, float>(A, static_cast<const float*>(x), static_cast<float*>(y), grid_cap, st,
+                                             NewtonStep<float>{na, nb, static_cast<const float*>(z)});
+    return spmv_any<double, double, double>(A, static_cast<const double*>(x), static_cast<double*>(y), grid_cap, st,
+                                            NewtonStep<double>{na, nb, static_cast<const double*>(z)});
 }
 
 hipError_t launch_spmv_panel(const CsrView& A, const double* x, double* y, int grid_cap, hipStream_t st,
                              const double* na, const double* nb, const double* z) {
-    const double avg = (double)A.nnz / (double)std::max<int64_t>(1, A.n);
-    return spmv_dispatch<float, double, double>(A.n, A.nnz, avg, A.rowptr, A.colind, static_cast<const float*>(A.val_op), x,
-                                                y, grid_cap, st, NewtonStep<double>{na, nb, z});
+    return spmv_any<float, double, double>(A, x, y, grid_cap, st, NewtonStep<double>{na, nb, z});
 }
 
 hipError_t launch_widen(int64_t n, const float* x, double* y, int grid_cap, hipStream_t st) {
@@ -881,10 +1067,31 @@ hipError_t launch_update(int64_t n, bool f32, const void* Q, int64_t ldq, int k,
     return hipGetLastError();
 }
 
-hipError_t launch_csr_check(int64_t n, int64_t nnz, const int32_t* rowptr, const int32_t* colind, int* bad,
+hipError_t launch_csr_check(int64_t n, int64_t nnz, const int32_t* rowptr, const int32_t* colind, int* words,
                             hipStream_t st) {
     const unsigned grid = (unsigned)((n + 1 + NT - 1) / NT);
-    hipLaunchKernelGGL(csr_check_kernel, dim3(grid), dim3(NT), 0, st, n, nnz, rowptr, colind, bad);
+    hipLaunchKernelGGL(csr_check_kernel, dim3(grid), dim3(NT), 0, st, n, nnz, rowptr, colind, words);
+    return hipGetLastError();
+}
+
+bool scan_diagonals(const int32_t* words, int64_t n, int64_t nnz, int eb, DiaView& d) {
+    d = DiaView{};
+    if (words[0] || words[1]) return false;
+    for (int k = 0; k < kMaxDiags; ++k)
+        if (words[2 + k] != kNoDiag) d.off[d.nd++] = (int32_t)((int64_t)(uint32_t)words[2 + k] - kDiagBias);
+    std::sort(d.off, d.off + d.nd);
+    d.ld = (n + 63) / 64 * 64;
+    return d.nd > 0 && (double)d.nd * (double)n * eb <= 0.85 * ((double)nnz * (eb + 4) + 4.0 * (double)n);
+}
+
+hipError_t launch_fill_diagonals(int64_t n, const int32_t* rowptr, const int32_t* colind, const double* val,
+                                 const double* dinv, bool f32, const DiaView& d, hipStream_t st) {
+    if (!d.val || d.nd < 1 || d.nd > kMaxDiags || d.ld < n) return hipErrorInvalidValue;
+    const dim3 g((unsigned)((n + NT - 1) / NT));
+    if (f32)
+        hipLaunchKernelGGL((fill_diagonals_kernel<float>), g, dim3(NT), 0, st, n, rowptr, colind, val, dinv, d);
+    else
+        hipLaunchKernelGGL((fill_diagonals_kernel<double>), g, dim3(NT), 0, st, n, rowptr, colind, val, dinv, d);
     return hipGetLastError();
 }
 
@@ -929,7 +1136,8 @@ hipError_t launch_gm_small(const GmSmallArgs& a, hipStream_t st, const BatchRelo
     return hipGetLastError();
 }
 
-int spmv_flat_unit(bool f32, double avg_nnz) {
+int spmv_flat_unit(bool f32, double avg_nnz, bool dia) {
+    if (dia) return 2 * NT;
     const SpmvKind k = f32 ? spmv_kind<float>(avg_nnz) : spmv_kind<double>(avg_nnz);
     return spmv_rows_per_block(k);
 }
@@ -947,12 +1155,24 @@ void spmv_flat_launch(SpmvKind k, const TX* x, TY* y, hipStream_t st, const Batc
     }
 }
 
-hipError_t launch_spmv_batched(bool f32, double avg_nnz, int64_t max_n, const void* x, void* y, int grid_cap,
+hipError_t launch_spmv_batched(bool f32, double avg_nnz, bool dia, int64_t max_n, const void* x, void* y, int grid_cap,
                                hipStream_t st, const BatchReloc& br) {
     if (br.nact < 1) return hipErrorInvalidValue;
+    if (dia) {
+        if (!br.blk0 || br.nblk < br.nact || br.chunk < 1 || br.chunk % spmv_flat_unit(f32, avg_nnz, true) != 0)
+            return hipErrorInvalidValue;
+        const dim3 g(br.nblk);
+        if (f32)
+            hipLaunchKernelGGL((spmv_dia_kernel_flat<0, 2, float, float, float>), g, dim3(NT), 0, st,
+                               static_cast<const float*>(x), static_cast<float*>(y), br);
+        else
+            hipLaunchKernelGGL((spmv_dia_kernel_flat<0, 2, double, double, double>), g, dim3(NT), 0, st,
+                               static_cast<const double*>(x), static_cast<double*>(y), br);
+        return hipGetLastError();
+    }
     const SpmvKind k = f32 ? spmv_kind<float>(avg_nnz) : spmv_kind<double>(avg_nnz);
     if (br.blk0) {
-        if (br.nblk < br.nact || br.chunk < 1 || br.chunk % spmv_flat_unit(f32, avg_nnz) != 0)
+        if (br.nblk < br.nact || br.chunk < 1 || br.chunk % spmv_flat_unit(f32, avg_nnz, false) != 0)
             return hipErrorInvalidValue;
         if (f32)
             spmv_flat_launch<float, float, float>(k, static_cast<const float*>(x), static_cast<float*>(y), st, br);
