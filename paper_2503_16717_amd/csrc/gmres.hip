@@ -636,7 +636,7 @@ sko_status gmres_impl(sko_ctx c, const sko_csr* A, const double* b, double* x, c
     if (g.jacobi) SKO_HIP(launch_jacobi_setup(A->n, A->nnz, A->rowptr, A->colind, A->val, g.dinv, g.status, g.st));
     if (dia.nd) {
         dia.val = ar.at<void>(o_val);
-        SKO_HIP(launch_fill_diagonals(A->n, A->rowptr, A->colind, A->val, g.dinv, g.f32, dia, g.st));
+        SKO_HIP(launch_fill_diagonals(A->n, A->nnz, A->rowptr, A->colind, A->val, g.dinv, g.f32, dia, g.st));
         g.A.dia = dia;
     } else if (g.jacobi || g.f32) {
         void* vo = ar.at<void>(o_val);
@@ -866,19 +866,30 @@ sko_status gmres_batched_impl(sko_ctx c, int32_t nsys, const sko_csr* A, const d
     EventPair ev_total;
     SKO_HIP(ev_total.create());
     SKO_HIP(hipEventRecord(ev_total.a, g.st));
-    // ---- per system: CSR check and diagonal scan, their words at the start of the workspace
-    sko_status s = ensure_workspace(c, sizeof(int32_t) * 32 * (size_t)nsys);
+    // ---- CSR check and diagonal scan of every system in one launch; its table and words stand at
+    // the start of the workspace until they are read
+    const size_t words_bytes = sizeof(int32_t) * 32 * (size_t)nsys;
+    sko_status s = ensure_workspace(c, words_bytes + sizeof(BatchSys) * nsys);
     if (s) return s;
-    if ((s = ensure_pinned(c, sizeof(int32_t) * 32 * (size_t)nsys))) return s;
+    if ((s = ensure_pinned(c, words_bytes + sizeof(BatchSys) * nsys))) return s;
     std::vector<DiaView> dia(nsys);
     g.dia_batch = true;
     {
         int* words = static_cast<int*>(c->ws);
+        BatchSys* tbl = reinterpret_cast<BatchSys*>(static_cast<char*>(c->ws) + words_bytes);
         int32_t* host = static_cast<int32_t*>(c->pinned);
-        SKO_HIP(launch_zero(words, sizeof(int32_t) * 32 * (size_t)nsys, g.st));
-        for (int32_t i = 0; i < nsys; ++i)
-            SKO_HIP(launch_csr_check(A[i].n, A[i].nnz, A[i].rowptr, A[i].colind, words + 32 * i, g.st));
-        SKO_HIP(hipMemcpyAsync(host, words, sizeof(int32_t) * 32 * (size_t)nsys, hipMemcpyDeviceToHost, g.st));
+        BatchSys* tbl_host = reinterpret_cast<BatchSys*>(static_cast<char*>(c->pinned) + words_bytes);
+        for (int32_t i = 0; i < nsys; ++i) {
+            tbl_host[i] = BatchSys{};
+            tbl_host[i].n = A[i].n;
+            tbl_host[i].nnz = A[i].nnz;
+            tbl_host[i].rowptr = A[i].rowptr;
+            tbl_host[i].colind = A[i].colind;
+        }
+        SKO_HIP(hipMemcpyAsync(tbl, tbl_host, sizeof(BatchSys) * nsys, hipMemcpyHostToDevice, g.st));
+        SKO_HIP(launch_zero(words, words_bytes, g.st));
+        SKO_HIP(launch_csr_check_batched(nsys, max_n, tbl, words, g.st));
+        SKO_HIP(hipMemcpyAsync(host, words, words_bytes, hipMemcpyDeviceToHost, g.st));
         SKO_HIP(hipStreamSynchronize(g.st));
         for (int32_t i = 0; i < nsys; ++i) {
             if (host[32 * i]) {
@@ -970,12 +981,12 @@ sko_status gmres_batched_impl(sko_ctx c, int32_t nsys, const sko_csr* A, const d
         return SKO_OK;
     };
 
-    // ---- per system: operator set-up, ||b|| (single-system launches)
+    // ---- operator set-up (one launch for every system where the operators are diagonals)
     for (int32_t i = 0; i < nsys; ++i) {
         const int64_t ldi = ((A[i].n + 63) / 64) * 64;
         BatchSys& d = tbl_h[i];
         d = BatchSys{};
-        d.n = A[i].n;
+        d.n = S[i].finished ? 0 : A[i].n;
         d.ld = ldi;
         d.nnz = A[i].nnz;
         d.Q = ar.at<char>(o_Q[i]);
@@ -988,23 +999,25 @@ sko_status gmres_batched_impl(sko_ctx c, int32_t nsys, const sko_csr* A, const d
         d.dinv = g.jacobi ? ar.at<double>(o_dinv[i]) : nullptr;
         d.seed = o->sketch.seed + (uint64_t)i;
         d.kupd = 0;
-        if (S[i].finished) continue;
-        int* st_i = reinterpret_cast<int*>(small_of(i) + st_off);
-        if (g.jacobi)
-            SKO_HIP(launch_jacobi_setup(A[i].n, A[i].nnz, A[i].rowptr, A[i].colind, A[i].val,
-                                        const_cast<double*>(d.dinv), st_i, g.st));
         if (g.dia_batch) {
             dia[i].val = ar.at<void>(o_val[i]);
-            SKO_HIP(launch_fill_diagonals(A[i].n, A[i].rowptr, A[i].colind, A[i].val, d.dinv, g.f32, dia[i], g.st));
             d.dia = dia[i].val;
             d.ldd = dia[i].ld;
             d.nd = dia[i].nd;
             std::copy(dia[i].off, dia[i].off + kMaxDiags, d.off);
         } else if (own_vals) {
-            void* vo = ar.at<void>(o_val[i]);
-            SKO_HIP(launch_scale_values(A[i].nnz, A[i].colind, A[i].val, d.dinv, g.f32, vo, g.st));
-            d.val_op = vo;
+            d.val_op = ar.at<void>(o_val[i]);
         }
+    }
+    SKO_HIP(hipMemcpyAsync(tbl_d, tbl_h, sizeof(BatchSys) * nsys, hipMemcpyHostToDevice, g.st));
+    if (g.jacobi) SKO_HIP(launch_jacobi_setup_batched(nsys, max_n, tbl_d, small0 + st_off, (int64_t)L.bytes, g.st));
+    if (g.dia_batch) SKO_HIP(launch_fill_diagonals_batched(nsys, max_n, tbl_d, g.f32, g.st));
+    // ---- ||b||, and CSR operator values, system by system
+    for (int32_t i = 0; i < nsys; ++i) {
+        if (S[i].finished) continue;
+        if (own_vals && !g.dia_batch)
+            SKO_HIP(launch_scale_values(A[i].nnz, A[i].colind, A[i].val, tbl_h[i].dinv, g.f32,
+                                        const_cast<void*>(tbl_h[i].val_op), g.st));
         GmCtx gi = g;
         gi.n = A[i].n;
         carve_small(gi, small_of(i), L, kr, k);
@@ -1030,8 +1043,6 @@ sko_status gmres_batched_impl(sko_ctx c, int32_t nsys, const sko_csr* A, const d
             S[i].result = S[i].bnorm == 0.0 ? SKO_OK : SKO_EINVAL;
         }
     }
-    SKO_HIP(hipMemcpyAsync(tbl_d, tbl_h, sizeof(BatchSys) * nsys, hipMemcpyHostToDevice, g.st));
-    SKO_HIP(hipStreamSynchronize(g.st));
 
     BatchReloc br{};
     br.sys = tbl_d;

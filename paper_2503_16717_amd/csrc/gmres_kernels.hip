@@ -423,15 +423,34 @@ __global__ void __launch_bounds__(NT) spmv_dia_kernel_flat(const TX* x0, TY* y0,
 constexpr int32_t kNoDiag = 0;  // words hold offset + kDiagBias, so 0 means unused
 constexpr int64_t kDiagBias = (int64_t)1 << 31;
 
-// CSR structure check and diagonal scan, one row per thread (a row is walked only where its
-// pointers are in range, so nothing outside colind is read).  The diagonals seen by a
-// workgroup collect in LDS first; each is then entered once in the global table.
-__global__ void __launch_bounds__(NT) csr_check_kernel(int64_t n, int64_t nnz, const int32_t* __restrict__ rowptr,
-                                                       const int32_t* __restrict__ colind, int* words) {
+// Entries [e0, e1) of the workgroup's rows copied into LDS with coalesced loads; false (nothing
+// copied) if they are out of range or too many.
+template <typename T>
+__device__ __forceinline__ bool stage_entries(const T* __restrict__ src, int64_t e0, int64_t e1, int64_t nnz, T* lds) {
+    if (e0 < 0 || e1 < e0 || e1 > nnz || e1 - e0 > STAGE) return false;
+    for (int i = threadIdx.x; i < (int)(e1 - e0); i += NT) lds[i] = __builtin_nontemporal_load(src + e0 + i);
+    return true;
+}
+
+// CSR structure check and diagonal scan of the NT rows of block `blk`, one row per thread (a row
+// is walked only where its pointers are in range, so nothing outside colind is read).  The
+// diagonals seen by a workgroup collect in LDS first; each is then entered once in the global
+// table.
+__device__ __forceinline__ void csr_check_body(int64_t n, int64_t nnz, const int32_t* __restrict__ rowptr,
+                                               const int32_t* __restrict__ colind, int* words, int64_t blk) {
     __shared__ unsigned tab[kMaxDiags];
     __shared__ int flags[2];
+    __shared__ int32_t sc[STAGE];
     if (threadIdx.x < kMaxDiags) tab[threadIdx.x] = 0u;
     if (threadIdx.x < 2) flags[threadIdx.x] = 0;
+    const int64_t base = blk * NT, rend = base + NT < n ? base + NT : n;
+    int64_t o = 0;
+    bool staged = false;
+    if (base < n) {
+        o = rowptr[base];
+        staged = stage_entries(colind, o, rowptr[rend], nnz, sc);
+    }
+    const int64_t o1 = staged ? (int64_t)rowptr[rend] : 0;
     __syncthreads();
     auto enter = [](unsigned* t, unsigned key) {
         for (int k = 0; k < kMaxDiags; ++k) {
@@ -444,7 +463,7 @@ __global__ void __launch_bounds__(NT) csr_check_kernel(int64_t n, int64_t nnz, c
         }
         return false;
     };
-    const int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
+    const int64_t i = base + threadIdx.x;
     bool bad = false, many = false;
     if (i <= n) {
         const int32_t r = rowptr[i];
@@ -453,17 +472,16 @@ __global__ void __launch_bounds__(NT) csr_check_kernel(int64_t n, int64_t nnz, c
             const int32_t r1 = rowptr[i + 1];
             bad = bad || r1 < r || r1 > nnz;
             if (!bad) {
+                // (unordered row pointers may leave the staged range: those rows read colind)
+                const bool in = staged && r >= o && r1 <= o1;
                 int64_t prev = -1;
-                unsigned last = 0u;
                 for (int32_t e = r; e < r1; ++e) {
-                    const int32_t c = colind[e];
+                    const int32_t c = in ? sc[e - o] : colind[e];
                     bad = bad || c < 0 || c >= n;
                     many = many || c <= prev;
                     prev = c;
                     // offset + 2^31 (never 0: offsets are above -2^31)
-                    const unsigned key = (unsigned)((int64_t)c - i + kDiagBias);
-                    if (!bad && !many && key != last) many = !enter(tab, key);
-                    last = key;
+                    if (!bad && !many) many = !enter(tab, (unsigned)((int64_t)c - i + kDiagBias));
                 }
             }
         }
@@ -479,40 +497,90 @@ __global__ void __launch_bounds__(NT) csr_check_kernel(int64_t n, int64_t nnz, c
         if (!enter(reinterpret_cast<unsigned*>(words + 2), tab[threadIdx.x])) atomicOr(words + 1, 1);
 }
 
-// d.val[k ld + row] = A(row, row + off[k]) (scaled by dinv[column]), 0 where the row has none;
+__global__ void __launch_bounds__(NT) csr_check_kernel(int64_t n, int64_t nnz, const int32_t* __restrict__ rowptr,
+                                                       const int32_t* __restrict__ colind, int* words) {
+    csr_check_body(n, nnz, rowptr, colind, words, blockIdx.x);
+}
+
+// System blockIdx.y of the table (n, nnz, rowptr, colind); its words 32 ints apart.
+__global__ void __launch_bounds__(NT) csr_check_kernel_batched(const BatchSys* sys, int* words) {
+    const BatchSys& d = sys[blockIdx.y];
+    if ((int64_t)blockIdx.x * NT > d.n) return;
+    csr_check_body(d.n, d.nnz, d.rowptr, d.colind, words + 32 * blockIdx.y, blockIdx.x);
+}
+
+// out[k ld + row] = A(row, row + off[k]) (scaled by dinv[column]), 0 where the row has none;
 // one row per thread, its entries and the diagonals both in ascending column order.
 template <typename TV>
-__global__ void __launch_bounds__(NT) fill_diagonals_kernel(int64_t n, const int32_t* __restrict__ rowptr,
-                                                            const int32_t* __restrict__ colind,
-                                                            const double* __restrict__ val,
-                                                            const double* __restrict__ dinv, const DiaView d) {
-    const int64_t row = (int64_t)blockIdx.x * NT + threadIdx.x;
+__device__ __forceinline__ void fill_diagonals_body(int64_t n, int64_t nnz, const int32_t* __restrict__ rowptr,
+                                                    const int32_t* __restrict__ colind,
+                                                    const double* __restrict__ val, const double* __restrict__ dinv,
+                                                    TV* __restrict__ out, int64_t ld, int nd, const int32_t* off,
+                                                    int64_t blk) {
+    __shared__ int32_t sc[STAGE];
+    __shared__ double sv[STAGE];
+    const int64_t base = blk * NT, rend = base + NT < n ? base + NT : n;
+    const int64_t o = rowptr[base];
+    bool staged = stage_entries(colind, o, rowptr[rend], nnz, sc);
+    if (staged) staged = stage_entries(val, o, rowptr[rend], nnz, sv);
+    __syncthreads();
+    const int64_t row = base + threadIdx.x;
     if (row >= n) return;
-    TV* out = static_cast<TV*>(const_cast<void*>(d.val)) + row;
     int32_t e = rowptr[row];
     const int32_t e1 = rowptr[row + 1];
-    for (int k = 0; k < d.nd; ++k) {
+    for (int k = 0; k < nd; ++k) {
         double v = 0.0;
         if (e < e1) {
-            const int32_t c = colind[e];
-            if (c == row + d.off[k]) {
-                v = dinv ? val[e] * dinv[c] : val[e];
+            const int32_t c = staged ? sc[e - o] : colind[e];
+            if (c == row + off[k]) {
+                v = staged ? sv[e - o] : val[e];
+                if (dinv) v *= dinv[c];
                 ++e;
             }
         }
-        out[(int64_t)k * d.ld] = static_cast<TV>(v);
+        __builtin_nontemporal_store(static_cast<TV>(v), out + row + (int64_t)k * ld);
     }
 }
 
-__global__ void diag_inv_kernel(int64_t n, const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colind,
-                                const double* __restrict__ val, double* __restrict__ dinv, int* status) {
-    const int64_t row = (int64_t)blockIdx.x * NT + threadIdx.x;
-    if (row >= n) return;
+template <typename TV>
+__global__ void __launch_bounds__(NT) fill_diagonals_kernel(int64_t n, int64_t nnz, const int32_t* rowptr,
+                                                            const int32_t* colind, const double* val,
+                                                            const double* dinv, const DiaView d) {
+    fill_diagonals_body<TV>(n, nnz, rowptr, colind, val, dinv, static_cast<TV*>(const_cast<void*>(d.val)), d.ld, d.nd,
+                            d.off, blockIdx.x);
+}
+
+template <typename TV>
+__global__ void __launch_bounds__(NT) fill_diagonals_kernel_batched(const BatchSys* sys) {
+    const BatchSys& d = sys[blockIdx.y];
+    if ((int64_t)blockIdx.x * NT >= d.n) return;
+    fill_diagonals_body<TV>(d.n, d.nnz, d.rowptr, d.colind, d.val, d.dinv, static_cast<TV*>(const_cast<void*>(d.dia)),
+                            d.ldd, d.nd, d.off, blockIdx.x);
+}
+
+__device__ __forceinline__ void diag_inv_row(int64_t row, const int32_t* __restrict__ rowptr,
+                                             const int32_t* __restrict__ colind, const double* __restrict__ val,
+                                             double* __restrict__ dinv, int* status) {
     double d = 0.0;
     for (int32_t e = rowptr[row]; e < rowptr[row + 1]; ++e)
         if (colind[e] == row) d = val[e];
     if (d == 0.0) atomicCAS(status, 0, -1);  // zero diagonal: Jacobi undefined
     dinv[row] = 1.0 / d;
+}
+
+__global__ void diag_inv_kernel(int64_t n, const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colind,
+                                const double* __restrict__ val, double* __restrict__ dinv, int* status) {
+    const int64_t row = (int64_t)blockIdx.x * NT + threadIdx.x;
+    if (row < n) diag_inv_row(row, rowptr, colind, val, dinv, status);
+}
+
+// status words `pitch` bytes apart
+__global__ void diag_inv_kernel_batched(const BatchSys* sys, char* status0, int64_t pitch) {
+    const BatchSys& d = sys[blockIdx.y];
+    const int64_t row = (int64_t)blockIdx.x * NT + threadIdx.x;
+    if (row < d.n)
+        diag_inv_row(row, d.rowptr, d.colind, d.val, const_cast<double*>(d.dinv),
+                     reinterpret_cast<int*>(status0 + blockIdx.y * pitch));
 }
 
 template <typename TV>
@@ -1084,14 +1152,36 @@ bool scan_diagonals(const int32_t* words, int64_t n, int64_t nnz, int eb, DiaVie
     return d.nd > 0 && (double)d.nd * (double)n * eb <= 0.85 * ((double)nnz * (eb + 4) + 4.0 * (double)n);
 }
 
-hipError_t launch_fill_diagonals(int64_t n, const int32_t* rowptr, const int32_t* colind, const double* val,
+hipError_t launch_fill_diagonals(int64_t n, int64_t nnz, const int32_t* rowptr, const int32_t* colind, const double* val,
                                  const double* dinv, bool f32, const DiaView& d, hipStream_t st) {
     if (!d.val || d.nd < 1 || d.nd > kMaxDiags || d.ld < n) return hipErrorInvalidValue;
     const dim3 g((unsigned)((n + NT - 1) / NT));
     if (f32)
-        hipLaunchKernelGGL((fill_diagonals_kernel<float>), g, dim3(NT), 0, st, n, rowptr, colind, val, dinv, d);
+        hipLaunchKernelGGL((fill_diagonals_kernel<float>), g, dim3(NT), 0, st, n, nnz, rowptr, colind, val, dinv, d);
     else
-        hipLaunchKernelGGL((fill_diagonals_kernel<double>), g, dim3(NT), 0, st, n, rowptr, colind, val, dinv, d);
+        hipLaunchKernelGGL((fill_diagonals_kernel<double>), g, dim3(NT), 0, st, n, nnz, rowptr, colind, val, dinv, d);
+    return hipGetLastError();
+}
+
+hipError_t launch_csr_check_batched(int nsys, int64_t max_n, const BatchSys* sys, int* words, hipStream_t st) {
+    const dim3 g((unsigned)((max_n + 1 + NT - 1) / NT), (unsigned)nsys);
+    hipLaunchKernelGGL(csr_check_kernel_batched, g, dim3(NT), 0, st, sys, words);
+    return hipGetLastError();
+}
+
+hipError_t launch_jacobi_setup_batched(int nsys, int64_t max_n, const BatchSys* sys, void* status0, int64_t pitch,
+                                       hipStream_t st) {
+    const dim3 g((unsigned)((max_n + NT - 1) / NT), (unsigned)nsys);
+    hipLaunchKernelGGL(diag_inv_kernel_batched, g, dim3(NT), 0, st, sys, static_cast<char*>(status0), pitch);
+    return hipGetLastError();
+}
+
+hipError_t launch_fill_diagonals_batched(int nsys, int64_t max_n, const BatchSys* sys, bool f32, hipStream_t st) {
+    const dim3 g((unsigned)((max_n + NT - 1) / NT), (unsigned)nsys);
+    if (f32)
+        hipLaunchKernelGGL((fill_diagonals_kernel_batched<float>), g, dim3(NT), 0, st, sys);
+    else
+        hipLaunchKernelGGL((fill_diagonals_kernel_batched<double>), g, dim3(NT), 0, st, sys);
     return hipGetLastError();
 }
 
