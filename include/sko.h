@@ -217,8 +217,8 @@ sko_status sko_orth_block(sko_ctx ctx, int64_t n, int32_t p, int32_t w,
  * outputs are the same.  The call allocates nothing: the reductions' partial sums, the
  * small factors and the status words live in a fixed device scratch of
  * SKO_NOALLOC_SCRATCH_BYTES (32 MiB) that the library holds on every device it runs on
- * until the process ends (its device address is looked up by sko_create); R is copied
- * straight into the caller's host arrays, and the context's kernel profiler does not see
+ * until the process ends (its device address is looked up by sko_create); R comes through
+ * pinned memory that sko_create allocated, and the context's kernel profiler does not see
  * these launches.  Needed scratch: 8 * G * ceil(max(p, k, w) * w / 32) * 32 bytes of
  * partial sums, G = min(ceil(n / 256), 8 * compute units), plus about 8 * (2 p w + k w +
  * (p + w)^2 + 5 w^2) bytes; a request above 32 MiB returns SKO_ESCRATCH (2^24 rows with

@@ -31,7 +31,8 @@ sko_status sko_create(int device, void* hip_stream, sko_ctx* out) {
         return SKO_ENOMEM;
     }
     // device address of this device's fixed scratch (sko_orth_block_noalloc), once per device
-    const sko_status ns = sko::noalloc_init(device);
+    sko_status ns = sko::noalloc_init(device);
+    if (ns == SKO_OK) ns = sko::alloc_results(c);
     if (ns != SKO_OK) {
         (void)hipHostFree(c->status_host);
         delete c;
@@ -47,6 +48,7 @@ sko_status sko_destroy(sko_ctx c) {
     (void)hipStreamSynchronize(c->stream);
     if (c->ws) (void)hipFree(c->ws);
     if (c->status_host) (void)hipHostFree(c->status_host);
+    if (c->res_host) (void)hipHostFree(c->res_host);
     if (c->pinned) (void)hipHostFree(c->pinned);
     if (c->zc_host) (void)hipHostFree(c->zc_host);
     if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);

@@ -182,6 +182,11 @@ struct sko_ctx_s {
     // copy launch follows each block.  zc_dev: the device's address of the same words.
     double* zc_host = nullptr;
     double* zc_dev = nullptr;
+    // mapped, coherent pinned memory (from sko_create) into which one kernel writes the small
+    // results and the status word of a call: a copy command per result costs more than the
+    // launch, several times more into pageable memory.  res_dev: its device address.
+    double* res_host = nullptr;
+    double* res_dev = nullptr;
     sko::Profiler prof;
     // sko_autotune_orth: workgroups per CU per (pass kernel, log2 of its strip count)
     std::map<std::pair<const void*, int>, int> grid_wpc;
@@ -263,6 +268,22 @@ inline sko_status ensure_zerocopy(sko_ctx c) {
     }
     c->zc_host = static_cast<double*>(h);
     c->zc_dev = static_cast<double*>(d);
+    return SKO_OK;
+}
+
+constexpr int kResultDoubles = 8192;  // capacity of res_host: results, then the status word
+
+inline sko_status alloc_results(sko_ctx c) {
+    void* h = nullptr;
+    if (hipHostMalloc(&h, sizeof(double) * kResultDoubles, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess)
+        return SKO_ENOMEM;
+    void* d = nullptr;
+    if (hipHostGetDevicePointer(&d, h, 0) != hipSuccess) {
+        (void)hipHostFree(h);
+        return SKO_EDEVICE;
+    }
+    c->res_host = static_cast<double*>(h);
+    c->res_dev = static_cast<double*>(d);
     return SKO_OK;
 }
 

@@ -493,8 +493,17 @@ __device__ __forceinline__ void csr_check_body(int64_t n, int64_t nnz, const int
         if (flags[0]) atomicOr(words, 1);
         if (flags[1]) atomicOr(words + 1, 1);
     }
-    if (threadIdx.x < kMaxDiags && tab[threadIdx.x] != 0u && !flags[1])
-        if (!enter(reinterpret_cast<unsigned*>(words + 2), tab[threadIdx.x])) atomicOr(words + 1, 1);
+    if (threadIdx.x < kMaxDiags && tab[threadIdx.x] != 0u && !flags[1]) {
+        // an ordinary (cached, perhaps stale) look first: nearly every workgroup finds its
+        // diagonals there, and device-scope accesses of all of them to one line would take
+        // longer than the scan
+        const unsigned key = tab[threadIdx.x];
+        bool known = false;
+        for (int k = 0; k < kMaxDiags; ++k)
+            known = known || __hip_atomic_load(reinterpret_cast<unsigned*>(words + 2) + k, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_WORKGROUP) == key;
+        if (!known && !enter(reinterpret_cast<unsigned*>(words + 2), key)) atomicOr(words + 1, 1);
+    }
 }
 
 __global__ void __launch_bounds__(NT) csr_check_kernel(int64_t n, int64_t nnz, const int32_t* __restrict__ rowptr,

@@ -667,6 +667,34 @@ sko_status finish(sko_ctx c, int* status_dev, int32_t* breakdown_col) {
     return col ? SKO_EBREAKDOWN : SKO_OK;
 }
 
+// `count` doubles at `src` and the status word, written to the host by one kernel; returns once
+// they are there (in c->res_host).  For results that fit (results_fit).
+bool results_fit(int64_t count) { return count >= 1 && count < kResultDoubles; }
+
+sko_status finish_results(sko_ctx c, const double* src, int count, const int* status_dev, int32_t* breakdown_col) {
+    SKO_HIP(launch_publish(src, count, status_dev, c->res_dev, c->stream));
+    SKO_HIP(hipStreamSynchronize(c->stream));
+    c->prof.flush();
+    const int col = *reinterpret_cast<const volatile int*>(c->res_host + count);
+    if (breakdown_col) *breakdown_col = col;
+    return col ? SKO_EBREAKDOWN : SKO_OK;
+}
+
+// R (rows x cols of the device matrix src, contiguous) and the status word: through the mapped
+// results, or for a larger R through the pinned staging.  *host: where R stands then.
+sko_status finish_matrix(sko_ctx c, const double* src, int64_t count, const int* status_dev, int32_t* breakdown_col,
+                         const double** host) {
+    if (results_fit(count)) {
+        *host = c->res_host;
+        return finish_results(c, src, (int)count, status_dev, breakdown_col);
+    }
+    sko_status s = ensure_pinned(c, sizeof(double) * (size_t)count);
+    if (s) return s;
+    SKO_HIP(hipMemcpyAsync(c->pinned, src, sizeof(double) * (size_t)count, hipMemcpyDeviceToHost, c->stream));
+    *host = static_cast<const double*>(c->pinned);
+    return finish(c, const_cast<int*>(status_dev), breakdown_col);
+}
+
 }  // namespace
 
 sko_status two_stage_blocks(sko_ctx c, int64_t n, int32_t nb, int32_t w, const void* V, int64_t ldv,
@@ -722,15 +750,10 @@ sko_status orth_blocks_impl(sko_ctx c, int64_t n, int32_t nb, int32_t w, const v
         if (s == SKO_EBREAKDOWN) return finish(c, e.status, breakdown_col);
         if (s) return s;
     }
-    double* Rh = nullptr;
-    if (R) {
-        if ((s = ensure_pinned(c, sizeof(double) * (size_t)N * N))) return s;
-        Rh = static_cast<double*>(c->pinned);
-        SKO_HIP(hipMemcpyAsync(Rh, Rfull, sizeof(double) * (size_t)N * N, hipMemcpyDeviceToHost, c->stream));
-    }
-    if ((s = finish(c, e.status, breakdown_col)) && s != SKO_EBREAKDOWN) return s;
-    if (R)
-        for (int jc = 0; jc < N; ++jc) std::memcpy(R + (int64_t)jc * ldr, Rh + (int64_t)jc * N, sizeof(double) * N);
+    if (!R) return finish(c, e.status, breakdown_col);
+    const double* Rh = nullptr;
+    if ((s = finish_matrix(c, Rfull, (int64_t)N * N, e.status, breakdown_col, &Rh)) && s != SKO_EBREAKDOWN) return s;
+    for (int jc = 0; jc < N; ++jc) std::memcpy(R + (int64_t)jc * ldr, Rh + (int64_t)jc * N, sizeof(double) * N);
     return s;
 }
 
@@ -789,10 +812,10 @@ sko_status orth_block_impl(sko_ctx c, int64_t n, int32_t p, int32_t w, const voi
     s = orth_block_run(c, ar, L, e, n, p, w, Q, ldq, V, ldv, Qo, ldqo, o, &Rcol);
     if (s == SKO_EBREAKDOWN) return finish(c, e.status, breakdown_col);
     if (s) return s;
-    if ((s = ensure_pinned(c, sizeof(double) * (size_t)N * w))) return s;
-    double* Rh = static_cast<double*>(c->pinned);
-    SKO_HIP(hipMemcpyAsync(Rh, Rcol, sizeof(double) * (size_t)N * w, hipMemcpyDeviceToHost, c->stream));
-    if ((s = finish(c, e.status, breakdown_col)) && s != SKO_EBREAKDOWN) return s;
+    // (p + w) w doubles always fit: p w <= kMaxUpdCoef
+    static_assert(kMaxUpdCoef + kMaxPassW * kMaxPassW < kResultDoubles, "a block step's R fits the mapped results");
+    if ((s = finish_results(c, Rcol, N * w, e.status, breakdown_col)) && s != SKO_EBREAKDOWN) return s;
+    const double* Rh = c->res_host;
     for (int jc = 0; jc < w; ++jc) {
         if (Rp && p > 0) std::memcpy(Rp + (int64_t)jc * p, Rh + (int64_t)jc * N, sizeof(double) * p);
         if (Rd) std::memcpy(Rd + (int64_t)jc * w, Rh + (int64_t)jc * N + p, sizeof(double) * w);
@@ -801,8 +824,8 @@ sko_status orth_block_impl(sko_ctx c, int64_t n, int32_t p, int32_t w, const voi
 }
 
 // The same block step on the device's fixed scratch (noalloc.hip) instead of the context's
-// workspace: no device or pinned allocation, no profiler bookkeeping; R goes straight into
-// the caller's host arrays.
+// workspace: no device or pinned allocation, no profiler bookkeeping; R comes through the
+// context's mapped results.
 sko_status orth_block_noalloc_impl(sko_ctx c, int64_t n, int32_t p, int32_t w, const void* Q, int64_t ldq,
                                    const void* V, int64_t ldv, void* Qo, int64_t ldqo, double* Rp, double* Rd,
                                    const sko_orth_opts* o, int32_t* breakdown_col) {
@@ -828,17 +851,14 @@ sko_status orth_block_noalloc_impl(sko_ctx c, int64_t n, int32_t p, int32_t w, c
         return s;
     }
     if (s) return s;
-    if (Rp && p > 0)
-        SKO_HIP(hipMemcpy2DAsync(Rp, sizeof(double) * p, Rcol, sizeof(double) * N, sizeof(double) * p, w,
-                                 hipMemcpyDeviceToHost, c->stream));
-    if (Rd)
-        SKO_HIP(hipMemcpy2DAsync(Rd, sizeof(double) * w, Rcol + p, sizeof(double) * N, sizeof(double) * w, w,
-                                 hipMemcpyDeviceToHost, c->stream));
-    SKO_HIP(hipMemcpyAsync(c->status_host, e.status, sizeof(int), hipMemcpyDeviceToHost, c->stream));
-    SKO_HIP(hipStreamSynchronize(c->stream));
-    const int col = *c->status_host;
-    if (breakdown_col) *breakdown_col = col;
-    return col ? SKO_EBREAKDOWN : SKO_OK;
+    s = finish_results(c, Rcol, N * w, e.status, breakdown_col);
+    if (s && s != SKO_EBREAKDOWN) return s;
+    const double* Rh = c->res_host;
+    for (int jc = 0; jc < w; ++jc) {
+        if (Rp && p > 0) std::memcpy(Rp + (int64_t)jc * p, Rh + (int64_t)jc * N, sizeof(double) * p);
+        if (Rd) std::memcpy(Rd + (int64_t)jc * w, Rh + (int64_t)jc * N + p, sizeof(double) * w);
+    }
+    return s;
 }
 
 // Y = Theta^T X (Section 3), the reduction of the update + sketch pass on its own: the same
@@ -876,10 +896,8 @@ sko_status sketch_apply_impl(sko_ctx c, int64_t n, int32_t w, const void* X, int
     sketch_small(sm, sp);
     if ((s = e.reduction({w, f32, sp.red, false, 0, false}, a, sp.rows, X, ldx, nullptr, 0, sm, sp.scale))) return s;
     const double* Ydev = sp.theta_g ? bb.C1 : bb.Ysk;
-    if ((s = ensure_pinned(c, sizeof(double) * (size_t)k * w))) return s;
-    double* Yh = static_cast<double*>(c->pinned);
-    SKO_HIP(hipMemcpyAsync(Yh, Ydev, sizeof(double) * (size_t)k * w, hipMemcpyDeviceToHost, c->stream));
-    if ((s = finish(c, e.status, nullptr))) return s;
+    const double* Yh = nullptr;
+    if ((s = finish_matrix(c, Ydev, (int64_t)k * w, e.status, nullptr, &Yh))) return s;
     for (int jc = 0; jc < w; ++jc) std::memcpy(Y + (int64_t)jc * ldy, Yh + (int64_t)jc * k, sizeof(double) * k);
     return SKO_OK;
 }
@@ -1196,15 +1214,10 @@ sko_status two_stage_blocks(sko_ctx c, int64_t n, int32_t nb, int32_t w, const v
             }
         }
     }
-    double* Rhost = nullptr;
-    if (R) {
-        if ((s = ensure_pinned(c, sizeof(double) * (size_t)N * N))) return s;
-        Rhost = static_cast<double*>(c->pinned);
-        SKO_HIP(hipMemcpyAsync(Rhost, Rfull, sizeof(double) * (size_t)N * N, hipMemcpyDeviceToHost, c->stream));
-    }
-    if ((s = finish(c, e.status, breakdown_col)) && s != SKO_EBREAKDOWN) return s;
-    if (R)
-        for (int jc = 0; jc < N; ++jc)
+    if (!R) return finish(c, e.status, breakdown_col);
+    const double* Rhost = nullptr;
+    if ((s = finish_matrix(c, Rfull, (int64_t)N * N, e.status, breakdown_col, &Rhost)) && s != SKO_EBREAKDOWN) return s;
+    for (int jc = 0; jc < N; ++jc)
             std::memcpy(R + (int64_t)jc * ldr, Rhost + (int64_t)jc * N, sizeof(double) * N);
     return s;
 }

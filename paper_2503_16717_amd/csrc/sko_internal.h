@@ -286,6 +286,10 @@ inline hipError_t launch_zero(void* p, size_t bytes, hipStream_t stream) {
 // Ra Rb into rh (w x w), Rdiag = R Rhat, Rproj = C1 + C2 Rhat into Rout); one workgroup.
 hipError_t launch_assemble(const SmallArgs& s, double* rh, hipStream_t stream);
 
+// dst[0..count) = src[0..count), the int *status at dst[count]; dst is host memory the device
+// reaches (visible to the host once the stream has been synchronised).
+hipError_t launch_publish(const double* src, int count, const int* status, double* dst, hipStream_t stream);
+
 // Small matrix helpers on the device (single workgroup).
 hipError_t launch_small_matmul_upper(int w, const double* A, const double* B, double* C,
                                      hipStream_t stream);

@@ -557,6 +557,7 @@ __device__ __forceinline__ void reduce_body(const ReduceArgs& a) {
     __shared__ int s_last;
     const int tid = threadIdx.x;
     reduce_partials(a);
+    if (a.small.op == OP_STORE && !a.small.theta_g) return;  // no step follows: no ticket either
     if (tid < 64) __threadfence();
     __syncthreads();
     if (tid == 0) {
@@ -618,6 +619,13 @@ __global__ void zero_words_kernel(uint32_t* base, int64_t pitch_words, int64_t w
         const int64_t r = i / width_words;
         base[r * pitch_words + (i - r * width_words)] = 0u;
     }
+}
+
+__global__ void __launch_bounds__(RT) publish_kernel(const double* src, int count, const int* status, double* dst) {
+    const int i = blockIdx.x * RT + threadIdx.x;
+    if (i < count) dst[i] = src[i];
+    if (i == 0) *reinterpret_cast<int*>(dst + count) = *status;
+    __threadfence_system();
 }
 
 __global__ void matmul_upper_kernel(int w, const double* A, const double* B, double* C) {
@@ -697,6 +705,12 @@ hipError_t launch_zero_2d(void* p, size_t pitch, size_t width, size_t rows, hipS
     const int64_t grid = std::min<int64_t>((total + 255) / 256, 1024);
     hipLaunchKernelGGL(zero_words_kernel, dim3((unsigned)grid), dim3(256), 0, stream, static_cast<uint32_t*>(p),
                        (int64_t)(pitch / 4), ww, total);
+    return hipGetLastError();
+}
+
+hipError_t launch_publish(const double* src, int count, const int* status, double* dst, hipStream_t stream) {
+    if (!src || !status || !dst || count < 1) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(publish_kernel, dim3((count + RT - 1) / RT), dim3(RT), 0, stream, src, count, status, dst);
     return hipGetLastError();
 }
 
