@@ -432,58 +432,60 @@ __device__ __forceinline__ bool stage_entries(const T* __restrict__ src, int64_t
     return true;
 }
 
-// CSR structure check and diagonal scan of the NT rows of block `blk`, one row per thread (a row
-// is walked only where its pointers are in range, so nothing outside colind is read).  The
-// diagonals seen by a workgroup collect in LDS first; each is then entered once in the global
-// table.
+// CSR structure check and diagonal scan, one row per thread over the row blocks blk, blk + nblk,
+// ... (a row is walked only where its pointers are in range, so nothing outside colind is read).
+// The diagonals a workgroup sees collect in LDS; at its end each is entered in the global table,
+// with device-scope accesses that all meet on one line: 2048 workgroups do that in a few
+// microseconds, one per 256 rows of the 192^3 matrix took 0.2 ms for it.
 __device__ __forceinline__ void csr_check_body(int64_t n, int64_t nnz, const int32_t* __restrict__ rowptr,
-                                               const int32_t* __restrict__ colind, int* words, int64_t blk) {
+                                               const int32_t* __restrict__ colind, int* words, int64_t blk,
+                                               int64_t nblk) {
     __shared__ unsigned tab[kMaxDiags];
     __shared__ int flags[2];
     __shared__ int32_t sc[STAGE];
     if (threadIdx.x < kMaxDiags) tab[threadIdx.x] = 0u;
     if (threadIdx.x < 2) flags[threadIdx.x] = 0;
-    const int64_t base = blk * NT, rend = base + NT < n ? base + NT : n;
-    int64_t o = 0;
-    bool staged = false;
-    if (base < n) {
-        o = rowptr[base];
-        staged = stage_entries(colind, o, rowptr[rend], nnz, sc);
-    }
-    const int64_t o1 = staged ? (int64_t)rowptr[rend] : 0;
-    __syncthreads();
-    auto enter = [](unsigned* t, unsigned key) {
+    auto enter = [&](unsigned key) {
         for (int k = 0; k < kMaxDiags; ++k) {
-            const unsigned have = __hip_atomic_load(t + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const unsigned have = *const_cast<volatile unsigned*>(&tab[k]);
             if (have == key) return true;
             if (have == 0u) {
-                const unsigned was = atomicCAS(t + k, 0u, key);
+                const unsigned was = atomicCAS(&tab[k], 0u, key);
                 if (was == 0u || was == key) return true;
             }
         }
         return false;
     };
-    const int64_t i = base + threadIdx.x;
     bool bad = false, many = false;
-    if (i <= n) {
+    for (int64_t base = blk * NT; base <= n; base += nblk * NT) {
+        const int64_t rend = base + NT < n ? base + NT : n;
+        int64_t o = 0, o1 = 0;
+        bool staged = false;
+        __syncthreads();  // the block before has been read (and the table cleared)
+        if (base < n) {
+            o = rowptr[base];
+            o1 = rowptr[rend];
+            staged = stage_entries(colind, o, o1, nnz, sc);
+        }
+        __syncthreads();
+        const int64_t i = base + threadIdx.x;
+        if (i > n) continue;
         const int32_t r = rowptr[i];
-        bad = r < 0 || r > nnz || (i == 0 && r != 0) || (i == n && r != nnz);
-        if (i < n) {
-            const int32_t r1 = rowptr[i + 1];
-            bad = bad || r1 < r || r1 > nnz;
-            if (!bad) {
-                // (unordered row pointers may leave the staged range: those rows read colind)
-                const bool in = staged && r >= o && r1 <= o1;
-                int64_t prev = -1;
-                for (int32_t e = r; e < r1; ++e) {
-                    const int32_t c = in ? sc[e - o] : colind[e];
-                    bad = bad || c < 0 || c >= n;
-                    many = many || c <= prev;
-                    prev = c;
-                    // offset + 2^31 (never 0: offsets are above -2^31)
-                    if (!bad && !many) many = !enter(tab, (unsigned)((int64_t)c - i + kDiagBias));
-                }
-            }
+        bad = bad || r < 0 || r > nnz || (i == 0 && r != 0) || (i == n && r != nnz);
+        if (i == n) continue;
+        const int32_t r1 = rowptr[i + 1];
+        bad = bad || r1 < r || r1 > nnz;
+        if (bad) continue;
+        // (unordered row pointers may leave the staged range: those rows read colind)
+        const bool in = staged && r >= o && r1 <= o1;
+        int64_t prev = -1;
+        for (int32_t e = r; e < r1; ++e) {
+            const int32_t c = in ? sc[e - o] : colind[e];
+            bad = bad || c < 0 || c >= n;
+            many = many || c <= prev;
+            prev = c;
+            // offset + 2^31 (never 0: offsets are above -2^31)
+            if (!bad && !many) many = !enter((unsigned)((int64_t)c - i + kDiagBias));
         }
     }
     if (bad) flags[0] = 1;
@@ -494,28 +496,31 @@ __device__ __forceinline__ void csr_check_body(int64_t n, int64_t nnz, const int
         if (flags[1]) atomicOr(words + 1, 1);
     }
     if (threadIdx.x < kMaxDiags && tab[threadIdx.x] != 0u && !flags[1]) {
-        // an ordinary (cached, perhaps stale) look first: nearly every workgroup finds its
-        // diagonals there, and device-scope accesses of all of them to one line would take
-        // longer than the scan
         const unsigned key = tab[threadIdx.x];
-        bool known = false;
-        for (int k = 0; k < kMaxDiags; ++k)
-            known = known || __hip_atomic_load(reinterpret_cast<unsigned*>(words + 2) + k, __ATOMIC_RELAXED,
-                                               __HIP_MEMORY_SCOPE_WORKGROUP) == key;
-        if (!known && !enter(reinterpret_cast<unsigned*>(words + 2), key)) atomicOr(words + 1, 1);
+        unsigned* t = reinterpret_cast<unsigned*>(words + 2);
+        bool done = false;
+        for (int k = 0; k < kMaxDiags && !done; ++k) {
+            const unsigned have = __hip_atomic_load(t + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            done = have == key;
+            if (have == 0u) {
+                const unsigned was = atomicCAS(t + k, 0u, key);
+                done = was == 0u || was == key;
+            }
+        }
+        if (!done) atomicOr(words + 1, 1);
     }
 }
 
 __global__ void __launch_bounds__(NT) csr_check_kernel(int64_t n, int64_t nnz, const int32_t* __restrict__ rowptr,
                                                        const int32_t* __restrict__ colind, int* words) {
-    csr_check_body(n, nnz, rowptr, colind, words, blockIdx.x);
+    csr_check_body(n, nnz, rowptr, colind, words, blockIdx.x, gridDim.x);
 }
 
 // System blockIdx.y of the table (n, nnz, rowptr, colind); its words 32 ints apart.
 __global__ void __launch_bounds__(NT) csr_check_kernel_batched(const BatchSys* sys, int* words) {
     const BatchSys& d = sys[blockIdx.y];
     if ((int64_t)blockIdx.x * NT > d.n) return;
-    csr_check_body(d.n, d.nnz, d.rowptr, d.colind, words + 32 * blockIdx.y, blockIdx.x);
+    csr_check_body(d.n, d.nnz, d.rowptr, d.colind, words + 32 * blockIdx.y, blockIdx.x, gridDim.x);
 }
 
 // out[k ld + row] = A(row, row + off[k]) (scaled by dinv[column]), 0 where the row has none;
@@ -1146,7 +1151,7 @@ hipError_t launch_update(int64_t n, bool f32, const void* Q, int64_t ldq, int k,
 
 hipError_t launch_csr_check(int64_t n, int64_t nnz, const int32_t* rowptr, const int32_t* colind, int* words,
                             hipStream_t st) {
-    const unsigned grid = (unsigned)((n + 1 + NT - 1) / NT);
+    const unsigned grid = (unsigned)std::min<int64_t>((n + 1 + NT - 1) / NT, 2048);
     hipLaunchKernelGGL(csr_check_kernel, dim3(grid), dim3(NT), 0, st, n, nnz, rowptr, colind, words);
     return hipGetLastError();
 }
@@ -1173,7 +1178,7 @@ hipError_t launch_fill_diagonals(int64_t n, int64_t nnz, const int32_t* rowptr, 
 }
 
 hipError_t launch_csr_check_batched(int nsys, int64_t max_n, const BatchSys* sys, int* words, hipStream_t st) {
-    const dim3 g((unsigned)((max_n + 1 + NT - 1) / NT), (unsigned)nsys);
+    const dim3 g((unsigned)std::min<int64_t>((max_n + 1 + NT - 1) / NT, 128), (unsigned)nsys);
     hipLaunchKernelGGL(csr_check_kernel_batched, g, dim3(NT), 0, st, sys, words);
     return hipGetLastError();
 }

@@ -164,6 +164,44 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Columns c0..w-1 of the k x w matrix A (LDS, ld k) minus b v (v^T column), rows j..k-1, by one
+// wave.  Four columns at a time: their shuffle reductions are independent chains of twelve
+// cross-lane moves each, and interleaved they cost little more than one (the 128-row sketch-space
+// step of a 6-column panel spent most of its 50 us in such chains, one after another).
+template <int RPL>
+__device__ __forceinline__ void reflect_columns(double* A, int k, int w, int c0, int j, const double (&vi)[RPL],
+                                                double b) {
+    const int lane = threadIdx.x & 63;
+    for (int cb = c0; cb < w; cb += 4) {
+        double ac[4][RPL], d[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            d[u] = 0.0;
+#pragma unroll
+            for (int r = 0; r < RPL; ++r) {
+                const int i = lane + 64 * r;
+                ac[u][r] = (cb + u < w && i < k) ? A[i + (cb + u) * k] : 0.0;
+                d[u] += vi[r] * ac[u][r];
+            }
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) d[u] += __shfl_xor(d[u], o, 64);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (cb + u < w) {
+#pragma unroll
+                for (int r = 0; r < RPL; ++r) {
+                    const int i = lane + 64 * r;
+                    if (i >= j && i < k) A[i + (cb + u) * k] = ac[u][r] - b * d[u] * vi[r];
+                }
+            }
+        }
+    }
+}
+
 // householder_lds for k <= 64 RPL, run by one wave (rows lane, lane + 64, ... of each
 // lane): the column norms and reflector products are per-lane partial sums then shuffle
 // reductions, and no step waits for the other waves.  The caller synchronises the
@@ -195,22 +233,7 @@ __device__ void householder_wave(double* A, int k, int w, double* E, double* R, 
         }
 #pragma unroll
         for (int r = 0; r < RPL; ++r) vi[r] = (lane + 64 * r == j) ? v0 : aj[r];
-        for (int c = j + 1; c < w; ++c) {
-            double ac[RPL];
-            double dl = 0.0;
-#pragma unroll
-            for (int r = 0; r < RPL; ++r) {
-                const int i = lane + 64 * r;
-                ac[r] = i < k ? A[i + c * k] : 0.0;
-                dl += vi[r] * ac[r];
-            }
-            const double d = wave_sum(dl);
-#pragma unroll
-            for (int r = 0; r < RPL; ++r) {
-                const int i = lane + 64 * r;
-                if (i >= j && i < k) A[i + c * k] = ac[r] - b * d * vi[r];
-            }
-        }
+        reflect_columns<RPL>(A, k, w, j + 1, j, vi, b);
         wave_sync();
         if (lane == 0) {
             A[j + j * k] = alpha;
@@ -244,22 +267,7 @@ __device__ void householder_wave(double* A, int k, int w, double* E, double* R, 
             const int i = lane + 64 * r;
             vi[r] = (i == j) ? v0 : ((i > j && i < k) ? A[i + j * k] : 0.0);
         }
-        for (int c = 0; c < w; ++c) {
-            double ec[RPL];
-            double dl = 0.0;
-#pragma unroll
-            for (int r = 0; r < RPL; ++r) {
-                const int i = lane + 64 * r;
-                ec[r] = i < k ? E[i + c * k] : 0.0;
-                dl += vi[r] * ec[r];
-            }
-            const double d = wave_sum(dl);
-#pragma unroll
-            for (int r = 0; r < RPL; ++r) {
-                const int i = lane + 64 * r;
-                if (i >= j && i < k) E[i + c * k] = ec[r] - b * d * vi[r];
-            }
-        }
+        reflect_columns<RPL>(E, k, w, 0, j, vi, b);
         wave_sync();
     }
     for (int idx = lane; idx < k * w; idx += 64) E[idx] *= sgn[idx / k];
@@ -388,6 +396,7 @@ __device__ void sketch_bcgs2(const SmallArgs& s, double* Z, double* E, double* Y
             for (int idx = tid; idx < na * w; idx += RT) {
                 const int a = idx % na, c = idx / na;
                 double d = 0.0;
+#pragma unroll 8
                 for (int i = 0; i < k; ++i) d += Ys[i + a * ldy] * Z[i + c * k];
                 E[idx] = d;
             }
@@ -395,6 +404,7 @@ __device__ void sketch_bcgs2(const SmallArgs& s, double* Z, double* E, double* Y
             for (int idx = tid; idx < k * w; idx += RT) {
                 const int i = idx % k, c = idx / k;
                 double v = Z[idx];
+#pragma unroll 8
                 for (int a = 0; a < na; ++a) v -= Ys[i + a * ldy] * E[a + c * na];
                 Z[idx] = v;
             }
