@@ -9,8 +9,11 @@ HBM before timing starts; Q is written to a separate buffer so every step sees t
 same input.
 
 value = algorithmic HBM bytes of one step / time per step, in GB/s.  Algorithmic bytes
-count each tall operand once per pass of the pass schedule (block j with p = 6j
-previous columns: (4p + 10w) columns of 8 bytes per row; first block 6w).
+count each tall operand once per pass of the method's block-by-block schedule (block j with
+p = 6j previous columns: (4p + 10w) columns of 8 bytes per row; first block 6w).  The library
+looks one block ahead and moves fewer bytes than that ("executed_schedule_bytes_per_step"), so
+value is a rate of the method's work and no HBM rate; the kernels' own rates are in "roofline"
+and "kernels_top".
 
 Also reported: roofline of the dominant kernel (event-timed launches over the timed
 region), the two-stage variant (s_hat = 30), the CPU oracle timed on a bounded sample of
@@ -46,6 +49,19 @@ def alg_bytes_one_stage(n: int, nb: int, w: int, eb: int = 8) -> float:
     return float(cols) * n * eb
 
 
+def executed_bytes_one_stage(n: int, nb: int, w: int, eb: int = 8) -> float:
+    """The look-ahead schedule of FP64 storage: per block the leading pass (4w; the first block's
+    sketch w), the solved Gram (w), the projection (p + 2w, last block p + w) and the update
+    (p + 4w; first block 3w, last block p + 2w and 2w for its final solve)."""
+    cols = 0
+    for j in range(nb):
+        p, last = j * w, j == nb - 1
+        cols += (4 * w if j else w) + w
+        cols += (p + (w if last else 2 * w)) if j else 0
+        cols += (p + 4 * w) if j else 3 * w
+    return float(cols) * n * eb
+
+
 def alg_bytes_two_stage_method(n: int, nb: int, w: int, ppb: int, eb: int = 8) -> float:
     """Tall traffic the two-stage method needs (each operand once per pass, the big-panel
     close fused like the one-stage passes): per panel the projection and update + sketch
@@ -66,33 +82,24 @@ def alg_bytes_two_stage_method(n: int, nb: int, w: int, ppb: int, eb: int = 8) -
 
 
 def alg_bytes_two_stage(n: int, nb: int, w: int, ppb: int, eb: int = 8) -> float:
-    """Pass schedule the library executes for the two-stage scheme (each tall operand once
-    per pass).  In the big-panel close of panels up to 40 columns, the row solve by R_h also
-    accumulates the reduction that follows it: the Gram matrix of the second CholQR (first
-    big panel) or the projection on up to 48 previous columns; the row update and its Gram
-    matrix stay two sweeps."""
+    """Sweep schedule the library executes for the two-stage scheme (each tall operand once per
+    sweep), big panels of up to 40 columns: projection and update of the whole big panel, the
+    sketches of its panels, Gram of V_hat Rbar^{-1} (rows solved, not stored); behind previous
+    columns the row solve with the projection (up to 48 of them; otherwise apart), the update
+    with its Gram matrix and the last solve; in the first big panel another solved Gram and the
+    solve of all three factors."""
     Wb = ppb * w
-    fuse = Wb <= 40
     cols = 0
     for big in range(nb // ppb):
         p = big * Wb
-        for i in range(ppb):
-            if p > 0:
-                cols += p + w          # C_i = Q_old^T V_i
-                cols += p + 2 * w      # V_hat_i = V_i - Q_old C_i (written) + sketch
-            else:
-                cols += w              # sketch of V_i
-            cols += (i * w + w) + w    # forward substitution, written
-        cols += Wb + 2 * Wb            # Gram of Q_bar, Q_hat = Q_bar R^{-1} (+ fused reduction)
         if p > 0:
-            if fuse and p <= 48:
-                cols += p              # Q_old read by the fused C_2 = Q_old^T Q_hat
-            else:
-                cols += p + Wb         # C_2 = Q_old^T Q_hat
-            cols += (p + 2 * Wb) + Wb  # V_bar = Q_hat - Q_old C_2, Gram of V_bar
-        elif not fuse:
-            cols += Wb                 # Gram of Q_hat
-        cols += 2 * Wb                 # Q_P = V_bar R^{-1}
+            cols += (p + Wb) + (p + 2 * Wb)      # C = Q_old^T V; V_hat = V - Q_old C
+        cols += Wb + Wb                          # sketches; Gram of Q_bar
+        if p > 0:
+            cols += 2 * Wb + (p if p <= 48 else p + Wb)   # Q_hat (+ C_2 = Q_old^T Q_hat)
+            cols += (p + 2 * Wb) + 2 * Wb        # V_bar and its Gram; Q = V_bar R_t^{-1}
+        else:
+            cols += Wb + 2 * Wb                  # Gram of Q_hat; Q from V_hat
     return float(cols) * n * eb
 
 
@@ -597,7 +604,9 @@ def main() -> int:
     extra = {"kernels_top": kernels, "event_ms_per_step": round(event_ms, 3),
              "ms_per_step_with_launch_events": round(ms_profiled, 4),
              "step_ms_median": round(step_ms[len(step_ms) // 2], 4), "step_ms_min": round(step_ms[0], 4),
-             "alg_bytes_per_step": abytes, "autotune_s": None if args.no_autotune else round(t_tune, 3)}
+             "alg_bytes_per_step": abytes,
+             "executed_schedule_bytes_per_step": executed_bytes_one_stage(n, NB, W),
+             "executed_GBps": round(executed_bytes_one_stage(n, NB, W) / (ms * 1e-3) / 1e9, 1), "autotune_s": None if args.no_autotune else round(t_tune, 3)}
 
     if not args.skip_two_stage:
         # two-stage variant of the same workload (s_hat = 30: 6 blocks per big panel, W = 36)

@@ -26,30 +26,33 @@ struct Use {
     int rows;  // reduction rows of the whole reduction
 };
 
-// The passes of the one-stage block step (Fig. 2c with the first intra step) for p
-// previous columns, in launch order.
-void one_stage_uses(int W, bool f32, int red_first, int rows_first, int p, std::vector<Use>& out) {
-    if (p > 0) out.push_back({{W, f32, RED_PROJ, false, 0, false}, p, p});
-    out.push_back({{W, f32, red_first, p > 0, 0, p > 0}, p, rows_first});
-    out.push_back({{W, f32, RED_GRAM, false, 1, false}, 0, W});
-    if (p > 0)
-        out.push_back({{W, f32, RED_PROJ, false, 2, true}, 0, p});
-    else
-        out.push_back({{W, f32, RED_GRAM, false, 2, true}, 0, W});
-    if (p > 0) out.push_back({{W, f32, RED_GRAM, true, 0, true}, p, W});
-    out.push_back({{W, f32, RED_NONE, false, 1, true}, 0, 0});
+PassKey pair_key(int W, bool f32, int red, int kind) {
+    PassKey k{W, f32, red, false, 0, false};
+    k.pair = kind;
+    return k;
 }
 
-// The row-strip passes of one two-stage panel (Fig. 5): projection on the previous big
-// panels, update + sketch, forward substitution against the panel's earlier blocks.
-void two_stage_uses(int w, bool f32, int red_sk, int k, int p_old, int loc, std::vector<Use>& out) {
-    if (p_old > 0) {
-        out.push_back({{w, f32, RED_PROJ, false, 0, false}, 0, p_old});
-        out.push_back({{w, f32, red_sk, true, 0, true}, p_old, k});
+// The passes of one block of the one-stage schedule with p previous columns, in launch order:
+// looking ahead (next: another block follows) or on its own.
+void one_stage_uses(int W, bool f32, int red_first, int rows_first, int p, bool ahead, bool next,
+                    std::vector<Use>& out) {
+    const bool two = ahead && next;
+    if (ahead && p > 0 && !f32) {
+        out.push_back({pair_key(W, f32, red_first, PAIR_LEAD), W, rows_first});
     } else {
-        out.push_back({{w, f32, red_sk, false, 0, false}, 0, k});
+        if (ahead && p > 0) out.push_back({pair_key(W, f32, RED_GRAM, PAIR_CROSS), 0, W});
+        if (!ahead && p > 0) out.push_back({{W, f32, RED_PROJ, false, 0, false}, p, p});
+        out.push_back({{W, f32, red_first, p > 0, 0, p > 0}, p, rows_first});
     }
-    out.push_back({{w, f32, RED_NONE, loc > 0, 1, true}, loc, 0});
+    out.push_back({{W, f32, RED_GRAM, false, 1, false}, 0, W});
+    if (p > 0) out.push_back({pair_key(W, f32, RED_PROJ, two ? PAIR_PROJ : SOLO_PROJ), 0, p});
+    if (two && !f32)
+        out.push_back({pair_key(W, f32, RED_GRAM, PAIR_UPD), p, W});
+    else if (p > 0)
+        out.push_back({pair_key(W, f32, RED_GRAM, SOLO_UPD), p, W});
+    else
+        out.push_back({{W, f32, RED_GRAM, false, 2, true}, 0, W});
+    if (!two) out.push_back({{W, f32, RED_NONE, false, 1, true}, 0, 0});
 }
 
 }  // namespace
@@ -75,13 +78,12 @@ sko_status autotune_orth_impl(sko_ctx c, int64_t n, int32_t nb, int32_t w, const
     if (!o->two_stage) {
         const int red_first = rand ? red_sk : RED_GRAM;
         const int rows_first = rand ? sp.rows : w;
-        for (int j = 0; j < nb; ++j) one_stage_uses(w, f32, red_first, rows_first, j * w, uses);
+        const bool ahead = one_stage_shape_looks_ahead(nb, w, o->intra);
+        for (int j = 0; j < nb; ++j)
+            one_stage_uses(w, f32, red_first, rows_first, j * w, ahead, j + 1 < nb, uses);
     } else {
-        const int ppb = std::max(1, o->panels_per_big);
-        for (int j = 0; j < nb; ++j) {
-            const int big = j / ppb, i = j % ppb;
-            two_stage_uses(w, f32, red_sk, sp.rows, big * ppb * w, i * w, uses);
-        }
+        // the two-stage scheme's row-strip passes are the sketches of its panels
+        uses.push_back({{w, f32, red_sk, false, 0, false}, 0, sp.rows});
     }
     std::map<const void*, std::vector<Use>> groups;
     int pmax = 1, rows_max = w;
@@ -96,12 +98,12 @@ sko_status autotune_orth_impl(sko_ctx c, int64_t n, int32_t nb, int32_t w, const
     }
     if ((int64_t)pmax * w > kMaxUpdCoef) return SKO_EUNSUPPORTED;
 
-    // ---- scratch: Y, X (n x w), Q (n x pmax), coefficients, identity factors, partials
+    // ---- scratch: Y, X, Y2, X2 (n x w), Q (n x pmax), coefficients, identity factors, partials
     const size_t eb = f32 ? 4 : 8;
     const int64_t rpl_max = std::max(pass_rows_per_launch(w, RED_PROJ), pass_rows_per_launch(w, red_sk));
-    const int64_t part_stride = ((std::min<int64_t>(rows_max, rpl_max) * w + 31) / 32) * 32;
+    const int64_t part_stride = ((std::min<int64_t>(rows_max, rpl_max) * 2 * w + 31) / 32) * 32;
     const size_t tall = eb * (size_t)n;
-    const size_t bytes = tall * (2 * (size_t)w + pmax) + sizeof(double) * ((size_t)pmax * w + 2 * (size_t)w * w) +
+    const size_t bytes = tall * (4 * (size_t)w + pmax) + sizeof(double) * ((size_t)pmax * 2 * w + 2 * (size_t)w * w) +
                          sizeof(double) * (size_t)part_stride * 8 * cus + 1024;
     char* buf = nullptr;
     if (hipMalloc(&buf, bytes) != hipSuccess) return SKO_ENOMEM;
@@ -111,9 +113,11 @@ sko_status autotune_orth_impl(sko_ctx c, int64_t n, int32_t nb, int32_t w, const
     } guard{buf};
     char* Y = buf;
     char* X = Y + tall * w;
-    char* Q = X + tall * w;
+    char* Y2 = X + tall * w;
+    char* X2 = Y2 + tall * w;
+    char* Q = X2 + tall * w;
     double* Cu = reinterpret_cast<double*>(Q + tall * pmax);
-    double* R1 = Cu + (size_t)pmax * w;
+    double* R1 = Cu + (size_t)pmax * 2 * w;
     double* partials = R1 + 2 * (size_t)w * w;
     SKO_HIP(hipMemsetAsync(buf, 0, bytes, c->stream));
     std::vector<double> eye(2 * (size_t)w * w, 0.0);
@@ -147,6 +151,14 @@ sko_status autotune_orth_impl(sko_ctx c, int64_t n, int32_t nb, int32_t w, const
         a.R2 = R1 + (size_t)w * w;
         a.X = X;
         a.ldx = n;
+        a.Y2 = Y2;
+        a.ldy2 = n;
+        a.X2 = u.key.pair == PAIR_UPD || u.key.pair == PAIR_LEAD ? X2 : nullptr;
+        a.ldx2 = n;
+        if (u.key.pair == PAIR_LEAD) {  // its coefficients are those of x, not of Q
+            a.pu = 0;
+            a.ldcu = u.p;
+        }
         a.Qp = Q;
         a.ldqp = n;
         a.theta = sp.red == RED_SKETCH_DENSE ? o->sketch.theta : nullptr;

@@ -324,5 +324,8 @@ sko_status one_stage_block(Engine& e, const BlockBufs& b, int intra, int p, cons
                            int col0);
 
 bool sketch_ok(const sko_sketch& sk, int64_t n);
+// Whether the one-stage QR of nb blocks of w columns looks one block ahead (V and Q apart, or the
+// same columns).
+bool one_stage_shape_looks_ahead(int nb, int w, int intra);
 
 }  // namespace sko

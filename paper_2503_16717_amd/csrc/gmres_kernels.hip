@@ -434,9 +434,7 @@ __device__ __forceinline__ bool stage_entries(const T* __restrict__ src, int64_t
 
 // CSR structure check and diagonal scan, one row per thread over the row blocks blk, blk + nblk,
 // ... (a row is walked only where its pointers are in range, so nothing outside colind is read).
-// The diagonals a workgroup sees collect in LDS; at its end each is entered in the global table,
-// with device-scope accesses that all meet on one line: 2048 workgroups do that in a few
-// microseconds, one per 256 rows of the 192^3 matrix took 0.2 ms for it.
+// The diagonals a workgroup sees collect in LDS; at its end each is entered in the global table.
 __device__ __forceinline__ void csr_check_body(int64_t n, int64_t nnz, const int32_t* __restrict__ rowptr,
                                                const int32_t* __restrict__ colind, int* words, int64_t blk,
                                                int64_t nblk) {

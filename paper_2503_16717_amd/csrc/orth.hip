@@ -396,6 +396,10 @@ sko_status one_stage_lookahead(Engine& e, const BlockBufs& b, int intra, int nb,
     return e.plain({W, f32, RED_NONE, false, 1, true}, a);
 }
 
+bool one_stage_shape_looks_ahead(int nb, int w, int intra) {
+    return nb >= 2 && w <= kMaxPairW && intra != SKO_INTRA_CHOLQR2_RECURSIVE;
+}
+
 namespace {
 
 // The host reads a device status word (one synchronisation of the stream).
@@ -633,7 +637,7 @@ OneStageLayout layout_one_stage(sko_ctx c, int64_t n, int W, int pmax, int k, in
 // a V shifted against Q would not survive).
 bool one_stage_looks_ahead(int64_t n, int nb, int w, bool f32, int intra, const void* V, int64_t ldv, const void* Q,
                            int64_t ldq) {
-    if (nb < 2 || w > kMaxPairW || intra == SKO_INTRA_CHOLQR2_RECURSIVE) return false;
+    if (!one_stage_shape_looks_ahead(nb, w, intra)) return false;
     if (V == Q && ldv == ldq) return true;
     const int64_t eb = f32 ? 4 : 8, N = (int64_t)nb * w;
     const char *v0 = static_cast<const char*>(V), *q0 = static_cast<const char*>(Q);

@@ -1,0 +1,127 @@
+"""The matrix-powers operator by diagonals or as CSR: matrices on either side of each condition of
+the choice (number of diagonals, padding, column order) must solve alike.  Tolerances: the
+explicit relative residual at the solver's tolerance, and x within the tolerance times the
+condition number of the diagonally dominant test matrices (at most 100) of a direct solve."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2503_16717_amd import workloads as wl  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+TOL = 1e-11
+
+
+@pytest.fixture(scope="module")
+def B():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2503_16717_amd import binding
+    return binding
+
+
+@pytest.fixture(scope="module")
+def ctx(B):
+    c = B.Context(0)
+    yield c
+    c.close()
+
+
+def banded(n, offsets, seed, drop=0.0):
+    """Diagonally dominant matrix with random values on the given diagonals (a share dropped)."""
+    r = np.random.default_rng([21, seed])
+    rows, cols, vals = [], [], []
+    i = np.arange(n)
+    for o in offsets:
+        ok = (i + o >= 0) & (i + o < n) & ((r.uniform(size=n) >= drop) | (o == 0))
+        rows.append(i[ok])
+        cols.append(i[ok] + o)
+        v = r.uniform(-1.0, 1.0, ok.sum()) if o else np.full(ok.sum(), 1.5 * len(offsets))
+        vals.append(v)
+    rows, cols, vals = map(np.concatenate, (rows, cols, vals))
+    order = np.lexsort((cols, rows))
+    rowptr = np.zeros(n + 1, dtype=np.int64)
+    np.cumsum(np.bincount(rows, minlength=n), out=rowptr[1:])
+    return wl.CSR(n, rowptr, cols[order], vals[order])
+
+
+def csr_twin(A):
+    """The same matrix with one row's entries out of order, which keeps it off the diagonal form."""
+    row = int(np.argmax(np.diff(A.rowptr) > 1))
+    e0, e1 = A.rowptr[row], A.rowptr[row + 1]
+    T = wl.CSR(A.n, A.rowptr.copy(), A.colind.copy(), A.val.copy())
+    T.colind[e0:e1] = T.colind[e0:e1][::-1].copy()
+    T.val[e0:e1] = T.val[e0:e1][::-1].copy()
+    return T
+
+
+def solve_and_check(B, ctx, A, **kw):
+    import scipy.sparse.linalg as sla
+    b = wl.rhs_uniform(A.n, 3)
+    x, info, st = ctx.gmres(A, b, tol=TOL, **kw)
+    if st != B.SKO_OK:
+        # nearly a multiple of the identity: the Krylov space is exhausted, in either form
+        assert st == B.SKO_EBREAKDOWN and ctx.gmres(csr_twin(A), b, tol=TOL, **kw)[2] == st, (st, info)
+        return
+    S = A.to_scipy().tocsc()
+    x = x.cpu().numpy()
+    assert np.linalg.norm(b - S @ x) / np.linalg.norm(b) <= TOL
+    ref = sla.spsolve(S, b)
+    assert np.linalg.norm(x - ref) <= 100 * TOL * np.linalg.norm(ref)
+
+
+CASES = {
+    "1 diagonal": (700, [0], 0.0),
+    "3 diagonals": (513, [-1, 0, 1], 0.0),
+    "upper only": (1000, [0, 1, 7, 300], 0.0),
+    "far corners": (600, [-599, 0, 599], 0.0),
+    "16 diagonals": (2049, sorted([-900, -400, -77, -30, -9, -3, -2, -1, 0, 1, 2, 5, 11, 64, 500, 1000]), 0.0),
+    "17 diagonals": (2049, sorted([-901, -900, -400, -77, -30, -9, -3, -2, -1, 0, 1, 2, 5, 11, 64, 500, 1000]), 0.0),
+    "part-filled": (3000, [-40, -5, -1, 0, 1, 5, 40], 0.7),
+    "a few gaps": (3000, [-40, -1, 0, 1, 40], 0.05),
+}
+
+
+@pytest.mark.parametrize("name", CASES)
+@pytest.mark.parametrize("precision", ["f64", "mixed"])
+def test_diagonal_counts(B, ctx, name, precision):
+    n, offs, drop = CASES[name]
+    A = banded(n, offs, len(name), drop)
+    sk = B.make_sketch("sparse_sign", 64, 8, 1)
+    for kw in (dict(s=4, m=12), dict(s=4, m=12, two_stage=True, shat=12, precond=1)):
+        if len(offs) == 1 and kw.get("precond"):
+            # A D^{-1} = I: every Krylov vector equals the first (which column of rounding noise gives
+            # the first non-positive pivot depends on the storage)
+            assert ctx.gmres(A, wl.rhs_uniform(n, 3), tol=TOL, precision=precision, sketch=sk,
+                             **kw)[2] == B.SKO_EBREAKDOWN
+            continue
+        solve_and_check(B, ctx, A, precision=precision, sketch=sk, **kw)
+
+
+def test_rows_out_of_order_keep_csr(B, ctx):
+    A = csr_twin(banded(900, [-3, 0, 3], 5))
+    solve_and_check(B, ctx, A, s=4, m=12, sketch=B.make_sketch("sparse_sign", 64, 8, 1))
+
+
+@pytest.mark.parametrize("basis", ["monomial", "newton"])
+def test_two_rows_per_thread(B, ctx, basis):
+    """Above the size at which a thread takes two rows, odd row count."""
+    A = banded((1 << 18) + 261, [-513, -1, 0, 1, 513], 8)
+    solve_and_check(B, ctx, A, s=4, m=12, basis=basis, sketch=B.make_sketch("sparse_sign", 64, 8, 1))
+
+
+def test_batch_of_mixed_forms(B, ctx):
+    """One system of a batch off the diagonal form: the whole batch runs on CSR."""
+    for offs in ([-2, 0, 2], list(range(-9, 10))):
+        systems = [banded(400 + 37 * i, [-20, -1, 0, 1, 20], i) for i in range(3)] + [banded(777, offs, 9)]
+        dev = [B.csr_to_device(A) for A in systems]
+        bs = [torch.from_numpy(wl.rhs_uniform(A.n, 3)).cuda() for A in systems]
+        xs = [torch.zeros_like(b) for b in bs]
+        o = B.gmres_opts(s=4, m=12, shat=12, two_stage=True, precond=1, tol=TOL,
+                         sketch=B.make_sketch("sparse_sign", 64, 8, 1))
+        st, infos = ctx.sko_gmres_batched([d[0] for d in dev], [b.data_ptr() for b in bs], [x.data_ptr() for x in xs], o)
+        assert st == B.SKO_OK
+        for A, b, x in zip(systems, bs, xs):
+            b, x = b.cpu().numpy(), x.cpu().numpy()
+            assert np.linalg.norm(b - A.to_scipy() @ x) / np.linalg.norm(b) <= TOL
