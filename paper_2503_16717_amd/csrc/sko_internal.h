@@ -266,8 +266,9 @@ hipError_t launch_wide_update(int64_t n, int W, bool f32, const void* Y, int64_t
 
 // Row-wise X = (Y - Qu Cu) * R^{-1} for wide blocks (w <= 64); used by the big-panel
 // close of the two-stage scheme.  Rpk is R in the packed form of SmallArgs::Rpk (null: no
-// solve); Rpk2 and Rpk3 (W <= kFusedMaxW, no update, one system) are solved with after it.  pw (here and above, FP32 storage): panel
-// width of Rpk's columns, whose values are rounded to FP32 panel by panel.
+// solve); Rpk2 and Rpk3 (W <= kFusedMaxW, no update, one system) are solved with after it.  pw (here
+// and above, FP32 storage; one system, no update): panel width of Rpk's columns, whose values are
+// rounded to FP32 panel by panel.
 hipError_t launch_wide_rowop(int64_t n, int W, bool f32, const void* Y, int64_t ldy,
                              const void* Qu, int64_t ldqu, int pu, const double* Cu,
                              const double* Rpk, void* X, int64_t ldx, hipStream_t stream,

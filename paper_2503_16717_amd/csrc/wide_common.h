@@ -84,36 +84,37 @@ __device__ __forceinline__ void round_cols(double (&x)[WB]) {
     }
 }
 
-// FP32 storage, `bnd` a multiple of a panel width pw > 0 (bnd = pw = 0: none): a panel's columns
-// are rounded to the storage type when the next panel begins, as panels stored one by one are.
-template <typename T, int WB, int C>
+// PW (FP32 storage, panel width pw, bnd = pw): a panel's columns are rounded to the storage type
+// when the next panel begins, as panels stored one by one are.  The branch per column that this
+// takes stays out of the other solves (61 FP32 columns, 7.1 million rows: 1.12 against 0.91 ms).
+template <typename T, int WB, int C, bool PW>
 __device__ __forceinline__ void solve_cols(double (&x)[WB], CD Rs, int w, const double* sD, int pw, int bnd) {
     if constexpr (C < WB) {
         if (C < w) {
-            if constexpr (sizeof(T) == 4 && C > 0) {
+            if constexpr (PW && sizeof(T) == 4 && C > 0) {
                 if (C == bnd) {
                     round_cols<T, WB, C>(x);
                     bnd += pw;
                 }
             }
             x[C] = solve_col<WB, C>(x, Rs + w + C * (C - 1) / 2, x[C]) * sD[C];
-            solve_cols<T, WB, C + 1>(x, Rs, w, sD, pw, bnd);
+            solve_cols<T, WB, C + 1, PW>(x, Rs, w, sD, pw, bnd);
         }
     }
 }
 
 // x R1^{-1} [R2^{-1} [R3^{-1}]]; between the factors the row is rounded to the storage type, so
 // a chain gives what storing and loading the rows between the solves gives.
-template <typename T, int WB, int TRSM>
+template <typename T, int WB, int TRSM, bool PW>
 __device__ __forceinline__ void solve_chain(double (&x)[WB], CD R1, CD R2, CD R3, int w, const double* sD, int pw) {
-    if constexpr (TRSM >= 1) solve_cols<T, WB, 0>(x, per_strip(R1), w, sD, pw, pw);
+    if constexpr (TRSM >= 1) solve_cols<T, WB, 0, PW>(x, per_strip(R1), w, sD, pw, pw);
     if constexpr (TRSM >= 2) {
         round_cols<T, WB, WB>(x);
-        solve_cols<T, WB, 0>(x, per_strip(R2), w, sD + WB, 0, 0);
+        solve_cols<T, WB, 0, false>(x, per_strip(R2), w, sD + WB, 0, 0);
     }
     if constexpr (TRSM >= 3) {
         round_cols<T, WB, WB>(x);
-        solve_cols<T, WB, 0>(x, per_strip(R3), w, sD + 2 * WB, 0, 0);
+        solve_cols<T, WB, 0, false>(x, per_strip(R3), w, sD + 2 * WB, 0, 0);
     }
 }
 

@@ -81,7 +81,8 @@ __device__ __forceinline__ void rowop_red_body(const FusedArgs& fa, const int wg
 #pragma unroll
             for (int c = 0; c < WB; ++c)
                 x[c] = ldv_nt(lane_elem(Y + r0 + (int64_t)(c < w ? c : w - 1) * ldy, lane_bytes));
-            solve_chain<T, WB, TRSM>(x, R0, R20, R20, w, sD, ra.pw);
+            // one solve with the rows stored is the solver's close, which rounds whole rows only
+            solve_chain<T, WB, TRSM, !(TRSM == 1 && WRITE)>(x, R0, R20, R20, w, sD, ra.pw);
             if constexpr (WRITE) {
 #pragma unroll
                 for (int c = 0; c < WB; ++c) {
@@ -223,6 +224,7 @@ template <int WB, typename T>
 hipError_t fused_dispatch(const FusedArgs& fa, int* grid, hipStream_t st, const BatchReloc* br) {
     const bool two = fa.ra.Rpk2 != nullptr, write = fa.ra.X != nullptr;
     if (!fa.ra.Rpk || ((two || !write) && br)) return hipErrorInvalidValue;
+    if (!two && write && sizeof(T) == 4 && fa.ra.pw > 0) return hipErrorInvalidValue;  // compiled without PW
     const int te = fa.E ? (fa.me + 15) / 16 : 0;
     if (!two && write) {
         switch (te) {

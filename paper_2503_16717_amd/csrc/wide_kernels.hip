@@ -32,7 +32,7 @@ using namespace wide;
 // One row per thread, grid-stride over strips of ROW_NT rows.  The factor R and the update
 // coefficients are read through the scalar cache (every lane uses the same entry), loaded
 // again per strip; only the diagonal reciprocals sit in LDS.
-template <int WB, typename T, bool UPD, int TRSM>
+template <int WB, typename T, bool UPD, int TRSM, bool PW>
 __device__ __forceinline__ void rowop_body(const RowopArgs& ra, const int wg, const int nwg) {
     const int64_t n = ra.n;
     const int w0 = ra.w, pu = ra.pu;
@@ -64,16 +64,16 @@ __device__ __forceinline__ void rowop_body(const RowopArgs& ra, const int wg, co
 #pragma unroll
         for (int c = 0; c < WB; ++c) x[c] = ldv_nt(lane_elem(Y + r0 + (int64_t)(c < w ? c : w - 1) * ldy, lane_bytes));
         if constexpr (UPD) update_rows<WB, 1, T>(xa, Qu + row, ldqu, pu, Cs, pu, w);
-        solve_chain<T, WB, TRSM>(x, R0, R20, R30, w, sD, ra.pw);
+        solve_chain<T, WB, TRSM, PW>(x, R0, R20, R30, w, sD, ra.pw);
 #pragma unroll
         for (int c = 0; c < WB; ++c)
             if (c < w) stv_nt(lane_elem(X + r0 + (int64_t)c * ldx, lane_bytes), static_cast<T>(x[c]));
     }
 }
 
-template <int WB, typename T, bool UPD, int TRSM>
+template <int WB, typename T, bool UPD, int TRSM, bool PW>
 __global__ void __launch_bounds__(ROW_NT) wide_rowop_kernel(const RowopArgs ra) {
-    rowop_body<WB, T, UPD, TRSM>(ra, blockIdx.x, gridDim.x);
+    rowop_body<WB, T, UPD, TRSM, PW>(ra, blockIdx.x, gridDim.x);
 }
 
 template <int WB, typename T, bool UPD, int TRSM>
@@ -90,7 +90,7 @@ __global__ void __launch_bounds__(ROW_NT) wide_rowop_kernel_batched(const RowopA
     ra.Rpk = batch_ptr(br, sys, d, t.Rpk);
     ra.X = batch_ptr(br, sys, d, t.X);
     ra.ldx = batch_ld(br, d, t.ldx);
-    rowop_body<WB, T, UPD, TRSM>(ra, blockIdx.x, gridDim.x);
+    rowop_body<WB, T, UPD, TRSM, false>(ra, blockIdx.x, gridDim.x);
 }
 
 // TA = ceil(ma / 16) and TB = ceil(nb / 16) tiles at compile time: only the accumulators
@@ -177,13 +177,13 @@ __global__ void __launch_bounds__(GT) wide_gemm_tn_kernel_batched(const GemmArgs
 }
 
 // One system: the resident workgroups only, each walking its strips.
-template <int WB, typename T, bool UPD, int TRSM>
+template <int WB, typename T, bool UPD, int TRSM, bool PW = false>
 void rowop_launch1(const RowopArgs& ra, hipStream_t st) {
     const int64_t strips = (ra.n + ROW_NT - 1) / ROW_NT;
-    int cap = resident_grid(reinterpret_cast<const void*>(&wide_rowop_kernel<WB, T, UPD, TRSM>), ROW_NT);
+    int cap = resident_grid(reinterpret_cast<const void*>(&wide_rowop_kernel<WB, T, UPD, TRSM, PW>), ROW_NT);
     if (cap < 1) cap = 1024;
     const int grid = (int)std::min<int64_t>(strips, cap);
-    hipLaunchKernelGGL((wide_rowop_kernel<WB, T, UPD, TRSM>), dim3(grid), dim3(ROW_NT), 0, st, ra);
+    hipLaunchKernelGGL((wide_rowop_kernel<WB, T, UPD, TRSM, PW>), dim3(grid), dim3(ROW_NT), 0, st, ra);
 }
 
 template <int WB, typename T, bool UPD, int TRSM>
@@ -201,20 +201,27 @@ void rowop_launch(const RowopArgs& ra, hipStream_t st, const BatchReloc* br) {
 
 template <int WB, typename T>
 hipError_t rowop_dispatch(const RowopArgs& ra, hipStream_t st, const BatchReloc* br) {
+    if (sizeof(T) == 4 && ra.pw > 0 && (ra.pu > 0 || br)) return hipErrorInvalidValue;  // compiled without PW
     if (ra.pu > 0 && ra.Rpk2) return hipErrorInvalidValue;
     if (ra.pu > 0 && ra.Rpk)
         rowop_launch<WB, T, true, 1>(ra, st, br);
     else if (ra.pu > 0)
         rowop_launch<WB, T, true, 0>(ra, st, br);
-    else if (ra.Rpk && !ra.Rpk2)
+    else if (ra.Rpk && !ra.Rpk2) {
+        if constexpr (sizeof(T) == 4) {
+            if (ra.pw > 0 && !br) {
+                rowop_launch1<WB, T, false, 1, true>(ra, st);
+                return hipGetLastError();
+            }
+        }
         rowop_launch<WB, T, false, 1>(ra, st, br);
-    else if constexpr (WB <= kFusedMaxW) {
+    } else if constexpr (WB <= kFusedMaxW) {
         // chains of solves: one system, panels whose reductions are fused with the solves
         if (!ra.Rpk || br) return hipErrorInvalidValue;
         if (ra.Rpk3)
-            rowop_launch1<WB, T, false, 3>(ra, st);
+            rowop_launch1<WB, T, false, 3, sizeof(T) == 4>(ra, st);
         else
-            rowop_launch1<WB, T, false, 2>(ra, st);
+            rowop_launch1<WB, T, false, 2, sizeof(T) == 4>(ra, st);
     } else
         return hipErrorInvalidValue;
     return hipGetLastError();
