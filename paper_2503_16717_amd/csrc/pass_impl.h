@@ -139,6 +139,43 @@ __device__ __forceinline__ void store_rows(T* col, int64_t row0, int64_t n, cons
         if (row0 + r < n) stv(col + row0 + r, v[r]);
 }
 
+// Transposes 64 x 64 bits held one row per lane (lo, hi: bits 0..31 and 32..63): afterwards bit r
+// of lane l is what bit l of lane r was.  Six exchanges between lanes whose numbers differ in one
+// bit, 32 first; all 64 lanes take part.
+struct BitTranspose {
+    unsigned p16, p8, m4, r4, m2, r2, m1, r1;  // this lane's byte selectors, kept bits and rotations
+    __device__ __forceinline__ void init(int lane) {
+        p16 = (lane & 16) ? 0x07060302u : 0x05040100u;
+        p8 = (lane & 8) ? 0x03070105u : 0x06020400u;
+        m4 = (lane & 4) ? 0xf0f0f0f0u : 0x0f0f0f0fu;
+        r4 = (lane & 4) ? 4u : 28u;
+        m2 = (lane & 2) ? 0xccccccccu : 0x33333333u;
+        r2 = (lane & 2) ? 2u : 30u;
+        m1 = (lane & 1) ? 0xaaaaaaaau : 0x55555555u;
+        r1 = (lane & 1) ? 1u : 31u;
+    }
+    template <int CTRL>
+    __device__ __forceinline__ static unsigned from(unsigned x) {
+        return (unsigned)__builtin_amdgcn_mov_dpp((int)x, CTRL, 0xf, 0xf, true);
+    }
+    __device__ __forceinline__ static unsigned merge(unsigned m, unsigned x, unsigned p, unsigned r) {
+        return (x & m) | (__builtin_amdgcn_alignbit(p, p, r) & ~m);
+    }
+    __device__ __forceinline__ unsigned low(unsigned x) const {
+        const auto w = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        x = __builtin_amdgcn_perm(w[1], w[0], p16);
+        x = __builtin_amdgcn_perm(from<0x128>(x), x, p8);             // row_ror:8
+        x = merge(m4, x, from<0x1b>(from<0x141>(x)), r4);             // row_half_mirror, quad_perm 3210
+        x = merge(m2, x, from<0x4e>(x), r2);                          // quad_perm 2301
+        return merge(m1, x, from<0xb1>(x), r1);                       // quad_perm 1032
+    }
+    __device__ __forceinline__ void run(unsigned& lo, unsigned& hi) const {
+        const auto w = __builtin_amdgcn_permlane32_swap(lo, hi, false, false);
+        lo = low(w[0]);
+        hi = low(w[1]);
+    }
+};
+
 // Element types of a pass: TY the input block Y, TQ the basis operand (Qu of the update,
 // Qp of the projection), TX the written block X.  Plain passes use one storage type for
 // all three; the mixed-precision GMRES panel reads an FP64 panel against the FP32 basis.
@@ -255,33 +292,21 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
     for (int m = 0; m < (MF ? MT : 1); ++m) dacc[m] = double4_t{0.0, 0.0, 0.0, 0.0};
 
     // Sparse sketch on row masks (SPM): lane l accumulates sketch row g = red_row0 + l (and
-    // g + 64), which is slot j of hash byte spm_t (none: spm_t = -1); byte b selects slot
-    // floor((b >> 1) B / 128) of its B = k / zeta and carries the sign in bit 0.  Per 64 staged rows the wave forms,
-    // for every byte t, the ballots of the bits of each row's slot and of its sign; a lane
-    // keeps the rows whose slot bits all equal its own (spm_jn[i]: all ones where bit i of
-    // spm_j is 0, so that ballot is inverted) for its own byte, then adds those rows into its
-    // W sums in ascending row order.  Only the rows with a nonzero in the lane's sketch row
-    // are touched: zeta W products per row instead of k W on MFMA blocks.
-    constexpr int SPM_BITS = 7;  // slots per byte up to 128 (k <= 128)
-    int spm_t[SPM ? SPR : 1], spm_nbits = 0;
-    unsigned spm_jn[SPM ? SPR : 1][SPM ? SPM_BITS : 1];
+    // g + 64), which is slot j of hash byte t; byte b selects slot floor((b >> 1) B / 128) of its
+    // B = k / zeta and carries the sign in bit 0.  Per 64 staged rows each lane sets the bits of its
+    // own row's sketch rows in a word (and again those with a minus sign), and the wave transposes
+    // the 64 x 64 bits: lane l then has the mask of the rows that sketch row l takes.  It adds
+    // them into its W sums in ascending row order.  Only the rows with a nonzero in the lane's
+    // sketch row are touched: zeta W products per row instead of k W on MFMA blocks.  (128 sketch
+    // rows, 11 FP64 columns, 7 million rows: 219 us; 229 us with the masks formed from ballots of
+    // every slot bit, about 30 instructions per byte and 64 rows.)
     double sacc[SPM ? SPR : 1][SPM ? W : 1];
 #pragma unroll
     for (int q = 0; q < (SPM ? SPR : 1); ++q)
 #pragma unroll
         for (int c = 0; c < (SPM ? W : 1); ++c) sacc[q][c] = 0.0;
-    if constexpr (SPM) {
-        const int B = a.sk_k / a.sk_zeta;
-        while ((1 << spm_nbits) < B) ++spm_nbits;
-#pragma unroll
-        for (int q = 0; q < SPR; ++q) {
-            const int g = a.red_row0 + lane + 64 * q;
-            const int t = g / B, j = g - t * B;
-            spm_t[q] = (lane + 64 * q < a.red_rows && t < a.sk_zeta) ? t : -1;
-#pragma unroll
-            for (int i = 0; i < SPM_BITS; ++i) spm_jn[q][i] = ((j >> i) & 1) ? 0u : ~0u;
-        }
-    }
+    BitTranspose bt;
+    if constexpr (SPM) bt.init(lane);
 
     const int64_t nstrips = (n + STRIP - 1) / STRIP;
     for (int64_t s = wg; s < nstrips; s += nwg) {
@@ -516,37 +541,26 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
                     const uint64_t vm = __ballot(base + rb + lane < n);
                     unsigned ml[SPR], mh[SPR], sl[SPR], sh[SPR];
 #pragma unroll
-                    for (int q = 0; q < SPR; ++q) ml[q] = mh[q] = sl[q] = sh[q] = 0u;
+                    for (int q = 0; q < SPR; ++q) {
+                        ml[q] = mh[q] = sl[q] = sh[q] = 0u;
 #pragma unroll
-                    for (int t = 0; t < 8; ++t) {
-                        if (t < a.sk_zeta) {
-                            const unsigned b8 = (unsigned)(h >> (8 * t)) & 0xffu;
-                            const unsigned slot = ((b8 >> 1) * B) >> 7;
-                            unsigned cl[SPR], ch[SPR];
-#pragma unroll
-                            for (int q = 0; q < SPR; ++q) cl[q] = ch[q] = ~0u;
-#pragma unroll
-                            for (int i = 0; i < SPM_BITS; ++i) {
-                                if (i < spm_nbits) {
-                                    const uint64_t bi = __ballot((slot >> i) & 1u);
-#pragma unroll
-                                    for (int q = 0; q < SPR; ++q) {
-                                        cl[q] &= (unsigned)bi ^ spm_jn[q][i];
-                                        ch[q] &= (unsigned)(bi >> 32) ^ spm_jn[q][i];
-                                    }
-                                }
-                            }
-                            const uint64_t sg = __ballot(b8 & 1u);
-                            // keep this byte's masks only in the lanes whose sketch row it holds
-#pragma unroll
-                            for (int q = 0; q < SPR; ++q) {
-                                const unsigned mine = t == spm_t[q] ? ~0u : 0u;
-                                ml[q] |= cl[q] & mine;
-                                mh[q] |= ch[q] & mine;
-                                sl[q] |= (unsigned)sg & mine;
-                                sh[q] |= (unsigned)(sg >> 32) & mine;
+                        for (int t = 0; t < 8; ++t) {
+                            // the byte's first sketch row, counted from the lanes' first
+                            const int o = t * (int)B - a.red_row0 - 64 * q;
+                            if (t < a.sk_zeta && o < 64 && o + (int)B > 0) {
+                                const unsigned b8 = (unsigned)(h >> (8 * t)) & 0xffu;
+                                const int pos = o + (int)(((b8 >> 1) * B) >> 7);
+                                uint64_t bit = 1ull << (pos & 63);
+                                if (o < 0 || o + (int)B > 64) bit = (unsigned)pos < 64u ? bit : 0ull;
+                                const unsigned minus = 0u - (b8 & 1u);
+                                ml[q] |= (unsigned)bit;
+                                mh[q] |= (unsigned)(bit >> 32);
+                                sl[q] |= (unsigned)bit & minus;
+                                sh[q] |= (unsigned)(bit >> 32) & minus;
                             }
                         }
+                        bt.run(ml[q], mh[q]);
+                        bt.run(sl[q], sh[q]);
                     }
 #pragma unroll
                     for (int q = 0; q < SPR; ++q) {
@@ -853,6 +867,12 @@ __global__ void __launch_bounds__((Cfg<W, RED>::NT), (min_waves<W, T, RED, UPD, 
     pass_body<W, Tys<T, T, T>, RED, UPD, NTRSM, WRITE, MTX>(a, blockIdx.x, gridDim.x);
 }
 
+// The two-block and solve-first passes (PairKind).  All stay HBM-bound: at n = 2^24, 6 FP64 columns,
+// averaged over 36 previous ones, the projection of both blocks runs at 5.9 TB/s (1.02 ms), their
+// update at 5.5 TB/s (1.31 ms), the leading pass at 5.2 TB/s (0.62 ms); one block at a time, with
+// Q read for each, the same work took 0.99 + 1.23 ms (projections), 1.22 + 1.24 ms (updates) and
+// 0.29 ms.  In FP32 at 11 columns the projection of both blocks is held to 3.5 TB/s by its 22
+// columns' MFMAs and conversions.
 template <int W, typename T, int RED, int PAIR, int MTX = 0>
 __global__ void __launch_bounds__((Cfg<W, RED>::NT)) pass_kernel_pair(const PassArgs a) {
     constexpr int NTRSM = PAIR == PAIR_LEAD || PAIR == PAIR_CROSS ? 1 : 2;
