@@ -298,7 +298,7 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
     // the 64 x 64 bits: lane l then has the mask of the rows that sketch row l takes.  It adds
     // them into its W sums in ascending row order.  Only the rows with a nonzero in the lane's
     // sketch row are touched: zeta W products per row instead of k W on MFMA blocks.  (128 sketch
-    // rows, 11 FP64 columns, 7 million rows: 219 us; 229 us with the masks formed from ballots of
+    // rows, 11 FP64 columns, 7 million rows: 217 us; 229 us with the masks formed from ballots of
     // every slot bit, about 30 instructions per byte and 64 rows.)
     double sacc[SPM ? SPR : 1][SPM ? W : 1];
 #pragma unroll
@@ -549,7 +549,7 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
                             const int o = t * (int)B - a.red_row0 - 64 * q;
                             if (t < a.sk_zeta && o < 64 && o + (int)B > 0) {
                                 const unsigned b8 = (unsigned)(h >> (8 * t)) & 0xffu;
-                                const int pos = o + (int)(((b8 >> 1) * B) >> 7);
+                                const int pos = o + (int)(__umul24(b8 >> 1, B) >> 7);  // B <= 128
                                 uint64_t bit = 1ull << (pos & 63);
                                 if (o < 0 || o + (int)B > 64) bit = (unsigned)pos < 64u ? bit : 0ull;
                                 const unsigned minus = 0u - (b8 & 1u);
