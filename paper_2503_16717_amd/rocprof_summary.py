@@ -47,6 +47,14 @@ def source_digest(paths=PASS_SOURCES) -> str:
 def profiler_name(kernel: str) -> str | None:
     """'void sko::passk::pass_kernel<6, double, 1, false, 0, false, 4>(...)' -> the name the
     library's profiler gives the same launch ('pass W=6 f64 red=proj/mt4 upd=0 trsm=0 write=0')."""
+    m = re.search(r"pass_kernel_pair<(\d+), (double|float), (\d), (\d)(?:, (\d+))?>", kernel)
+    if m:
+        w, t, red, kind, mtx = m.groups()
+        upd, trsm, write, suffix = {1: (0, 2, 0, " pair"), 2: (1, 2, 1, " pair"), 3: (1, 1, 1, " lead"),
+                                    4: (0, 2, 0, " solo"), 5: (1, 2, 1, " solo"), 6: (0, 1, 1, " cross")}[int(kind)]
+        mt = (f"/mt{int(mtx)}" if mtx is not None and int(mtx) in (4, 6) else "/mt8") if red == "1" else ""
+        return (f"pass W={w} {'f32' if t == 'float' else 'f64'} red={_REDS[int(red)]}{mt} upd={upd} trsm={trsm} "
+                f"write={write}{suffix}")
     m = re.search(r"pass_kernel(?:_batched)?<(\d+), (double|float), (\d), (true|false), (\d), (true|false)"
                   r"(?:, (\d+))?>", kernel)
     if not m:
