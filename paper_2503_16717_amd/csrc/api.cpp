@@ -28,7 +28,7 @@ sko_status sko_create(int device, void* hip_stream, sko_ctx* out) {
     }
     if (hipHostMalloc(reinterpret_cast<void**>(&c->status_host), 64, hipHostMallocDefault) != hipSuccess) {
         delete c;
-        return SKO_ENOMEM;
+        return sko::out_of_memory();
     }
     // device address of this device's fixed scratch (sko_orth_block_noalloc), once per device
     sko_status ns = sko::noalloc_init(device);

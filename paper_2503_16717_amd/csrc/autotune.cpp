@@ -106,7 +106,7 @@ sko_status autotune_orth_impl(sko_ctx c, int64_t n, int32_t nb, int32_t w, const
     const size_t bytes = tall * (4 * (size_t)w + pmax) + sizeof(double) * ((size_t)pmax * 2 * w + 2 * (size_t)w * w) +
                          sizeof(double) * (size_t)part_stride * 8 * cus + 1024;
     char* buf = nullptr;
-    if (hipMalloc(&buf, bytes) != hipSuccess) return SKO_ENOMEM;
+    if (hipMalloc(&buf, bytes) != hipSuccess) return out_of_memory();
     struct Free {
         char* p;
         ~Free() { (void)hipFree(p); }

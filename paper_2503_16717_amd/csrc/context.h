@@ -220,6 +220,14 @@ class Arena {
     size_t used_ = 0;
 };
 
+// The status of a refused allocation.  The runtime keeps the error of a failed call until it is
+// read, and every launch reports the last error: left there, it would fail the next launch (the
+// retry with less memory, the caller's next call) although that launch succeeded.
+inline sko_status out_of_memory() {
+    (void)hipGetLastError();
+    return SKO_ENOMEM;
+}
+
 // Grow the context workspace to at least `bytes` (never shrinks).
 inline sko_status ensure_workspace(sko_ctx c, size_t bytes) {
     if (c->ws_bytes >= bytes) return SKO_OK;
@@ -232,7 +240,7 @@ inline sko_status ensure_workspace(sko_ctx c, size_t bytes) {
     size_t want = bytes + bytes / 4;
     if (hipMalloc(&c->ws, want) != hipSuccess) {
         c->ws = nullptr;
-        return SKO_ENOMEM;
+        return out_of_memory();
     }
     c->ws_bytes = want;
     return SKO_OK;
@@ -249,7 +257,7 @@ inline sko_status ensure_pinned(sko_ctx c, size_t bytes) {
     }
     if (hipHostMalloc(&c->pinned, bytes, hipHostMallocDefault) != hipSuccess) {
         c->pinned = nullptr;
-        return SKO_ENOMEM;
+        return out_of_memory();
     }
     c->pinned_bytes = bytes;
     return SKO_OK;
@@ -260,7 +268,7 @@ inline sko_status ensure_zerocopy(sko_ctx c) {
     if (c->zc_host) return SKO_OK;
     void* h = nullptr;
     if (hipHostMalloc(&h, 4 * sizeof(double), hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess)
-        return SKO_ENOMEM;
+        return out_of_memory();
     void* d = nullptr;
     if (hipHostGetDevicePointer(&d, h, 0) != hipSuccess) {
         (void)hipHostFree(h);
@@ -276,7 +284,7 @@ constexpr int kResultDoubles = 8192;  // capacity of res_host: results, then the
 inline sko_status alloc_results(sko_ctx c) {
     void* h = nullptr;
     if (hipHostMalloc(&h, sizeof(double) * kResultDoubles, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess)
-        return SKO_ENOMEM;
+        return out_of_memory();
     void* d = nullptr;
     if (hipHostGetDevicePointer(&d, h, 0) != hipSuccess) {
         (void)hipHostFree(h);
