@@ -125,3 +125,58 @@ def test_batch_of_mixed_forms(B, ctx):
         for A, b, x in zip(systems, bs, xs):
             b, x = b.cpu().numpy(), x.cpu().numpy()
             assert np.linalg.norm(b - A.to_scipy() @ x) / np.linalg.norm(b) <= TOL
+
+
+def coupled_fields(N, dim=2):
+    """Two stencil fields that share a unit coupling: diagonals at both ends of the matrix, so no
+    stretch of rows has every diagonal inside it."""
+    import scipy.sparse as sp
+    S = (wl.convdiff_2d(N, 10.0, 20.0) if dim == 2 else wl.convdiff_3d(N, (5.0, 10.0, 15.0))).to_scipy()
+    S = S + sp.identity(S.shape[0])
+    T = sp.bmat([[S, 0.1 * sp.identity(S.shape[0])], [-0.1 * sp.identity(S.shape[0]), S]]).tocsr()
+    T.sort_indices()
+    return wl.CSR(T.shape[0], T.indptr.astype(np.int64), T.indices, T.data)
+
+
+def spmv_kernels(ctx, solve, repeats=5):
+    """{kernel name: mean microseconds} of the matrix-powers launches of `solve`, the best of several runs."""
+    best = {}
+    for _ in range(repeats):
+        ctx.sko_profile_enable(True)
+        solve()
+        for k in ctx.sko_profile_read():
+            if k["name"].startswith("spmv"):
+                t = 1e3 * k["total_ms"] / k["launches"]
+                best[k["name"]] = min(t, best.get(k["name"], t))
+        ctx.sko_profile_enable(False)
+    return best
+
+
+# 2 x 12^2 rows: one workgroup; 2 x 31^2: a ragged last one; 2 x 400^2: two rows per thread
+@pytest.mark.parametrize("N,dim", [(12, 2), (31, 2), (400, 2), (9, 3)])
+@pytest.mark.parametrize("precision", ["f64", "mixed"])
+def test_coupled_fields_solve(B, ctx, N, dim, precision):
+    A = coupled_fields(N, dim)
+    b = wl.rhs_uniform(A.n, 3)
+    kw = dict(s=4, m=12, precond=1, precision=precision, tol=1e-8, maxiter=4000,
+              sketch=B.make_sketch("sparse_sign", 64, 8, 1))
+    assert list(spmv_kernels(ctx, lambda: ctx.gmres(A, b, **kw), 1)) == [
+        "spmv dia " + ("f32" if precision == "mixed" else "f64")]
+    for two in (dict(), dict(two_stage=True, shat=12)):
+        x, info, st = ctx.gmres(A, b, **kw, **two)
+        assert st == B.SKO_OK, (st, info)
+        assert np.linalg.norm(b - A.to_scipy() @ x.cpu().numpy()) / np.linalg.norm(b) <= 1e-8
+
+
+@pytest.mark.parametrize("precision", ["f64", "mixed"])
+def test_coupled_fields_are_no_slower_by_diagonals(B, ctx, precision):
+    """The form is chosen for its fewer bytes; every workgroup of this matrix has a diagonal outside."""
+    A = coupled_fields(1000)
+    b = wl.rhs_uniform(A.n, 3)
+    kw = dict(s=5, m=20, precision=precision, tol=1e-14, maxiter=20, sketch=B.make_sketch("sparse_sign", 64, 8, 1))
+    dia = spmv_kernels(ctx, lambda: ctx.gmres(A, b, **kw))
+    csr = spmv_kernels(ctx, lambda: ctx.gmres(csr_twin(A), b, **kw))
+    print(dia, csr, flush=True)
+    ty = "f32" if precision == "mixed" else "f64"
+    assert list(dia) == [f"spmv dia {ty}"] and list(csr) == [f"spmv {ty}"]
+    assert dia[f"spmv dia {ty}"] <= csr[f"spmv {ty}"]
