@@ -33,7 +33,11 @@ sko_status sko_create(int device, void* hip_stream, sko_ctx* out) {
     // device address of this device's fixed scratch (sko_orth_block_noalloc), once per device
     sko_status ns = sko::noalloc_init(device);
     if (ns == SKO_OK) ns = sko::alloc_results(c);
+    if (ns == SKO_OK && hipMalloc(reinterpret_cast<void**>(&c->words),
+                                  sizeof(int) * (sko::kStatusWords + sko::kCheckWords)) != hipSuccess)
+        ns = sko::out_of_memory();
     if (ns != SKO_OK) {
+        if (c->res_host) (void)hipHostFree(c->res_host);
         (void)hipHostFree(c->status_host);
         delete c;
         return ns;
@@ -49,6 +53,7 @@ sko_status sko_destroy(sko_ctx c) {
     if (c->ws) (void)hipFree(c->ws);
     if (c->status_host) (void)hipHostFree(c->status_host);
     if (c->res_host) (void)hipHostFree(c->res_host);
+    if (c->words) (void)hipFree(c->words);
     if (c->pinned) (void)hipHostFree(c->pinned);
     if (c->zc_host) (void)hipHostFree(c->zc_host);
     if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);

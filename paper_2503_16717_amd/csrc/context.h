@@ -187,6 +187,10 @@ struct sko_ctx_s {
     // launch, several times more into pageable memory.  res_dev: its device address.
     double* res_host = nullptr;
     double* res_dev = nullptr;
+    // device words that outlive the workspace's growth (from sko_create): the single-system GMRES
+    // solver's status and arrival counters, then the words of its matrix check, which run before
+    // the workspace's size is known
+    int* words = nullptr;
     sko::Profiler prof;
     // sko_autotune_orth: workgroups per CU per (pass kernel, log2 of its strip count)
     std::map<std::pair<const void*, int>, int> grid_wpc;
@@ -278,6 +282,8 @@ inline sko_status ensure_zerocopy(sko_ctx c) {
     c->zc_dev = static_cast<double*>(d);
     return SKO_OK;
 }
+
+constexpr int kStatusWords = 64, kCheckWords = 64;  // sko_ctx_s::words
 
 constexpr int kResultDoubles = 8192;  // capacity of res_host: results, then the status word
 

@@ -544,6 +544,16 @@ sko_status check_opts(const sko_csr* A, const sko_gmres_opts* o, GmCtx& g) {
     return SKO_OK;
 }
 
+// Whether a solve of at most maxiter vectors is long enough for the operator's diagonal storage.  On
+// 192^3 (FP64) scan and fill cost 240 us where the CSR values would be used as they are, and 20 us
+// where Jacobi scaling copies them anyway; an SpMV gains 82 us.  Solves by diagonals against CSR, us:
+// 1 vector 1298 / 1163, 2 1445 / 1388, 3 1574 / 1603, 4 1706 / 1828 (no Jacobi, 192^3); at 3 vectors
+// 262 / 265 (64^3, Jacobi) and 368 / 363 (1000 x 1000); at 4 393 / 399 (1000 x 1000).
+bool diagonals_may_pay(const GmCtx& g, int64_t maxiter) {
+    const int64_t step = g.two ? g.shat : g.s;
+    return maxiter >= kDiaMinVectors || (maxiter + step - 1) / step * step >= kDiaMinVectors;
+}
+
 // Rows of the sketch (final = false: the rows the passes reduce, k_count for Count-Gauss).
 int sketch_rows(const GmCtx& g, bool final = true) {
     const bool need_sketch = g.two || g.intra == SKO_INTRA_RANDCHOLQR;
@@ -569,18 +579,17 @@ sko_status gmres_impl(sko_ctx c, const sko_csr* A, const double* b, double* x, c
     EventPair ev_total;
     SKO_HIP(ev_total.create());
     SKO_HIP(hipEventRecord(ev_total.a, g.st));
-    // ---- CSR structure check before any kernel indexes through it, and the diagonal scan; its
-    // words stand at the start of the workspace until they are read
-    sko_status s = ensure_workspace(c, 256);
-    if (s) return s;
+    // ---- CSR structure check before any kernel indexes through it, and the diagonal scan
+    sko_status s;
     if ((s = ensure_pinned(c, 256))) return s;
     if ((s = ensure_zerocopy(c))) return s;
     DiaView dia;
     {
-        int* words = static_cast<int*>(c->ws);
+        int* words = c->words + kStatusWords;
         int32_t* host = static_cast<int32_t*>(c->pinned);
-        SKO_HIP(launch_zero(words, 256, g.st));
-        SKO_HIP(launch_csr_check(A->n, A->nnz, A->rowptr, A->colind, words, g.st));
+        static_assert(kScanWords <= kCheckWords, "the check's words fit the context's");
+        SKO_HIP(launch_zero(c->words, sizeof(int) * (kStatusWords + kCheckWords), g.st));
+        SKO_HIP(launch_csr_check(A->n, A->nnz, A->rowptr, A->colind, diagonals_may_pay(g, maxiter), words, g.st));
         SKO_HIP(hipMemcpyAsync(host, words, sizeof(int32_t) * kScanWords, hipMemcpyDeviceToHost, g.st));
         SKO_HIP(hipStreamSynchronize(g.st));
         if (host[0]) return SKO_EINVAL;
@@ -629,7 +638,7 @@ sko_status gmres_impl(sko_ctx c, const sko_csr* A, const double* b, double* x, c
     PhaseTimer pt;
     pt.on = o->phase_timing != 0;
     g.pt = &pt;
-    SKO_HIP(launch_zero(g.status, 256, g.st));
+    g.status = c->words;
 
     // ---- operator set-up: diagonal form, or Jacobi scaling / float copy of the MPK values
     g.A = CsrView{A->n, A->nnz, A->rowptr, A->colind, A->val, A->val, DiaView{}};
@@ -840,9 +849,11 @@ sko_status gmres_batched_impl(sko_ctx c, int32_t nsys, const sko_csr* A, const d
     const int k = sketch_rows(g), kr = sketch_rows(g, false);
     const bool own_vals = g.jacobi || g.f32;
     int64_t max_n = 0;
+    bool halves = false;
     double nnz_sum = 0.0, n_sum = 0.0;
     for (int32_t i = 0; i < nsys; ++i) {
         max_n = std::max<int64_t>(max_n, A[i].n);
+        halves = halves || long_rows(A[i].n, A[i].nnz);
         nnz_sum += (double)A[i].nnz;
         n_sum += (double)A[i].n;
     }
@@ -888,7 +899,7 @@ sko_status gmres_batched_impl(sko_ctx c, int32_t nsys, const sko_csr* A, const d
         }
         SKO_HIP(hipMemcpyAsync(tbl, tbl_host, sizeof(BatchSys) * nsys, hipMemcpyHostToDevice, g.st));
         SKO_HIP(launch_zero(words, words_bytes, g.st));
-        SKO_HIP(launch_csr_check_batched(nsys, max_n, tbl, words, g.st));
+        SKO_HIP(launch_csr_check_batched(nsys, max_n, tbl, diagonals_may_pay(g, maxiter), halves, words, g.st));
         SKO_HIP(hipMemcpyAsync(host, words, words_bytes, hipMemcpyDeviceToHost, g.st));
         SKO_HIP(hipStreamSynchronize(g.st));
         for (int32_t i = 0; i < nsys; ++i) {
@@ -1011,7 +1022,7 @@ sko_status gmres_batched_impl(sko_ctx c, int32_t nsys, const sko_csr* A, const d
     }
     SKO_HIP(hipMemcpyAsync(tbl_d, tbl_h, sizeof(BatchSys) * nsys, hipMemcpyHostToDevice, g.st));
     if (g.jacobi) SKO_HIP(launch_jacobi_setup_batched(nsys, max_n, tbl_d, small0 + st_off, (int64_t)L.bytes, g.st));
-    if (g.dia_batch) SKO_HIP(launch_fill_diagonals_batched(nsys, max_n, tbl_d, g.f32, g.st));
+    if (g.dia_batch) SKO_HIP(launch_fill_diagonals_batched(nsys, max_n, tbl_d, g.f32, halves, g.st));
     // ---- ||b||, and CSR operator values, system by system
     for (int32_t i = 0; i < nsys; ++i) {
         if (S[i].finished) continue;

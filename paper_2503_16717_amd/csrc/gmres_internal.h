@@ -15,6 +15,7 @@ struct BatchSys;
 // A matrix whose nonzeros lie on at most kMaxDiags diagonals, in diagonal storage: value k of
 // row i (column i + off[k], off ascending) at val[k * ld + i], zero where the row has none.
 constexpr int kMaxDiags = 16;
+constexpr int64_t kDiaMinVectors = 4;  // shortest solve whose set-up looks for diagonals
 struct DiaView {
     const void* val = nullptr;  // MPK operator values (double or float); null: not in this form
     int64_t ld = 0;
@@ -59,19 +60,24 @@ hipError_t launch_residual(const CsrView& A, const double* x, const double* b, b
                            int grid, hipStream_t st);
 hipError_t launch_update(int64_t n, bool f32, const void* Q, int64_t ldq, int k, const double* y,
                          const double* dinv, double* x, hipStream_t st);
-// `words`: kScanWords ints, zero.
-hipError_t launch_csr_check(int64_t n, int64_t nnz, const int32_t* rowptr, const int32_t* colind, int* words,
-                            hipStream_t st);
+// `words`: kScanWords ints, zero.  scan: look for the diagonals too (without it words[1] is set).
+hipError_t launch_csr_check(int64_t n, int64_t nnz, const int32_t* rowptr, const int32_t* colind, bool scan,
+                            int* words, hipStream_t st);
 // d.val from the CSR values (scaled by dinv[column] if given).
 hipError_t launch_fill_diagonals(int64_t n, int64_t nnz, const int32_t* rowptr, const int32_t* colind,
                                  const double* val, const double* dinv, bool f32, const DiaView& d, hipStream_t st);
+// Whether a matrix's rows are staged in two halves (more entries per row than one part holds);
+// `halves` below: whether any system's are.
+bool long_rows(int64_t n, int64_t nnz);
 // The set-up of many systems in one launch each: system i's row of the device table `sys` (a
 // system with n = 0 is left alone), its check words at words + 32 i, its status word (Jacobi)
 // i * pitch bytes behind status0.
-hipError_t launch_csr_check_batched(int nsys, int64_t max_n, const BatchSys* sys, int* words, hipStream_t st);
+hipError_t launch_csr_check_batched(int nsys, int64_t max_n, const BatchSys* sys, bool scan, bool halves, int* words,
+                                    hipStream_t st);
 hipError_t launch_jacobi_setup_batched(int nsys, int64_t max_n, const BatchSys* sys, void* status0, int64_t pitch,
                                        hipStream_t st);
-hipError_t launch_fill_diagonals_batched(int nsys, int64_t max_n, const BatchSys* sys, bool f32, hipStream_t st);
+hipError_t launch_fill_diagonals_batched(int nsys, int64_t max_n, const BatchSys* sys, bool f32, bool halves,
+                                         hipStream_t st);
 hipError_t launch_jacobi_setup(int64_t n, int64_t nnz, const int32_t* rowptr, const int32_t* colind,
                                const double* val, double* dinv, int* status, hipStream_t st);
 hipError_t launch_scale_values(int64_t nnz, const int32_t* colind, const double* val, const double* dinv, bool f32,

@@ -8,6 +8,7 @@
 //   * the small Hessenberg bookkeeping (T_in / T_out, Givens least squares).
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "batch.h"
 #include "gmres_internal.h"
@@ -450,107 +451,263 @@ __global__ void __launch_bounds__(NT) spmv_dia_kernel_flat(const TX* x0, TY* y0,
 constexpr int32_t kNoDiag = 0;  // words hold offset + kDiagBias, so 0 means unused
 constexpr int64_t kDiagBias = (int64_t)1 << 31;
 
-// Entries [e0, e1) of the workgroup's rows copied into LDS with coalesced loads; false (nothing
-// copied) if they are out of range or too many.
-template <typename T>
+// Entries [e0, e1) of the workgroup's rows copied into LDS with coalesced loads, all in flight
+// together; false (nothing copied) if they are out of range or too many.  NTL: non-temporal.
+template <bool NTL, typename T>
 __device__ __forceinline__ bool stage_entries(const T* __restrict__ src, int64_t e0, int64_t e1, int64_t nnz, T* lds) {
     if (e0 < 0 || e1 < e0 || e1 > nnz || e1 - e0 > STAGE) return false;
-    for (int i = threadIdx.x; i < (int)(e1 - e0); i += NT) lds[i] = __builtin_nontemporal_load(src + e0 + i);
+    const int cnt = (int)(e1 - e0);
+    T v[STAGE / NT];
+#pragma unroll
+    for (int u = 0; u < STAGE / NT; ++u) {
+        const int i = u * NT + threadIdx.x;
+        if (i < cnt) v[u] = NTL ? __builtin_nontemporal_load(src + e0 + i) : src[e0 + i];
+    }
+#pragma unroll
+    for (int u = 0; u < STAGE / NT; ++u) {
+        const int i = u * NT + threadIdx.x;
+        if (i < cnt) lds[i] = v[u];
+    }
     return true;
 }
 
-// CSR structure check and diagonal scan, one row per thread over the row blocks blk, blk + nblk,
-// ... (a row is walked only where its pointers are in range, so nothing outside colind is read).
-// The diagonals a workgroup sees collect in LDS; at its end each is entered in the global table.
-__device__ __forceinline__ void csr_check_body(int64_t n, int64_t nnz, const int32_t* __restrict__ rowptr,
-                                               const int32_t* __restrict__ colind, int* words, int64_t blk,
-                                               int64_t nblk) {
-    __shared__ unsigned tab[kMaxDiags];
-    __shared__ int flags[2];
-    __shared__ int32_t sc[STAGE];
-    if (threadIdx.x < kMaxDiags) tab[threadIdx.x] = 0u;
-    if (threadIdx.x < 2) flags[threadIdx.x] = 0;
-    auto enter = [&](unsigned key) {
-        for (int k = 0; k < kMaxDiags; ++k) {
-            const unsigned have = *const_cast<volatile unsigned*>(&tab[k]);
-            if (have == key) return true;
-            if (have == 0u) {
-                const unsigned was = atomicCAS(&tab[k], 0u, key);
-                if (was == 0u || was == key) return true;
-            }
-        }
-        return false;
-    };
-    bool bad = false, many = false;
-    for (int64_t base = blk * NT; base <= n; base += nblk * NT) {
-        const int64_t rend = base + NT < n ? base + NT : n;
-        int64_t o = 0, o1 = 0;
-        bool staged = false;
-        __syncthreads();  // the block before has been read (and the table cleared)
-        if (base < n) {
-            o = rowptr[base];
-            o1 = rowptr[rend];
-            staged = stage_entries(colind, o, o1, nnz, sc);
-        }
-        __syncthreads();
-        const int64_t i = base + threadIdx.x;
-        if (i > n) continue;
-        const int32_t r = rowptr[i];
-        bad = bad || r < 0 || r > nnz || (i == 0 && r != 0) || (i == n && r != nnz);
-        if (i == n) continue;
-        const int32_t r1 = rowptr[i + 1];
-        bad = bad || r1 < r || r1 > nnz;
-        if (bad) continue;
-        // (unordered row pointers may leave the staged range: those rows read colind)
-        const bool in = staged && r >= o && r1 <= o1;
-        int64_t prev = -1;
-        for (int32_t e = r; e < r1; ++e) {
-            const int32_t c = in ? sc[e - o] : colind[e];
-            bad = bad || c < 0 || c >= n;
-            many = many || c <= prev;
-            prev = c;
-            // offset + 2^31 (never 0: offsets are above -2^31)
-            if (!bad && !many) many = !enter((unsigned)((int64_t)c - i + kDiagBias));
+// A workgroup's NT rows from `base`: staged in one part, or (HALVES) in two, for matrices whose rows
+// hold more than STAGE / NT entries on average; rows of up to kMaxDiags entries then still fit.
+// (13 diagonals, 2^20 rows: a solve of 20 vectors takes 1.39 ms, 1.62 ms with rows that read the
+// arrays directly.  Shorter rows keep the one part: check and fill of the 192^3 stencil take 102 and
+// 210 us, 186 and 259 us where the number of parts is decided per workgroup.)
+static_assert(NT / 2 * kMaxDiags <= STAGE, "half the rows of a diagonal matrix are staged at once");
+template <bool HALVES>
+struct RowParts {
+    static constexpr int N = HALVES ? 2 : 1;
+    int64_t first, mid, last;
+    __device__ RowParts(int64_t n, int64_t base, const int32_t* __restrict__ rowptr) {
+        first = rowptr[base];
+        mid = HALVES ? rowptr[base + NT / 2 < n ? base + NT / 2 : n] : 0;
+        last = rowptr[base + NT < n ? base + NT : n];
+    }
+    __device__ int64_t begin(int part) const { return part ? mid : first; }
+    __device__ int64_t end(int part) const { return part == N - 1 ? last : mid; }
+    __device__ static bool mine(int part) { return !HALVES || (int)(threadIdx.x >= NT / 2) == part; }
+};
+
+// Enters key into a table of kMaxDiags words (0: free); false if it is full.
+__device__ __forceinline__ bool enter_key(unsigned* tab, unsigned key) {
+    for (int k = 0; k < kMaxDiags; ++k) {
+        const unsigned have = *const_cast<volatile unsigned*>(&tab[k]);
+        if (have == key) return true;
+        if (have == 0u) {
+            const unsigned was = atomicCAS(&tab[k], 0u, key);
+            if (was == 0u || was == key) return true;
         }
     }
+    return false;
+}
+
+// The wave's smallest x, on DPP moves (a shuffle per step costs an LDS round trip each).
+__device__ __forceinline__ unsigned wave_min(unsigned x) {
+    auto step = [&](auto ctrl) {
+        const unsigned o = (unsigned)__builtin_amdgcn_mov_dpp((int)x, decltype(ctrl)::value, 0xf, 0xf, true);
+        x = o < x ? o : x;
+    };
+    step(std::integral_constant<int, 0xb1>{});   // quad_perm 1032
+    step(std::integral_constant<int, 0x4e>{});   // quad_perm 2301
+    step(std::integral_constant<int, 0x141>{});  // row_half_mirror
+    step(std::integral_constant<int, 0x140>{});  // row_mirror
+    unsigned m = (unsigned)__builtin_amdgcn_readlane((int)x, 0);
+#pragma unroll
+    for (int l = 16; l < 64; l += 16) {
+        const unsigned o = (unsigned)__builtin_amdgcn_readlane((int)x, l);
+        m = o < m ? o : m;
+    }
+    return m;
+}
+
+struct PatternScratch {
+    int32_t first[64], len[64];
+    int32_t col[64 * (kMaxDiags + 1)];  // a row's columns, kMaxDiags + 1 words apart
+};
+
+// The diagonals of 64 sampled rows (one drawn from each 64th of the matrix), ascending, as offsets
+// in pat (LDS); returns how many, or -1 if these rows already hold more than kMaxDiags or are not
+// sorted and in range.  By a whole workgroup; each finds the same.
+__device__ __forceinline__ int sample_pattern(int64_t n, int64_t nnz, const int32_t* __restrict__ rowptr,
+                                              const int32_t* __restrict__ colind, PatternScratch& ps, int32_t* pat,
+                                              int* count) {
+    const int tid = threadIdx.x;
+    const int64_t step = n / 64;
+    int64_t row = step > 0 ? tid * step + (int64_t)(((uint64_t)(tid * 2654435761u) * (uint64_t)step) >> 32) : tid;
+    if (row >= n) row = n - 1;
+    int len = 0;
+    if (tid < 64) {
+        const int32_t r = rowptr[row], r1 = rowptr[row + 1];
+        if (r >= 0 && r1 >= r && r1 <= nnz) len = r1 - r;
+        ps.first[tid] = r;
+        ps.len[tid] = len;
+    }
+    __syncthreads();
+    constexpr int PER = 64 * kMaxDiags / NT;  // entries per thread
+    int32_t c[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int i = u * NT + tid, q = i / kMaxDiags, k = i % kMaxDiags;
+        c[u] = k < ps.len[q] ? colind[ps.first[q] + k] : 0;
+    }
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int i = u * NT + tid, q = i / kMaxDiags, k = i % kMaxDiags;
+        ps.col[q * (kMaxDiags + 1) + k] = c[u];
+    }
+    __syncthreads();
+    if (tid < 64) {
+        // the rows' offsets are merged: each round takes the smallest one left
+        const int32_t* col = ps.col + tid * (kMaxDiags + 1);
+        constexpr unsigned NONE = ~0u;
+        bool over = len > kMaxDiags;
+        int at = 0, np = 0;
+        int32_t prev = -1;
+        auto next = [&]() -> unsigned {  // offset + 2^31 - 1
+            if (at >= len || over) return NONE;
+            const int32_t cc = col[at++];
+            over = over || cc <= prev || cc >= n;
+            prev = cc;
+            return (unsigned)(cc - row + (kDiagBias - 1));
+        };
+        unsigned cur = next();
+        while (!__ballot(over)) {
+            const unsigned least = wave_min(cur);
+            if (least == NONE) break;
+            if (np == kMaxDiags) {
+                over = true;
+                break;
+            }
+            if (tid == 0) pat[np] = (int32_t)((int64_t)least - (kDiagBias - 1));
+            ++np;
+            if (cur == least) cur = next();
+        }
+        const bool none = __ballot(over) != 0;
+        if (tid == 0) *count = none ? -1 : np;
+    }
+    __syncthreads();
+    return *count;
+}
+
+// CSR structure check and (scan) diagonal scan by workgroup blk of nblk <= n / NT + 1, each on the
+// row blocks blk, blk + nblk, ...  (nothing outside rowptr[0..n] and colind[0..nnz) is read,
+// whatever they hold).  Without the scan, or where the sampled rows already rule diagonal storage
+// out, the columns are checked entry by entry.  Otherwise one row per thread:
+// a row whose entries all lie on the sampled diagonals needs one pass along them and reports
+// nothing (block 0 reports them); the diagonals of other rows collect in LDS, and at its end a
+// workgroup enters those that the global table does not hold yet.
+// The 7-point stencil on 192^3 takes 102 us (233 us with every entry looked up in the LDS table and
+// every workgroup entering all of its diagonals; 70 us for the entry-by-entry check alone).
+template <bool HALVES>
+__device__ __forceinline__ void csr_check_body(int64_t n, int64_t nnz, const int32_t* __restrict__ rowptr,
+                                               const int32_t* __restrict__ colind, bool scan, int* words,
+                                               int64_t blk, int64_t nblk) {
+    __shared__ unsigned tab[kMaxDiags], known[kMaxDiags];
+    __shared__ int flags[2], npat;
+    __shared__ int32_t pat[kMaxDiags];
+    __shared__ __align__(16) int32_t sc[STAGE];
+    static_assert(sizeof(PatternScratch) <= sizeof(sc), "the sample's scratch lies in the staging area");
+    const int tid = threadIdx.x;
+    if (tid < kMaxDiags) tab[tid] = 0u;
+    if (tid < 2) flags[tid] = 0;
+    if (!scan) __syncthreads();
+    const int np = scan ? sample_pattern(n, nnz, rowptr, colind, *reinterpret_cast<PatternScratch*>(sc), pat, &npat) : -1;
+    if (blk == 0 && tid < np) tab[tid] = (unsigned)((int64_t)pat[tid] + kDiagBias);
+    // offset + 2^31 (never 0: offsets are above -2^31)
+    auto enter = [&](int64_t off) {
+        for (int k = 0; k < np; ++k)
+            if (pat[k] == off) return true;
+        return enter_key(tab, (unsigned)(off + kDiagBias));
+    };
+    bool bad = false, many = np < 0 && blk == 0;  // (one workgroup reports what all of them find)
+    for (int64_t base = blk * NT; base <= n; base += nblk * NT) {
+        const int64_t i = base + tid;
+        const int32_t r = i <= n ? rowptr[i] : 0, r1 = i < n ? rowptr[i + 1] : r;
+        if (i <= n) bad = bad || r < 0 || r > nnz || (i == 0 && r != 0) || (i == n && r != nnz) || r1 < r || r1 > nnz;
+        if (np < 0) continue;
+        const RowParts<HALVES> p(n, base < n ? base : n - 1, rowptr);
+#pragma unroll
+        for (int part = 0; part < p.N; ++part) {
+            const int64_t o = p.begin(part), o1 = p.end(part);
+            __syncthreads();  // the part before has been read
+            const bool staged = stage_entries<false>(colind, o, o1, nnz, sc);
+            __syncthreads();
+            if (i >= n || bad || !p.mine(part)) continue;
+            // (unordered row pointers may leave the staged range: those rows read colind)
+            const bool in = staged && r >= o && r1 <= o1;
+            auto column = [&](int32_t e) { return in ? sc[e - o] : colind[e]; };
+            int32_t e = r, c = e < r1 ? column(e) : 0;
+            for (int k = 0; k < np; ++k) {
+                if (e < r1 && c == i + pat[k]) {
+                    bad = bad || c < 0 || c >= n;
+                    ++e;
+                    c = e < r1 ? column(e) : 0;
+                }
+            }
+            if (e == r1) continue;
+            int64_t prev = -1;
+            for (e = r; e < r1; ++e) {
+                c = column(e);
+                bad = bad || c < 0 || c >= n;
+                many = many || c <= prev;
+                prev = c;
+                if (!bad && !many) many = !enter(c - i);
+            }
+        }
+    }
+    if (np < 0)
+        for (int64_t e = blk * NT + tid; e < nnz; e += 4 * nblk * NT) {
+            int32_t c[4];  // four loads in flight
+#pragma unroll
+            for (int u = 0; u < 4; ++u) c[u] = e + u * nblk * NT < nnz ? colind[e + u * nblk * NT] : 0;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) bad = bad || c[u] < 0 || c[u] >= n;
+        }
     if (bad) flags[0] = 1;
     if (many) flags[1] = 1;
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (tid == 0) {
         if (flags[0]) atomicOr(words, 1);
         if (flags[1]) atomicOr(words + 1, 1);
     }
-    if (threadIdx.x < kMaxDiags && tab[threadIdx.x] != 0u && !flags[1]) {
-        const unsigned key = tab[threadIdx.x];
-        unsigned* t = reinterpret_cast<unsigned*>(words + 2);
+    if (np < 0 || flags[1]) return;
+    unsigned* t = reinterpret_cast<unsigned*>(words + 2);
+    if (tid < kMaxDiags) known[tid] = __hip_atomic_load(t + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (tid < kMaxDiags && tab[tid] != 0u) {
+        const unsigned key = tab[tid];
         bool done = false;
+        for (int k = 0; k < kMaxDiags && !done; ++k) done = known[k] == key;
         for (int k = 0; k < kMaxDiags && !done; ++k) {
-            const unsigned have = __hip_atomic_load(t + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            done = have == key;
-            if (have == 0u) {
-                const unsigned was = atomicCAS(t + k, 0u, key);
-                done = was == 0u || was == key;
-            }
+            if (known[k] != 0u) continue;
+            const unsigned was = atomicCAS(t + k, 0u, key);
+            done = was == 0u || was == key;
         }
         if (!done) atomicOr(words + 1, 1);
     }
 }
 
+template <bool HALVES>
 __global__ void __launch_bounds__(NT) csr_check_kernel(int64_t n, int64_t nnz, const int32_t* __restrict__ rowptr,
-                                                       const int32_t* __restrict__ colind, int* words) {
-    csr_check_body(n, nnz, rowptr, colind, words, blockIdx.x, gridDim.x);
+                                                       const int32_t* __restrict__ colind, bool scan, int* words) {
+    csr_check_body<HALVES>(n, nnz, rowptr, colind, scan, words, blockIdx.x, gridDim.x);
 }
 
 // System blockIdx.y of the table (n, nnz, rowptr, colind); its words 32 ints apart.
-__global__ void __launch_bounds__(NT) csr_check_kernel_batched(const BatchSys* sys, int* words) {
+template <bool HALVES>
+__global__ void __launch_bounds__(NT) csr_check_kernel_batched(const BatchSys* sys, bool scan, int* words) {
     const BatchSys& d = sys[blockIdx.y];
-    if ((int64_t)blockIdx.x * NT > d.n) return;
-    csr_check_body(d.n, d.nnz, d.rowptr, d.colind, words + 32 * blockIdx.y, blockIdx.x, gridDim.x);
+    const int64_t blocks = d.n / NT + 1, nblk = blocks < gridDim.x ? blocks : gridDim.x;
+    if (blockIdx.x >= nblk) return;
+    csr_check_body<HALVES>(d.n, d.nnz, d.rowptr, d.colind, scan, words + 32 * blockIdx.y, blockIdx.x, nblk);
 }
 
 // out[k ld + row] = A(row, row + off[k]) (scaled by dinv[column]), 0 where the row has none;
 // one row per thread, its entries and the diagonals both in ascending column order.
-template <typename TV>
+template <bool HALVES, typename TV>
 __device__ __forceinline__ void fill_diagonals_body(int64_t n, int64_t nnz, const int32_t* __restrict__ rowptr,
                                                     const int32_t* __restrict__ colind,
                                                     const double* __restrict__ val, const double* __restrict__ dinv,
@@ -558,42 +715,45 @@ __device__ __forceinline__ void fill_diagonals_body(int64_t n, int64_t nnz, cons
                                                     int64_t blk) {
     __shared__ int32_t sc[STAGE];
     __shared__ double sv[STAGE];
-    const int64_t base = blk * NT, rend = base + NT < n ? base + NT : n;
-    const int64_t o = rowptr[base];
-    bool staged = stage_entries(colind, o, rowptr[rend], nnz, sc);
-    if (staged) staged = stage_entries(val, o, rowptr[rend], nnz, sv);
-    __syncthreads();
-    const int64_t row = base + threadIdx.x;
-    if (row >= n) return;
-    int32_t e = rowptr[row];
-    const int32_t e1 = rowptr[row + 1];
-    for (int k = 0; k < nd; ++k) {
-        double v = 0.0;
-        if (e < e1) {
-            const int32_t c = staged ? sc[e - o] : colind[e];
-            if (c == row + off[k]) {
-                v = staged ? sv[e - o] : val[e];
-                if (dinv) v *= dinv[c];
-                ++e;
+    const int64_t base = blk * NT, row = base + threadIdx.x;
+    const RowParts<HALVES> p(n, base, rowptr);
+    const int32_t r = row < n ? rowptr[row] : 0, e1 = row < n ? rowptr[row + 1] : 0;
+#pragma unroll
+    for (int part = 0; part < p.N; ++part) {
+        const int64_t o = p.begin(part), o1 = p.end(part);
+        if (part) __syncthreads();  // the part before has been read
+        const bool staged = stage_entries<true>(colind, o, o1, nnz, sc) && stage_entries<true>(val, o, o1, nnz, sv);
+        __syncthreads();
+        if (row >= n || !p.mine(part)) continue;
+        int32_t e = r;
+        for (int k = 0; k < nd; ++k) {
+            double v = 0.0;
+            if (e < e1) {
+                const int32_t c = staged ? sc[e - o] : colind[e];
+                if (c == row + off[k]) {
+                    v = staged ? sv[e - o] : val[e];
+                    if (dinv) v *= dinv[c];
+                    ++e;
+                }
             }
+            __builtin_nontemporal_store(static_cast<TV>(v), out + row + (int64_t)k * ld);
         }
-        __builtin_nontemporal_store(static_cast<TV>(v), out + row + (int64_t)k * ld);
     }
 }
 
-template <typename TV>
+template <bool HALVES, typename TV>
 __global__ void __launch_bounds__(NT) fill_diagonals_kernel(int64_t n, int64_t nnz, const int32_t* rowptr,
                                                             const int32_t* colind, const double* val,
                                                             const double* dinv, const DiaView d) {
-    fill_diagonals_body<TV>(n, nnz, rowptr, colind, val, dinv, static_cast<TV*>(const_cast<void*>(d.val)), d.ld, d.nd,
+    fill_diagonals_body<HALVES, TV>(n, nnz, rowptr, colind, val, dinv, static_cast<TV*>(const_cast<void*>(d.val)), d.ld, d.nd,
                             d.off, blockIdx.x);
 }
 
-template <typename TV>
+template <bool HALVES, typename TV>
 __global__ void __launch_bounds__(NT) fill_diagonals_kernel_batched(const BatchSys* sys) {
     const BatchSys& d = sys[blockIdx.y];
     if ((int64_t)blockIdx.x * NT >= d.n) return;
-    fill_diagonals_body<TV>(d.n, d.nnz, d.rowptr, d.colind, d.val, d.dinv, static_cast<TV*>(const_cast<void*>(d.dia)),
+    fill_diagonals_body<HALVES, TV>(d.n, d.nnz, d.rowptr, d.colind, d.val, d.dinv, static_cast<TV*>(const_cast<void*>(d.dia)),
                             d.ldd, d.nd, d.off, blockIdx.x);
 }
 
@@ -1174,10 +1334,13 @@ hipError_t launch_update(int64_t n, bool f32, const void* Q, int64_t ldq, int k,
     return hipGetLastError();
 }
 
-hipError_t launch_csr_check(int64_t n, int64_t nnz, const int32_t* rowptr, const int32_t* colind, int* words,
-                            hipStream_t st) {
-    const unsigned grid = (unsigned)std::min<int64_t>((n + 1 + NT - 1) / NT, 2048);
-    hipLaunchKernelGGL(csr_check_kernel, dim3(grid), dim3(NT), 0, st, n, nnz, rowptr, colind, words);
+bool long_rows(int64_t n, int64_t nnz) { return nnz > (STAGE / NT) * n; }
+
+hipError_t launch_csr_check(int64_t n, int64_t nnz, const int32_t* rowptr, const int32_t* colind, bool scan,
+                            int* words, hipStream_t st) {
+    const unsigned grid = (unsigned)std::min<int64_t>(n / NT + 1, 2048);
+    hipLaunchKernelGGL((long_rows(n, nnz) ? &csr_check_kernel<true> : &csr_check_kernel<false>), dim3(grid), dim3(NT), 0,
+                       st, n, nnz, rowptr, colind, scan, words);
     return hipGetLastError();
 }
 
@@ -1195,16 +1358,18 @@ hipError_t launch_fill_diagonals(int64_t n, int64_t nnz, const int32_t* rowptr, 
                                  const double* dinv, bool f32, const DiaView& d, hipStream_t st) {
     if (!d.val || d.nd < 1 || d.nd > kMaxDiags || d.ld < n) return hipErrorInvalidValue;
     const dim3 g((unsigned)((n + NT - 1) / NT));
-    if (f32)
-        hipLaunchKernelGGL((fill_diagonals_kernel<float>), g, dim3(NT), 0, st, n, nnz, rowptr, colind, val, dinv, d);
-    else
-        hipLaunchKernelGGL((fill_diagonals_kernel<double>), g, dim3(NT), 0, st, n, nnz, rowptr, colind, val, dinv, d);
+    const bool halves = long_rows(n, nnz);
+    hipLaunchKernelGGL((f32 ? (halves ? &fill_diagonals_kernel<true, float> : &fill_diagonals_kernel<false, float>)
+                            : (halves ? &fill_diagonals_kernel<true, double> : &fill_diagonals_kernel<false, double>)),
+                       g, dim3(NT), 0, st, n, nnz, rowptr, colind, val, dinv, d);
     return hipGetLastError();
 }
 
-hipError_t launch_csr_check_batched(int nsys, int64_t max_n, const BatchSys* sys, int* words, hipStream_t st) {
-    const dim3 g((unsigned)std::min<int64_t>((max_n + 1 + NT - 1) / NT, 128), (unsigned)nsys);
-    hipLaunchKernelGGL(csr_check_kernel_batched, g, dim3(NT), 0, st, sys, words);
+hipError_t launch_csr_check_batched(int nsys, int64_t max_n, const BatchSys* sys, bool scan, bool halves,
+                                    int* words, hipStream_t st) {
+    const dim3 g((unsigned)std::min<int64_t>(max_n / NT + 1, 128), (unsigned)nsys);
+    hipLaunchKernelGGL((halves ? &csr_check_kernel_batched<true> : &csr_check_kernel_batched<false>), g, dim3(NT), 0, st,
+                       sys, scan, words);
     return hipGetLastError();
 }
 
@@ -1215,12 +1380,13 @@ hipError_t launch_jacobi_setup_batched(int nsys, int64_t max_n, const BatchSys* 
     return hipGetLastError();
 }
 
-hipError_t launch_fill_diagonals_batched(int nsys, int64_t max_n, const BatchSys* sys, bool f32, hipStream_t st) {
+hipError_t launch_fill_diagonals_batched(int nsys, int64_t max_n, const BatchSys* sys, bool f32, bool halves,
+                                        hipStream_t st) {
     const dim3 g((unsigned)((max_n + NT - 1) / NT), (unsigned)nsys);
-    if (f32)
-        hipLaunchKernelGGL((fill_diagonals_kernel_batched<float>), g, dim3(NT), 0, st, sys);
-    else
-        hipLaunchKernelGGL((fill_diagonals_kernel_batched<double>), g, dim3(NT), 0, st, sys);
+    hipLaunchKernelGGL(
+        (f32 ? (halves ? &fill_diagonals_kernel_batched<true, float> : &fill_diagonals_kernel_batched<false, float>)
+             : (halves ? &fill_diagonals_kernel_batched<true, double> : &fill_diagonals_kernel_batched<false, double>)),
+        g, dim3(NT), 0, st, sys);
     return hipGetLastError();
 }
 

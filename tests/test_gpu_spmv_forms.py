@@ -180,3 +180,91 @@ def test_coupled_fields_are_no_slower_by_diagonals(B, ctx, precision):
     ty = "f32" if precision == "mixed" else "f64"
     assert list(dia) == [f"spmv dia {ty}"] and list(csr) == [f"spmv {ty}"]
     assert dia[f"spmv dia {ty}"] <= csr[f"spmv {ty}"]
+
+
+def with_values(n, offsets, seed, extra=()):
+    """A matrix on the given diagonals with a varying dominant main diagonal, and single entries
+    (row, column, value) besides."""
+    import scipy.sparse as sp
+    r = np.random.default_rng([22, seed])
+    S = sp.lil_matrix((n, n))
+    for o in offsets:
+        S.setdiag(r.uniform(-1.0, 1.0, n) if o else len(offsets) * r.uniform(0.7, 1.4, n), o)
+    for i, j, v in extra:
+        S[i, j] = v
+    S = S.tocsr()
+    S.sort_indices()
+    return wl.CSR(n, S.indptr.astype(np.int64), S.indices, S.data)
+
+
+BAND5, BAND13 = [-30, -1, 0, 1, 30], list(range(-6, 7))
+# name: (matrix, by diagonals)
+STRUCTURES = {
+    "one row": (lambda: with_values(1, [0], 1), True),
+    "fewer rows than samples": (lambda: with_values(40, [-1, 0, 1], 2), True),
+    "a whole row block": (lambda: with_values(256, BAND5, 3), True),
+    "one row more": (lambda: with_values(257, BAND5, 4), True),
+    "rows in two parts": (lambda: with_values(1500, BAND13, 5), True),
+    "a diagonal of one entry": (lambda: with_values(3000, BAND5, 6, [(1777, 200, 0.5)]), True),
+    "a 17th diagonal of one entry": (
+        lambda: with_values(3000, list(range(-8, 8)), 7, [(1777, 200, 0.5)]), False),
+    "a row of 17 entries": (
+        lambda: with_values(3000, BAND5, 8, [(1501, 1000 + 7 * i, 0.05) for i in range(12)]), False),
+    "random columns": (
+        lambda: with_values(900, [0], 9, [(i, (i * 37 + 11 * j * j) % 900, 0.1) for i in range(900) for j in range(1, 5)]),
+        False),
+}
+
+
+@pytest.mark.parametrize("name", STRUCTURES)
+@pytest.mark.parametrize("precond", [0, 1])
+def test_structure_scan(B, ctx, name, precond):
+    """The scan's shortcuts (sampled rows, rows along the known diagonals) find every diagonal."""
+    make, by_diagonals = STRUCTURES[name]
+    A = make()
+    b = wl.rhs_uniform(A.n, 3)
+    kw = dict(s=1 if A.n == 1 else 4, m=1 if A.n == 1 else 12, precond=precond, tol=1e-9,
+              maxiter=4 if A.n == 1 else 600, sketch=B.make_sketch("sparse_sign", 64, 8, 1))
+    names = list(spmv_kernels(ctx, lambda: ctx.gmres(A, b, **kw), 1))
+    assert names == ["spmv dia f64" if by_diagonals else "spmv f64"]
+    x, info, st = ctx.gmres(A, b, **kw)
+    if A.n > 1:  # a Krylov space of one vector has no second one to orthogonalise
+        assert st == B.SKO_OK, (st, info)
+        assert np.linalg.norm(b - A.to_scipy() @ x.cpu().numpy()) / np.linalg.norm(b) <= 1e-9
+
+
+@pytest.mark.parametrize("name", STRUCTURES)
+def test_structure_check_rejects(B, ctx, name):
+    """One wrong column or row pointer anywhere, in each route of the check."""
+    A = STRUCTURES[name][0]()
+    b = torch.from_numpy(wl.rhs_uniform(A.n, 3)).cuda()
+    kw = dict(s=1, m=1, sketch=B.make_sketch("sparse_sign", 64, 8, 1))
+
+    def status(rowptr, colind, maxiter):
+        Ad, keep = B.csr_to_device(A)
+        rp, ci = torch.from_numpy(rowptr).cuda(), torch.from_numpy(colind).cuda()
+        Ad.rowptr, Ad.colind = rp.data_ptr(), ci.data_ptr()
+        return ctx.gmres((Ad, (keep, rp, ci)), b, maxiter=maxiter, **kw)[2]
+
+    for maxiter in (1, 50):  # without and with the scan
+        for at in sorted({0, A.nnz // 3, A.nnz // 2, A.nnz - 1}):
+            for col in (-1, A.n, 2 ** 31 - 1, -2 ** 31):
+                ci = A.colind.copy()
+                ci[at] = col
+                assert status(A.rowptr, ci, maxiter) == B.SKO_EINVAL, (maxiter, at, col)
+        for at in sorted({0, A.n // 2, A.n}):
+            for d in (-1, 1, A.nnz + 1, -2 ** 30):
+                rp = A.rowptr.copy()
+                rp[at] += d
+                if rp[0] == 0 and rp[-1] == A.nnz and np.all(np.diff(rp.astype(np.int64)) >= 0):
+                    continue  # still a valid structure
+                assert status(rp, A.colind, maxiter) == B.SKO_EINVAL, (maxiter, at, d)
+
+
+def test_short_solves_keep_csr(B, ctx):
+    """A solve of fewer vectors than the diagonals' set-up pays for runs as it is."""
+    A = wl.laplacian_2d(30)
+    b = wl.rhs_uniform(A.n, 3)
+    sk = B.make_sketch("sparse_sign", 64, 8, 1)
+    for s, maxiter, name in ((3, 3, "spmv f64"), (3, 4, "spmv dia f64"), (4, 1, "spmv dia f64"), (1, 3, "spmv f64")):
+        assert list(spmv_kernels(ctx, lambda: ctx.gmres(A, b, s=s, m=4 * s, tol=1e-14, maxiter=maxiter, sketch=sk), 1)) == [name]
