@@ -726,9 +726,14 @@ sko_status orth_blocks_impl(sko_ctx c, int64_t n, int32_t nb, int32_t w, const v
 
     const bool f32 = o->precision == SKO_MIXED_F32;
     const int k = rand ? sketch_plan(o->sketch).rows : w;
-    const bool ahead = one_stage_looks_ahead(n, nb, w, f32, o->intra, V, ldv, Q, ldq);
+    bool ahead = one_stage_looks_ahead(n, nb, w, f32, o->intra, V, ldv, Q, ldq);
     OneStageLayout L = layout_one_stage(c, n, w, N - w, k, N, ahead);
     sko_status s = ensure_workspace(c, L.total);
+    if (s == SKO_ENOMEM && ahead) {  // block by block takes half the partial sums
+        ahead = false;
+        L = layout_one_stage(c, n, w, N - w, k, N);
+        s = ensure_workspace(c, L.total);
+    }
     if (s) return s;
     Arena ar(c);
     Engine e(c, n, w, f32, o->sketch);

@@ -137,10 +137,13 @@ int main(int argc, char** argv) {
             g_from = 1 << 16, g_refuse = 1000;
             report("refused_status", sko_orth_blocks(c, n, nb, w, V, n, Q, n, R.data(), N, &o, &col));
             g_refuse = 0;
+        } else if (mode == "blocks") {
+            g_from = 1 << 16, g_refuse = 1;
         } else {
             return 2;
         }
         report("status", sko_orth_blocks(c, n, nb, w, V, n, Q, n, R.data(), N, &o, &col));
+        if (mode == "blocks") report("refused", 1 - g_refuse);
         sko_ctx c2 = nullptr;
         if (sko_create(0, nullptr, &c2) != SKO_OK) return 2;
         g_refuse = 0;

@@ -45,3 +45,8 @@ def test_solve_without_room_for_the_diagonals_runs_on_csr(program, mode):
 def test_refused_call_leaves_the_next_one_alone(program):
     got = run(program, "every")
     assert got == dict(refused_status=SKO_ENOMEM, status=SKO_OK, status_plain=SKO_OK, same_r=1, left_error=0)
+
+
+def test_blocks_without_room_to_look_ahead_go_one_by_one(program):
+    got = run(program, "blocks")
+    assert got == dict(status=SKO_OK, refused=1, status_plain=SKO_OK, same_r=1, left_error=0)
