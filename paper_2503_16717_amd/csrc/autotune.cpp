@@ -98,12 +98,13 @@ sko_status autotune_orth_impl(sko_ctx c, int64_t n, int32_t nb, int32_t w, const
     }
     if ((int64_t)pmax * w > kMaxUpdCoef) return SKO_EUNSUPPORTED;
 
-    // ---- scratch: Y, X, Y2, X2 (n x w), Q (n x pmax), coefficients, identity factors, partials
+    // ---- scratch: Y, X (n x w), Q (n x pmax), coefficients, identity factors, partials.  The
+    // two-block passes run in place on Y and X, as the look-ahead schedule runs them on V and Q.
     const size_t eb = f32 ? 4 : 8;
     const int64_t rpl_max = std::max(pass_rows_per_launch(w, RED_PROJ), pass_rows_per_launch(w, red_sk));
     const int64_t part_stride = ((std::min<int64_t>(rows_max, rpl_max) * 2 * w + 31) / 32) * 32;
     const size_t tall = eb * (size_t)n;
-    const size_t bytes = tall * (4 * (size_t)w + pmax) + sizeof(double) * ((size_t)pmax * 2 * w + 2 * (size_t)w * w) +
+    const size_t bytes = tall * (2 * (size_t)w + pmax) + sizeof(double) * ((size_t)pmax * 2 * w + 2 * (size_t)w * w) +
                          sizeof(double) * (size_t)part_stride * 8 * cus + 1024;
     char* buf = nullptr;
     if (hipMalloc(&buf, bytes) != hipSuccess) return out_of_memory();
@@ -113,9 +114,7 @@ sko_status autotune_orth_impl(sko_ctx c, int64_t n, int32_t nb, int32_t w, const
     } guard{buf};
     char* Y = buf;
     char* X = Y + tall * w;
-    char* Y2 = X + tall * w;
-    char* X2 = Y2 + tall * w;
-    char* Q = X2 + tall * w;
+    char* Q = X + tall * w;
     double* Cu = reinterpret_cast<double*>(Q + tall * pmax);
     double* R1 = Cu + (size_t)pmax * 2 * w;
     double* partials = R1 + 2 * (size_t)w * w;
@@ -149,11 +148,13 @@ sko_status autotune_orth_impl(sko_ctx c, int64_t n, int32_t nb, int32_t w, const
         a.Cu = Cu;
         a.R1 = R1;
         a.R2 = R1 + (size_t)w * w;
-        a.X = X;
+        const int kind = u.key.pair;
+        const bool two = kind != PAIR_NONE && kind != SOLO_PROJ && kind != SOLO_UPD;
+        a.X = two ? Y : X;
         a.ldx = n;
-        a.Y2 = Y2;
+        a.Y2 = X;
         a.ldy2 = n;
-        a.X2 = u.key.pair == PAIR_UPD || u.key.pair == PAIR_LEAD ? X2 : nullptr;
+        a.X2 = kind == PAIR_UPD || kind == PAIR_LEAD ? X : nullptr;
         a.ldx2 = n;
         if (u.key.pair == PAIR_LEAD) {  // its coefficients are those of x, not of Q
             a.pu = 0;

@@ -17,12 +17,14 @@
 
 static size_t g_from = SIZE_MAX;  // requests of this size and above are refused ...
 static int g_refuse = 0;          // ... as many times as this
+static size_t g_largest = 0;
 
 extern "C" hipError_t hipMalloc(void** p, size_t bytes) {
     if (bytes >= g_from && g_refuse > 0) {
         --g_refuse;
         return hipExtMallocWithFlags(p, size_t(1) << 60, hipDeviceMallocDefault);
     }
+    if (bytes > g_largest) g_largest = bytes;
     return hipExtMallocWithFlags(p, bytes, hipDeviceMallocDefault);
 }
 
@@ -137,6 +139,12 @@ int main(int argc, char** argv) {
             g_from = 1 << 16, g_refuse = 1000;
             report("refused_status", sko_orth_blocks(c, n, nb, w, V, n, Q, n, R.data(), N, &o, &col));
             g_refuse = 0;
+        } else if (mode == "autotune") {
+            const int64_t rows = 1 << 19;
+            report("tune_one_stage", sko_autotune_orth(c, rows, nb, w, &o));
+            report("doubles_per_row", (long long)(g_largest / (8 * (size_t)rows)));
+            sko_destroy(c);
+            return 0;
         } else if (mode == "blocks") {
             g_from = 1 << 16, g_refuse = 1;
         } else {

@@ -50,3 +50,9 @@ def test_refused_call_leaves_the_next_one_alone(program):
 def test_blocks_without_room_to_look_ahead_go_one_by_one(program):
     got = run(program, "blocks")
     assert got == dict(status=SKO_OK, refused=1, status_plain=SKO_OK, same_r=1, left_error=0)
+
+
+def test_autotuner_scratch(program):
+    """Scratch of 2 w + p_max = 30 columns (the rest: partial sums of 8 workgroups per compute unit)."""
+    got = run(program, "autotune")
+    assert got["tune_one_stage"] == SKO_OK and 30 <= got["doubles_per_row"] <= 33
