@@ -285,9 +285,10 @@ sko_status sko_gmres_batched(sko_ctx ctx, int32_t nsys, const sko_csr* A,
  * Launch-shape autotuning (the row-strip passes of the block orthogonalisation).
  * How many workgroups per compute unit stream a pass fastest depends on the pass variant
  * (its registers, LDS and the number of column streams it reads).  This call times every
- * pass variant that sko_orth_blocks(ctx, n, nb, w, ..., opts) launches, each at its median
- * operand width, on scratch blocks the library allocates (n x (2w + p_max) elements plus
- * small buffers, freed before returning), for 2..8 workgroups per compute unit, and keeps
+ * pass variant that sko_orth_blocks(ctx, n, nb, w, ..., opts) launches, and those of the
+ * same block steps taken one at a time (sko_orth_block; the panels of sko_gmres), each at its
+ * median operand width, on scratch blocks the library allocates (n x (2w + p_max) elements
+ * plus small buffers, freed before returning), for 2..8 workgroups per compute unit, and keeps
  * the fastest count in ctx for that variant and row-count class (floor(log2(n / 256))).
  * Later launches of those variants on this context, by any entry point, use the choice;
  * all other launches keep the default (as many workgroups as are resident at once).  The

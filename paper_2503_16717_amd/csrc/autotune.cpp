@@ -55,6 +55,19 @@ void one_stage_uses(int W, bool f32, int red_first, int rows_first, int p, bool 
     if (!two) out.push_back({{W, f32, RED_NONE, false, 1, true}, 0, 0});
 }
 
+// The row-strip passes of one panel of the two-stage scheme (Fig. 5) as the GMRES solver, which
+// has one panel at a time, runs them: projection on the previous big panels, update + sketch,
+// forward substitution against the panel's earlier blocks.  Of whole matrices only the sketch is
+// such a pass.
+void two_stage_uses(int w, bool f32, int red_sk, int k, int p_old, int loc, std::vector<Use>& out) {
+    if (p_old > 0) {
+        out.push_back({{w, f32, RED_PROJ, false, 0, false}, 0, p_old});
+        out.push_back({{w, f32, red_sk, true, 0, true}, p_old, k});
+    }
+    out.push_back({{w, f32, red_sk, false, 0, false}, 0, k});
+    out.push_back({{w, f32, RED_NONE, loc > 0, 1, true}, loc, 0});
+}
+
 }  // namespace
 
 sko_status autotune_orth_impl(sko_ctx c, int64_t n, int32_t nb, int32_t w, const sko_orth_opts* o) {
@@ -79,11 +92,16 @@ sko_status autotune_orth_impl(sko_ctx c, int64_t n, int32_t nb, int32_t w, const
         const int red_first = rand ? red_sk : RED_GRAM;
         const int rows_first = rand ? sp.rows : w;
         const bool ahead = one_stage_shape_looks_ahead(nb, w, o->intra);
-        for (int j = 0; j < nb; ++j)
-            one_stage_uses(w, f32, red_first, rows_first, j * w, ahead, j + 1 < nb, uses);
+        for (int j = 0; j < nb; ++j) {
+            if (ahead) one_stage_uses(w, f32, red_first, rows_first, j * w, true, j + 1 < nb, uses);
+            one_stage_uses(w, f32, red_first, rows_first, j * w, false, false, uses);  // block by block
+        }
     } else {
-        // the two-stage scheme's row-strip passes are the sketches of its panels
-        uses.push_back({{w, f32, red_sk, false, 0, false}, 0, sp.rows});
+        const int ppb = std::max(1, o->panels_per_big);
+        for (int j = 0; j < nb; ++j) {
+            const int big = j / ppb, i = j % ppb;
+            two_stage_uses(w, f32, red_sk, sp.rows, big * ppb * w, i * w, uses);
+        }
     }
     std::map<const void*, std::vector<Use>> groups;
     int pmax = 1, rows_max = w;

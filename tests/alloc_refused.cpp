@@ -13,7 +13,8 @@
 #include <string>
 #include <vector>
 
-#include "sko.h"
+#include "context.h"
+#include "sko_internal.h"
 
 static size_t g_from = SIZE_MAX;  // requests of this size and above are refused ...
 static int g_refuse = 0;          // ... as many times as this
@@ -140,9 +141,37 @@ int main(int argc, char** argv) {
             report("refused_status", sko_orth_blocks(c, n, nb, w, V, n, Q, n, R.data(), N, &o, &col));
             g_refuse = 0;
         } else if (mode == "autotune") {
+            // single block steps' and panels' passes, tuned or not (projections of 18 columns: 4 tiles)
             const int64_t rows = 1 << 19;
+            const int bucket = 11, W = (int)w;
+            auto tuned = [&](sko::PassKey k) {
+                k.tiles = 4;
+                return (long long)c->grid_wpc.count({sko::pass_kernel_id(k), bucket});
+            };
+            auto solo = [&](int red, int kind) {
+                sko::PassKey k{W, false, red, false, 0, false};
+                k.pair = kind;
+                return k;
+            };
             report("tune_one_stage", sko_autotune_orth(c, rows, nb, w, &o));
             report("doubles_per_row", (long long)(g_largest / (8 * (size_t)rows)));
+            report("block_steps", tuned({W, false, sko::RED_PROJ, false, 0, false}) +
+                                      tuned({W, false, sko::RED_SKETCH_SPARSE, true, 0, true}) +
+                                      tuned({W, false, sko::RED_GRAM, false, 1, false}) +
+                                      tuned(solo(sko::RED_PROJ, sko::SOLO_PROJ)) +
+                                      tuned(solo(sko::RED_GRAM, sko::SOLO_UPD)) +
+                                      tuned({W, false, sko::RED_NONE, false, 1, true}));
+            report("look_ahead", tuned(solo(sko::RED_PROJ, sko::PAIR_PROJ)) + tuned(solo(sko::RED_GRAM, sko::PAIR_UPD)) +
+                                     tuned(solo(sko::RED_SKETCH_SPARSE, sko::PAIR_LEAD)));
+            c->grid_wpc.clear();
+            o.two_stage = 1;
+            o.panels_per_big = 2;
+            report("tune_two_stage", sko_autotune_orth(c, rows, nb, w, &o));
+            report("panels", tuned({W, false, sko::RED_PROJ, false, 0, false}) +
+                                 tuned({W, false, sko::RED_SKETCH_SPARSE, true, 0, true}) +
+                                 tuned({W, false, sko::RED_SKETCH_SPARSE, false, 0, false}) +
+                                 tuned({W, false, sko::RED_NONE, true, 1, true}) +
+                                 tuned({W, false, sko::RED_NONE, false, 1, true}));
             sko_destroy(c);
             return 0;
         } else if (mode == "blocks") {

@@ -21,7 +21,7 @@ def program(tmp_path_factory):
         pytest.skip("no GPU")
     exe = str(tmp_path_factory.mktemp("alloc") / "alloc_refused")
     subprocess.run(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", f"-I{ROCM}/include", f"-I{ROOT}/include",
-                    os.path.join(HERE, "alloc_refused.cpp"), "-o", exe, os.path.join(PKG, "libsko.so"),
+                    f"-I{PKG}/csrc", os.path.join(HERE, "alloc_refused.cpp"), "-o", exe, os.path.join(PKG, "libsko.so"),
                     f"-L{ROCM}/lib", "-lamdhip64", f"-Wl,-rpath,{PKG}:{ROCM}/lib"], check=True)
     return exe
 
@@ -56,3 +56,10 @@ def test_autotuner_scratch(program):
     """Scratch of 2 w + p_max = 30 columns (the rest: partial sums of 8 workgroups per compute unit)."""
     got = run(program, "autotune")
     assert got["tune_one_stage"] == SKO_OK and 30 <= got["doubles_per_row"] <= 33
+
+
+def test_autotuner_kinds(program):
+    """The look-ahead's passes, and those of the same shapes taken one block or panel at a time."""
+    got = run(program, "autotune")
+    del got["doubles_per_row"]
+    assert got == dict(tune_one_stage=SKO_OK, block_steps=6, look_ahead=3, tune_two_stage=SKO_OK, panels=5)
