@@ -294,12 +294,18 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
     // Sparse sketch on row masks (SPM): lane l accumulates sketch row g = red_row0 + l (and
     // g + 64), which is slot j of hash byte t; byte b selects slot floor((b >> 1) B / 128) of its
     // B = k / zeta and carries the sign in bit 0.  Per 64 staged rows each lane sets the bits of its
-    // own row's sketch rows in a word (and again those with a minus sign), and the wave transposes
-    // the 64 x 64 bits: lane l then has the mask of the rows that sketch row l takes.  It adds
-    // them into its W sums in ascending row order.  Only the rows with a nonzero in the lane's
-    // sketch row are touched: zeta W products per row instead of k W on MFMA blocks.  (128 sketch
-    // rows, 11 FP64 columns, 7 million rows: 217 us; 229 us with the masks formed from ballots of
-    // every slot bit, about 30 instructions per byte and 64 rows.)
+    // own row's sketch rows in a word, and the wave transposes the 64 x 64 bits: lane l then has the
+    // mask of the rows that sketch row l takes.  (The rows' signs in a byte are one ballot, which the
+    // lanes of the byte's sketch rows keep.)  It adds those rows into its W sums in ascending row
+    // order.  Only the rows with a nonzero in the lane's sketch row are touched: zeta W products per
+    // row instead of k W on MFMA blocks.
+    // The masks take a third of the instructions where few rows fall to a lane, and uniform values
+    // held for them across the sweep overflow the scalar registers (spills to lanes of vector
+    // registers).  us with masks from ballots of every slot bit | masks and signs transposed, up to 185
+    // spills | now, none in the plain sketches: 11 FP64 columns, 128 rows, zeta = 8, 7 077 889 rows
+    // 209 | 209 | 194; 6 FP32 columns, 64 rows, 2^22 rows 87.8 | 93.4 | 79.5; 8 FP32 columns 104 | 119 |
+    // 96; 6 FP64 columns 68.4 | 67.1 | 65.2.  Where ballots of a single bit did (k = 2 zeta, zeta = 1) FP64
+    // sketches take 1 to 5 % more than with them.
     double sacc[SPM ? SPR : 1][SPM ? W : 1];
 #pragma unroll
     for (int q = 0; q < (SPM ? SPR : 1); ++q)
@@ -533,39 +539,65 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
             if constexpr (SPM) {
                 // ---------------- phase B, sparse-sign sketch on row masks ----------------
                 constexpr int WROWS = STRIP / C::NWAVE;  // rows this wave staged (64 per thread row)
-                const unsigned B = (unsigned)(a.sk_k / a.sk_zeta);
+                const int B0 = a.sk_k / a.sk_zeta;
+                // masks of the wave's RPT groups of 64 rows, formed side by side (their chains of
+                // lane exchanges overlap)
+                unsigned ml[RPT][SPR], mh[RPT][SPR], sl[RPT][SPR], sh[RPT][SPR];
+                uint64_t h[RPT];
+#pragma unroll
+                for (int u = 0; u < RPT; ++u) h[u] = hs[wave * WROWS + u * 64 + lane];
+                // uniform operands derived again here: held for the sweep, the bytes' offsets and
+                // conditions overflow the scalar registers
+                const int B = per_strip(B0), zeta = per_strip(a.sk_zeta);
+#pragma unroll
+                for (int q = 0; q < SPR; ++q) {
+#pragma unroll
+                    for (int u = 0; u < RPT; ++u) ml[u][q] = mh[u][q] = sl[u][q] = sh[u][q] = 0u;
+                    int o = per_strip(-a.red_row0) - 64 * q;  // the byte's first sketch row among the lanes'
+#pragma unroll
+                    for (int t = 0; t < 8; ++t) {
+                        if (t < zeta && o < 64 && o + B > 0) {
+                            const bool at = lane >= o;
+                            unsigned bit[RPT];
+                            int pos[RPT];
+#pragma unroll
+                            for (int u = 0; u < RPT; ++u) {
+                                const unsigned b8 = (unsigned)(h[u] >> (8 * t)) & 0xffu;
+                                pos[u] = ((int)__umul24(b8 >> 1, (unsigned)B) + o * 128) >> 7;  // B <= 128
+                                bit[u] = 1u << (pos[u] & 31);
+                                const uint64_t sg = __ballot(b8 & 1u);
+                                sl[u][q] = at ? (unsigned)sg : sl[u][q];
+                                sh[u][q] = at ? (unsigned)(sg >> 32) : sh[u][q];
+                            }
+                            if ((o & 31) + B <= 32) {  // all of the byte's rows in one half
+#pragma unroll
+                                for (int u = 0; u < RPT; ++u) {
+                                    if (o & 32)
+                                        mh[u][q] |= bit[u];
+                                    else
+                                        ml[u][q] |= bit[u];
+                                }
+                            } else {
+#pragma unroll
+                                for (int u = 0; u < RPT; ++u) {
+                                    ml[u][q] |= (unsigned)pos[u] < 32u ? bit[u] : 0u;
+                                    mh[u][q] |= (unsigned)(pos[u] - 32) < 32u ? bit[u] : 0u;
+                                }
+                            }
+                        }
+                        o += B;
+                    }
+#pragma unroll
+                    for (int u = 0; u < RPT; ++u) bt.run(ml[u][q], mh[u][q]);
+                }
 #pragma unroll
                 for (int u = 0; u < RPT; ++u) {
                     const int rb = wave * WROWS + u * 64;  // strip-local row of mask bit 0
-                    const uint64_t h = hs[rb + lane];
                     const uint64_t vm = __ballot(base + rb + lane < n);
-                    unsigned ml[SPR], mh[SPR], sl[SPR], sh[SPR];
 #pragma unroll
                     for (int q = 0; q < SPR; ++q) {
-                        ml[q] = mh[q] = sl[q] = sh[q] = 0u;
-#pragma unroll
-                        for (int t = 0; t < 8; ++t) {
-                            // the byte's first sketch row, counted from the lanes' first
-                            const int o = t * (int)B - a.red_row0 - 64 * q;
-                            if (t < a.sk_zeta && o < 64 && o + (int)B > 0) {
-                                const unsigned b8 = (unsigned)(h >> (8 * t)) & 0xffu;
-                                const int pos = o + (int)(__umul24(b8 >> 1, B) >> 7);  // B <= 128
-                                uint64_t bit = 1ull << (pos & 63);
-                                if (o < 0 || o + (int)B > 64) bit = (unsigned)pos < 64u ? bit : 0ull;
-                                const unsigned minus = 0u - (b8 & 1u);
-                                ml[q] |= (unsigned)bit;
-                                mh[q] |= (unsigned)(bit >> 32);
-                                sl[q] |= (unsigned)bit & minus;
-                                sh[q] |= (unsigned)(bit >> 32) & minus;
-                            }
-                        }
-                        bt.run(ml[q], mh[q]);
-                        bt.run(sl[q], sh[q]);
-                    }
-#pragma unroll
-                    for (int q = 0; q < SPR; ++q) {
-                        ml[q] &= (unsigned)vm;
-                        mh[q] &= (unsigned)(vm >> 32);
+                        ml[u][q] &= (unsigned)vm;
+                        mh[u][q] &= (unsigned)(vm >> 32);
                     }
                     // one sketch row per lane: each mask in two 32-row halves (the lowest set bit,
                     // its clearing and the sign are single 32-bit operations); two rows per lane:
@@ -579,11 +611,11 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
                             using MW = typename std::conditional<NH == 2, unsigned, uint64_t>::type;
                             MW msk, sgm;
                             if constexpr (NH == 2) {
-                                msk = hf ? mh[q] : ml[q];
-                                sgm = hf ? sh[q] : sl[q];
+                                msk = hf ? mh[u][q] : ml[u][q];
+                                sgm = hf ? sh[u][q] : sl[u][q];
                             } else {
-                                msk = ((uint64_t)mh[q] << 32) | ml[q];
-                                sgm = ((uint64_t)sh[q] << 32) | sl[q];
+                                msk = ((uint64_t)mh[u][q] << 32) | ml[u][q];
+                                sgm = ((uint64_t)sh[u][q] << 32) | sl[u][q];
                             }
                             const int rh = rb + 32 * hf;
                             while (msk) {

@@ -160,3 +160,35 @@ def test_invalid_arguments_rejected(B, ctx):
     assert ctx.sko_sketch_apply(n, w, X.data_ptr(), n - 1, B.SKO_F64, good, Y, 64) == B.SKO_EINVAL
     with pytest.raises(TypeError):
         ctx.sketch_apply(X.float(), good)                                 # dtype checked
+
+
+# B = k / zeta rows per hash byte: bytes inside a 32-row half of the lanes' 64 sketch rows (B = 4, 8), across
+# the halves (3, 11, 24, 25), across the rows of one launch (200 rows: two), as wide as all of them (127, 128)
+@pytest.mark.parametrize("k,zeta", [(15, 5), (33, 3), (24, 6), (96, 4), (100, 4), (200, 8), (127, 1), (256, 2), (128, 1)])
+@pytest.mark.parametrize("precision", ["f64", "mixed"])
+def test_bytes_across_lane_halves_bit_exact(B, ctx, k, zeta, precision):
+    n, seed = 3003, 23
+    rng = np.random.default_rng(k + zeta)
+    rows = [0, 63, 64, 511, 512, n - 1] + list(rng.integers(0, n, 6))
+    vals = [float(v) for v in rng.integers(1, 1 << 20, len(rows))]
+    dt = torch.float64 if precision == "f64" else torch.float32
+    Y = ctx.sketch_apply(_one_hot(n, rows, vals, dt), B.make_sketch("sparse_sign", k, zeta, seed), precision)
+    assert np.array_equal(Y, _oracle_rows(rows, vals, k, zeta, seed))
+
+
+def test_float_sketch_keeps_up_with_double(B, ctx):
+    """FP32 storage halves the bytes of a sketch and adds conversions; it may take longer, but no more
+    than 1.4 times as long (8 columns, 64 rows: 1.3; 1.5 with the mask operands in spilled registers)."""
+    n, w, sk = 1 << 22, 8, B.make_sketch("sparse_sign", 64, 8, 3)
+    best = {}
+    for precision, dt in (("f64", torch.float64), ("mixed", torch.float32)):
+        X = torch.randn((w, n), dtype=dt, device="cuda").t()
+        times = []
+        for _ in range(9):
+            ctx.sko_profile_enable(True)
+            ctx.sketch_apply(X, sk, precision)
+            times += [s["total_ms"] / s["launches"] for s in ctx.sko_profile_read() if s["name"].startswith("pass")]
+            ctx.sko_profile_enable(False)
+        best[precision] = min(times)
+    print(best, flush=True)
+    assert best["mixed"] <= 1.4 * best["f64"]
