@@ -246,8 +246,11 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
     // their diagonals' reciprocals: in registers, or for wide blocks in LDS, read again per
     // strip (two solves of 11 columns would hold 44 registers of them for the whole sweep:
     // 144 against 101 VGPRs, 3 against 4 waves, for the FP32 solve + projection on 64 columns,
-    // 0.88 against 0.79 ms at 2^24 rows)
-    constexpr bool RINV_LDS = NTRSM > 0 && W >= 9;
+    // 0.88 against 0.79 ms at 2^24 rows; one solve + Gram of 13 FP32 columns 207 against 178 us at 2^23
+    // rows).  One solve behind an update of 10 or more columns keeps them in registers: there the LDS
+    // form's higher occupancy does not pay (solve into the FP32 basis behind 55 columns, 192^3 rows: 10
+    // columns 322 us in LDS, 311 in registers; 11: 357, 345; 12: 365, 346; 16: 467, 447; but 9: 299, 306).
+    constexpr bool RINV_LDS = NTRSM > 0 && W >= 9 && !(UPD && W >= 10);
     __shared__ double srinv[RINV_LDS ? NTRSM * W : 1];
     double rinv[NTRSM > 0 && !RINV_LDS ? NTRSM * W : 1];
     if constexpr (RINV_LDS) {
