@@ -855,21 +855,8 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
     }
 }
 
-// Waves per SIMD the register allocation must leave room for (1: no demand).  Float-storage
-// projections and plain sketches of up to 12 columns sit a few registers above a limit when
-// left alone, and the lost wave costs up to 20 % (11 columns on 128 rows of Q with two solves,
-// n = 2^24: 2.46 ms with 184 VGPRs and two waves, 2.00 ms now).
-template <int W, typename T, int RED, bool UPD, int NTRSM, int MTX>
-constexpr int min_waves() {
-    constexpr int MT = MTX > 0 ? MTX : Cfg<W, RED>::MT;
-    if (sizeof(T) != 4 || W > 12) return 1;
-    if (RED == RED_PROJ && W >= 9) return MT == 8 ? (NTRSM > 0 ? 3 : 4) : MT == 4 && NTRSM == 0 ? 5 : 1;
-    if (RED == RED_SKETCH_SPARSE && !UPD) return MT == 4 ? (W <= 6 ? 6 : W <= 9 ? 5 : 1) : (W <= 10 ? 4 : 1);
-    return 1;
-}
-
 template <int W, typename T, int RED, bool UPD, int NTRSM, bool WRITE, int MTX = 0>
-__global__ void __launch_bounds__((Cfg<W, RED>::NT), (min_waves<W, T, RED, UPD, NTRSM, MTX>())) pass_kernel(const PassArgs a) {
+__global__ void __launch_bounds__((Cfg<W, RED>::NT)) pass_kernel(const PassArgs a) {
     pass_body<W, Tys<T, T, T>, RED, UPD, NTRSM, WRITE, MTX>(a, blockIdx.x, gridDim.x);
 }
 
@@ -881,7 +868,7 @@ __global__ void __launch_bounds__((Cfg<W, RED>::NT)) pass_kernel_panel(const Pas
 
 // Batched form: the template arguments are moved to the system of blockIdx.y.
 template <int W, typename T, int RED, bool UPD, int NTRSM, bool WRITE, int MTX = 0>
-__global__ void __launch_bounds__((Cfg<W, RED>::NT), (min_waves<W, T, RED, UPD, NTRSM, MTX>())) pass_kernel_batched(const PassArgs t, const BatchReloc br) {
+__global__ void __launch_bounds__((Cfg<W, RED>::NT)) pass_kernel_batched(const PassArgs t, const BatchReloc br) {
     const int sys = batch_system(br);
     const BatchSys& d = br.sys[sys];
     PassArgs a = t;
@@ -946,13 +933,7 @@ KernelPtr select_w(const PassKey& k) {
         if (r == RED_SKETCH_DENSE) return &pass_kernel<W, T, RED_SKETCH_DENSE, true, 0, true>;
     }
     if (!u && t == 1 && !wr && r == RED_GRAM) return &pass_kernel<W, T, RED_GRAM, false, 1, false>;
-    if (!u && t == 2 && wr) {
-        if (r == RED_PROJ)
-            return mt == 4   ? &pass_kernel<W, T, RED_PROJ, false, 2, true, 4>
-                   : mt == 6 ? &pass_kernel<W, T, RED_PROJ, false, 2, true, 6>
-                             : &pass_kernel<W, T, RED_PROJ, false, 2, true>;
-        if (r == RED_GRAM) return &pass_kernel<W, T, RED_GRAM, false, 2, true>;
-    }
+    if (!u && t == 2 && wr && r == RED_GRAM) return &pass_kernel<W, T, RED_GRAM, false, 2, true>;
     if (r == RED_NONE && t == 1 && wr) {
         if (!u) return &pass_kernel<W, T, RED_NONE, false, 1, true>;
         return &pass_kernel<W, T, RED_NONE, true, 1, true>;
