@@ -178,10 +178,9 @@ struct Engine {
         return SKO_OK;
     }
 
-    // X = (Y - Qu Cu) R^{-1} (rowop) and, in the same sweep over X, C = E^T X (E: me <= 64
-    // tall columns, solve only) or the Gram X^T X (E null), reduced into `small` as
-    // gemm_reduction does.  An update without a solve takes the MFMA update kernel with its
-    // Gram matrix (36 columns on 36, n = 2^24: 2.77 ms in one sweep, 3.34 + 1.11 ms as the row
+    // X = Y R^{-1} or X = Y - Qu Cu (rowop: one of the two) and, in the same sweep over X, C = E^T X (E:
+    // me <= 64 tall columns, solve only) or the Gram X^T X (E null), reduced into `small` as
+    // gemm_reduction does.  An update takes the MFMA update kernel with its Gram matrix (36 columns on 36, n = 2^24: 2.77 ms in one sweep, 3.34 + 1.11 ms as the row
     // operation and a Gram sweep).  Row solves wider than kFusedMaxW
     // keep the two sweeps apart (the row and the accumulators no longer fit two waves'
     // registers), and so do projections on more than 48 columns.  Rpk2: a second factor; X null:

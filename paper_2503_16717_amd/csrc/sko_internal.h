@@ -264,9 +264,9 @@ hipError_t launch_wide_update(int64_t n, int W, bool f32, const void* Y, int64_t
                               int p, const double* C, void* X, int64_t ldx, double* partials, int* grid,
                               hipStream_t stream, const BatchReloc* br = nullptr);
 
-// Row-wise X = (Y - Qu Cu) * R^{-1} for wide blocks (w <= 64); used by the big-panel
-// close of the two-stage scheme.  Rpk is R in the packed form of SmallArgs::Rpk (null: no
-// solve); Rpk2 and Rpk3 (W <= kFusedMaxW, no update, one system) are solved with after it.  pw (here
+// Row-wise X = Y R^{-1} or (pu > 0, no factor) X = Y - Qu Cu for wide blocks (w <= 64); used by the
+// big-panel close of the two-stage scheme.  Rpk is R in the packed form of SmallArgs::Rpk; Rpk2
+// and Rpk3 (W <= kFusedMaxW, one system) are solved with after it.  pw (here
 // and above, FP32 storage; one system, no update): panel width of Rpk's columns, whose values are
 // rounded to FP32 panel by panel.
 hipError_t launch_wide_rowop(int64_t n, int W, bool f32, const void* Y, int64_t ldy,

@@ -1,9 +1,9 @@
 // Kernels for wide blocks (up to 64 columns): the big panels of the two-stage scheme
 // (Figs. 5 and 6: CholQR of the big panel, BCGS against the previous big panels).
 //
-//  wide_rowop   X = (Y - Qu Cu) R^{-1} row by row, one row per thread, the row kept in
-//               registers (compile-time maximum width, runtime width); R and Cu are read
-//               through the scalar cache.  R comes packed (reciprocal diagonal, then the
+//  wide_rowop   X = Y R^{-1} [R2^{-1} [R3^{-1}]] or X = Y - Qu Cu row by row, one row per thread, the
+//               row kept in registers (compile-time maximum width, runtime width); R and Cu are read
+//               through the scalar cache (the update where it exceeds wide_update_fits).  R comes packed (reciprocal diagonal, then the
 //               strictly upper columns back to back): for 61 columns that is 14.6 KB, which
 //               the scalar cache holds, where the column-major square spans 18.6 KB of lines
 //               and a strip's sweep over it would miss on every chunk.
@@ -202,10 +202,8 @@ void rowop_launch(const RowopArgs& ra, hipStream_t st, const BatchReloc* br) {
 template <int WB, typename T>
 hipError_t rowop_dispatch(const RowopArgs& ra, hipStream_t st, const BatchReloc* br) {
     if (sizeof(T) == 4 && ra.pw > 0 && (ra.pu > 0 || br)) return hipErrorInvalidValue;  // compiled without PW
-    if (ra.pu > 0 && ra.Rpk2) return hipErrorInvalidValue;
-    if (ra.pu > 0 && ra.Rpk)
-        rowop_launch<WB, T, true, 1>(ra, st, br);
-    else if (ra.pu > 0)
+    if (ra.pu > 0 && ra.Rpk) return hipErrorInvalidValue;  // an update or solves, not both
+    if (ra.pu > 0)
         rowop_launch<WB, T, true, 0>(ra, st, br);
     else if (ra.Rpk && !ra.Rpk2) {
         if constexpr (sizeof(T) == 4) {
