@@ -1015,6 +1015,7 @@ sko_status gmres_batched_impl(sko_ctx c, int32_t nsys, const sko_csr* A, const d
             d.dia = dia[i].val;
             d.ldd = dia[i].ld;
             d.nd = dia[i].nd;
+            static_assert(sizeof(BatchSys::off) == sizeof(DiaView::off), "a system's table row holds every diagonal");
             std::copy(dia[i].off, dia[i].off + kMaxDiags, d.off);
         } else if (own_vals) {
             d.val_op = ar.at<void>(o_val[i]);

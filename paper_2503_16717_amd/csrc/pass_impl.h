@@ -470,7 +470,7 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
                         for (int j = 0; j < a.pu; ++j) {
                             const double q = ldv(Q + (int64_t)j * a.ldqu);
 #pragma unroll
-                            for (int c = 0; c < W; ++c) x[0][c] -= q * gC[j + c * a.pu];
+                            for (int c = 0; c < W; ++c) x[0][c] -= q * gC[j + c * ldcu];
                         }
                     }
                 }
