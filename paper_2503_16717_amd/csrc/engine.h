@@ -180,7 +180,11 @@ struct Engine {
 
     // X = Y R^{-1} or X = Y - Qu Cu (rowop: one of the two) and, in the same sweep over X, C = E^T X (E:
     // me <= 64 tall columns, solve only) or the Gram X^T X (E null), reduced into `small` as
-    // gemm_reduction does.  An update takes the MFMA update kernel with its Gram matrix (36 columns on 36, n = 2^24: 2.77 ms in one sweep, 3.34 + 1.11 ms as the row
+    // gemm_reduction does.  An update takes the MFMA update kernel with its Gram matrix (FP32 panels
+    // of more than 48 columns two sweeps: with four tiles of accumulators one wave per SIMD is left,
+    // and FP32 has the fewer bytes to save; two-stage step of two big panels, 2^21 rows, fused |
+    // apart: 48 columns 4.49 | 4.53 ms, 52 5.83 | 5.72, 56 6.32 | 6.23; FP64 5.97 | 6.14, 6.93 | 7.02,
+    // 7.50 | 7.59) (36 columns on 36, n = 2^24: 2.77 ms in one sweep, 3.34 + 1.11 ms as the row
     // operation and a Gram sweep).  Row solves wider than kFusedMaxW
     // keep the two sweeps apart (the row and the accumulators no longer fit two waves'
     // registers), and so do projections on more than 48 columns.  Rpk2: a second factor; X null:
@@ -188,7 +192,7 @@ struct Engine {
     sko_status rowop_reduction(int Wd, const void* Y, int64_t ldy, const void* Qu, int64_t ldqu, int pu,
                                const double* Cu, const double* Rpk, void* X, int64_t ldx, const void* E, int64_t lde,
                                int me, SmallArgs small, int64_t ldo, const double* Rpk2 = nullptr, int pw = 0) {
-        if (pu > 0 && !Rpk && !E && wide_update_fits(Wd, pu, true)) {
+        if (pu > 0 && !Rpk && !E && (!f32 || Wd <= 48) && wide_update_fits(Wd, pu, true)) {
             int G = br ? (int)std::max<int64_t>(1, std::min<int64_t>(gemm_grid(true, Wd, Wd),
                                                                      (n + kUpdateUnitRows - 1) / kUpdateUnitRows))
                        : 0;

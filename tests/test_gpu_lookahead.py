@@ -128,3 +128,25 @@ def test_two_stage_panel_widths(B, ctx, w, ppb, nb, n, reorth):
     assert metrics.backward_error(V, Q, R) <= 1e-14
     if reorth:
         assert metrics.orth_error(Q)[0] <= 1e-13
+
+
+# big panels of 48 columns fuse the update with its Gram matrix, wider FP32 ones do not
+@pytest.mark.parametrize("w,ppb,fused", [(12, 4, True), (13, 4, False), (14, 4, False)])
+@pytest.mark.parametrize("n", [1003, 6000])
+def test_two_stage_mixed_wide_panels(B, ctx, w, ppb, fused, n):
+    nb, u32 = 2 * ppb, 2.0 ** -24
+    V = wl.glued_blocks(n, nb, w, 1.0)
+    Vd = B.colmajor_from_numpy(V, "cuda", dtype=torch.float32)
+    ctx.sko_profile_enable(True)
+    Q, R, st, col = ctx.orth_blocks(Vd, w, two_stage=True, panels_per_big=ppb, precision="mixed",
+                                    sketch=B.make_sketch("sparse_sign", 128, 8, 2))
+    names = [s["name"] for s in ctx.sko_profile_read()]
+    ctx.sko_profile_enable(False)
+    assert st == B.SKO_OK, (st, col)
+    assert any(s.startswith("wide_update+gram") for s in names) == fused
+    # Q is rounded to FP32 entry by entry: ||I - Q^T Q|| <= 2 u32 ||Q||_F, ||V - Q R||_F <= u32 ||Q||_F ||R||_2 to
+    # first order (V_hat and V_bar are rounded once each before it: bounds doubled)
+    Q = Q.double().cpu().numpy()
+    assert metrics.orth_error(Q)[0] <= 4 * u32 * np.sqrt(nb * w)
+    V = Vd.double().cpu().numpy()
+    assert np.linalg.norm(V - Q @ R) <= 4 * u32 * np.sqrt(nb * w) * np.linalg.norm(R, 2)
