@@ -268,3 +268,33 @@ def test_short_solves_keep_csr(B, ctx):
     sk = B.make_sketch("sparse_sign", 64, 8, 1)
     for s, maxiter, name in ((3, 3, "spmv f64"), (3, 4, "spmv dia f64"), (4, 1, "spmv dia f64"), (1, 3, "spmv f64")):
         assert list(spmv_kernels(ctx, lambda: ctx.gmres(A, b, s=s, m=4 * s, tol=1e-14, maxiter=maxiter, sketch=sk), 1)) == [name]
+
+
+BY_DIAGONALS = {"1 diagonal", "3 diagonals", "upper only", "16 diagonals", "a few gaps"}
+
+
+@pytest.mark.parametrize("name", CASES)
+@pytest.mark.parametrize("precision", ["f64", "mixed"])
+@pytest.mark.parametrize("scheme", ["one-stage", "two-stage"])
+def test_every_form_solves(B, ctx, name, precision, scheme):
+    """The structures of CASES with a main diagonal that varies (no early end of the Krylov space): the
+    expected form runs, and the residual is checked for every one of them."""
+    n, offs, drop = CASES[name]
+    A = with_values(n, offs, len(name))
+    if drop:
+        r = np.random.default_rng([23, len(name)])
+        S = A.to_scipy().tocoo()
+        keep = (S.row == S.col) | (r.uniform(size=S.nnz) >= drop)
+        import scipy.sparse as sp
+        S = sp.csr_matrix((S.data[keep], (S.row[keep], S.col[keep])), shape=S.shape)
+        S.sort_indices()
+        A = wl.CSR(n, S.indptr.astype(np.int64), S.indices, S.data)
+    b = wl.rhs_uniform(n, 3)
+    kw = dict(s=4, m=12, precision=precision, tol=1e-8, maxiter=2000, sketch=B.make_sketch("sparse_sign", 64, 8, 1))
+    if scheme == "two-stage":
+        kw.update(two_stage=True, shat=12)
+    names = list(spmv_kernels(ctx, lambda: ctx.gmres(A, b, **kw), 1))
+    assert len(names) == 1 and names[0].startswith("spmv dia ") == (name in BY_DIAGONALS), names
+    x, info, st = ctx.gmres(A, b, **kw)
+    assert st == B.SKO_OK, (st, info)
+    assert np.linalg.norm(b - A.to_scipy() @ x.cpu().numpy()) / np.linalg.norm(b) <= 1e-8
