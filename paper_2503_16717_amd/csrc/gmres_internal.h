@@ -31,7 +31,10 @@ constexpr int kScanWords = 2 + kMaxDiags;
 // Diagonals of a scanned matrix (ascending in d.off, d.nd of them); false where diagonal storage
 // does not pay: eb bytes a value on every row and diagonal against the CSR form's values,
 // column indices and row pointers.  A 7-point stencil moves 56 + 16 bytes per row instead of
-// 88 + 16 (FP64), a matrix with many part-filled diagonals would move more.
+// 88 + 16 (FP64), a matrix with many part-filled diagonals would move more.  The line lies at 0.85 of
+// the CSR bytes: an SpMV still gains beyond it at 2^20 rows (us, CSR | diagonals, FP64: 9 diagonals at
+// 0.87 30.6 | 21.0, 13 at 1.02 34.2 | 27.6) but not at 2^16 (13 at 1.02 6.5 | 7.1), the storage grows
+// with it, and so does the set-up.
 bool scan_diagonals(const int32_t* words, int64_t n, int64_t nnz, int eb, DiaView& d);
 
 // CSR operand: structure + FP64 values of A (explicit residual) and the values used by

@@ -16,8 +16,9 @@
 //    LDS, and issues 4 MFMAs per tile.  A 16 x 16 accumulator is 4 doubles per lane, so one
 //    launch covers up to 16 * MT output rows; the waves' tiles are summed through LDS once
 //    at the end.
-//  * Gram x^T x: lanes own strip rows, waves own output rows, FP64 FMAs into register
-//    accumulators.
+//  * Gram x^T x: blocks of up to 8 columns on FP64 FMAs (lanes own strip rows, waves own output
+//    rows, register accumulators), wider ones and the two-block passes on MFMA tiles with both
+//    operands from LDS.
 //
 // Every tall operand is read from HBM once per pass; partial sums stay in registers for the
 // whole sweep and are written once per workgroup at the end.
@@ -34,8 +35,11 @@ typedef double double4_t __attribute__((ext_vector_type(4)));
 
 // Block width from which the Gram matrix runs on MFMA tiles: below, the vector form's W / 4
 // accumulator rows per wave are few; at 11 columns they take 66 VGPRs and 14 LDS reads per 64
-// rows and wave (FP64 after one solve, 1 000 003 rows: 36.8 us vector, 21.6 us MFMA; FP32 behind
-// the update on 66 columns, 2^24 rows: 1.35 and 1.27 ms).
+// rows and wave.  us, vector | MFMA: after one solve, FP64, 2^22 rows: 7 columns 55 | 47, 8 61 | 54, 9 69 | 61,
+// 11 82 | 69, 16 151 | 100; 300 007 rows: 8 18.7 | 9.7, 11 27.9 | 11.5.  Behind two solves and the update of a
+// block, FP32, 2^22 rows: 8 columns 180 | 170, 9 222 | 241, 10 242 | 249, 11 327 | 301, 12 251 | 205, 16 399 | 268;
+// 300 007 rows: 8 27 | 19, 9 38 | 27, 11 49 | 31.  (7 and 8 columns would gain too; at 9 and 10 the small row
+// counts decide.)
 constexpr int kGramMfmaW = 9;
 
 // Per-(width, reduction) launch configuration.
@@ -56,7 +60,8 @@ struct Cfg {
     static constexpr int ROWS = MF ? 16 * MT : NWAVE * MAXA;
 };
 
-// The tall operands stream through a pass once: loads and stores are non-temporal.
+// The tall operands stream through a pass once: loads and stores are non-temporal (the two-row
+// forms' 8-byte accesses are ordinary ones).
 template <typename T>
 __device__ __forceinline__ double ldv(const T* p) {
     return static_cast<double>(__builtin_nontemporal_load(p));
@@ -208,6 +213,9 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
                          (RED == RED_GRAM && W >= kGramMfmaW && (!F32 || UPD || PAIR == SOLO_UPD));
     constexpr int WS = PAIR == PAIR_CROSS ? 2 * W : WR;
     constexpr int GA0 = PAIR == PAIR_CROSS ? W : 0;  // staged column of the Gram's first row
+    // (one in the two-block and solve-first passes of float blocks up to 8 columns too: fewer bytes in
+    // flight per thread than with two rows, but two columns of traffic less; orth_blocks of 12 x 4, 12 x 6
+    // and 8 x 8 FP32 columns, 2^24 rows: 17.2, 27.4, 18.8 ms; block by block with two rows 21.7, 34.3, 24.2)
     constexpr int RPT = PAIR != PAIR_NONE ? 1 : (F32 && (W <= 8 || (NTRSM == 0 && !UPD))) ? 2 : 1;
     constexpr int STRIP = NT * RPT;
     constexpr int RPL = STRIP / 64;
@@ -227,7 +235,9 @@ __device__ __forceinline__ void pass_body(const PassArgs& a, const int wg, const
     __shared__ __align__(16) XS xs[HAS_RED ? WS * LDX : 1];
     __shared__ uint64_t hs[RED == RED_SKETCH_SPARSE ? STRIP : 1];
     // two-block projections of 16 to 24 columns: one 16 x 16 x 4 tile column for the first 16, 4 x
-    // 4 x 4 blocks for the others (a B operand register per row and 16 columns instead of four)
+    // 4 x 4 blocks for the others (a B operand register per row and 16 columns instead of four).
+    // us on up to 64 columns, FP32, 2^22 rows, blocks | tile and blocks: two blocks of 8 197 | 146, 9 202 | 197,
+    // 10 215 | 192, 12 290 | 236; FP64 the same within 1 % at every width
     constexpr bool HYB = PAIR == PAIR_PROJ && WR >= 16;
     constexpr int C16 = HYB ? 16 : 0;           // columns on 16 x 16 x 4
     constexpr int CB = (WR - C16 + 3) / 4;      // 4-column blocks

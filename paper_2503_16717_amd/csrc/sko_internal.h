@@ -49,7 +49,10 @@ enum PairKind : int {
     SOLO_UPD = 5,   // x R1^{-1} R2^{-1} - Qu Cu -> X; reduces x^T x
     PAIR_CROSS = 6, // (FP32) x R1^{-1} -> X; y as it is; reduces x^T y
 };
-constexpr int kMaxPairW = 12;  // block width up to which the two-block passes exist
+// Block width up to which the two-block passes exist.  Wider blocks go one at a time: two of 14
+// columns exceed the 64 KiB of static LDS.  (13 columns fit and would gain: 8 blocks, 2^22 rows, FP64
+// 15.07 ms one at a time, 13.49 ms looking ahead.)
+constexpr int kMaxPairW = 12;
 
 struct PassArgs {
     int64_t n;
