@@ -6,19 +6,21 @@
 // double storage; not for wide float blocks with triangular solves, which would not fit the
 // registers): the rows are loaded with coalesced accesses, updated, triangular-solved
 // and written back; the result is staged in LDS column-major (padded leading dimension,
-// so column reads across lanes do not collide in the LDS banks).  Phase B computes the pass's one reduction from the staged strip:
+// so column reads across lanes do not collide in the LDS banks).  Phase B computes the pass's
+// one reduction from the staged strip:
 //
-//  * projection Q^T x and the sketches Theta^T x: FP64 MFMA (v_mfma_f64_16x16x4) tiles of
-//    16 output rows.  The waves split the strip's 16-row groups; per group every lane
-//    supplies 4 consecutive rows of one output row's operand (Q and a dense Theta are read
-//    as one 32-byte piece per lane, so 16 lanes use each 128-byte line whole; the
-//    sparse-sign Theta is decoded from the rows' hashes) and the matching 4 rows of x from
-//    LDS, and issues 4 MFMAs per tile.  A 16 x 16 accumulator is 4 doubles per lane, so one
-//    launch covers up to 16 * MT output rows; the waves' tiles are summed through LDS once
-//    at the end.
-//  * Gram x^T x: blocks of up to 8 columns on FP64 FMAs (lanes own strip rows, waves own output
-//    rows, register accumulators), wider ones and the two-block passes on MFMA tiles with both
-//    operands from LDS.
+//  * projection Q^T x and the dense sketch Theta^T x: FP64 MFMA tiles of 16 output rows
+//    (v_mfma_f64_16x16x4, for up to 12 columns v_mfma_f64_4x4x4).  The waves split the strip's
+//    16-row groups; per group every lane supplies 4 consecutive rows of one output row's operand
+//    (Q or Theta, read as one 32-byte piece per lane, so 16 lanes use each 128-byte line whole)
+//    and the matching 4 rows of x from LDS, and issues 4 MFMAs per tile.  A 16 x 16 accumulator
+//    is 4 doubles per lane, so one launch covers up to 16 * MT output rows; the waves' tiles are
+//    summed through LDS once at the end.
+//  * sparse-sign sketch: no MFMA; every lane owns one or two sketch rows and adds the staged rows
+//    that the masks built from the rows' hashes select for it.
+//  * Gram x^T x: blocks of up to 8 columns, and wider FP32 ones without an update, on FP64 FMAs
+//    (lanes own strip rows, waves own output rows, register accumulators); the others and the
+//    two-block passes on MFMA tiles with both operands from LDS.
 //
 // Every tall operand is read from HBM once per pass; partial sums stay in registers for the
 // whole sweep and are written once per workgroup at the end.
